@@ -179,12 +179,10 @@ struct Tree {
     DevBuf w_fr, w_fr2, w_cnt, w_off, w_tg, w_sr, w_fl, w_c;  // walk and list-building scratch
     DevBuf w_state, w_res, w_dec; // device-side walk counters, list totals, pair decisions
     DevBuf w_geo, w_top;          // per node, packed for the walk (COM + r_max; children, level)
-    DevBuf w_pst;                 // tile status words of the fused frontier passes
-    uint32_t w_epoch = 0;         // epoch of the last fused pass (tags its status words)
     // sizes seen by the previous walk of this tree (capacity hints for the
     // passes that run without host synchronisation; 0 = none yet)
     int64_t walk_hint_fr = 0, walk_hint_far = 0, walk_hint_near = 0;
-    std::vector<int64_t> walk_hint_nf;  // frontier size of every pass
+    std::vector<int64_t> walk_hint_nf;  // frontier entries of every pass
     // near-field work items: a target leaf's list cut into pieces of bounded
     // source count, each run by one wavefront into its own partial sums
     int64_t n_items = 0, n_partial = 0;
@@ -232,9 +230,6 @@ struct Tree {
 };
 
 // ---- scans (scan.hip) -----------------------------------------------------
-struct U3 {
-    uint32_t a, b, c;
-};
 size_t scan_scratch_bytes(int64_t n);
 // Exclusive scan of n values (in == out allowed); writes the total to
 // *total_dev (device).

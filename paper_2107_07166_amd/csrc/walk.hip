@@ -1,20 +1,26 @@
 // Mutual dual-tree walk and per-target interaction lists.
 //
-// The walk processes a frontier of unordered node pairs level-synchronously
-// from (root, root) (one such pair per set of a forest; the children of a
-// pair belong to its set, so nodes of different sets never meet, and each
-// set may have its own theta).  For each pair:
+// The walk decides unordered node pairs level-synchronously from (root, root)
+// (one such pair per set of a forest; the children of a pair belong to its
+// set, so nodes of different sets never meet, and each set may have its own
+// theta).  For each pair:
 //   A == B : a leaf gives a near (P2P) self pair; otherwise the children
-//            pairs (c_i, c_j), i <= j, join the next frontier;
+//            pairs (c_i, c_j), i <= j, are decided in the next pass;
 //   A != B : R = sqrt((dx*dx + dy*dy) + dz*dz), d = Z_A - Z_B.  The pair is a
 //            far (M2L) pair iff R > 0 and r_A + r_B <= theta * R
 //            (Eq. mac_criterion with theta = tan of the MAC angle); else two
 //            leaves give a near pair; else one node is split (the non-leaf
 //            if one is a leaf, else the larger r_max, then the lower level,
 //            then the lower index) and its children are paired with the other.
-// Counts are compacted with prefix sums, so the emitted lists are in a fixed
-// order and the pair sets do not depend on scheduling.  FP64 without
-// contraction so that every decision is reproducible.
+// A pass's frontier holds runs of sibling pairs: entry (f, O) stands for the
+// pairs of O with node f and every later sibling of f.  A split gives one
+// entry, a self pair one per child c_i (the run from c_i against c_i).
+// Eight lanes take an entry, one pair each, so sibling records are read
+// together and only the split pairs, about one in six, are written and read
+// back.  Counts are compacted with prefix sums, so the emitted lists are in a
+// fixed order (the frontier's, pass after pass) and the pair sets do not
+// depend on scheduling.  FP64 without contraction so that every decision is
+// reproducible.
 #pragma clang fp contract(off)
 
 #include <algorithm>
@@ -28,12 +34,14 @@ namespace {
 constexpr int TB = 256;
 
 // Per node, packed for the walk: geo = (centre of mass x, y, z, r_max),
-// top = (child count, level, first child, set).  theta: per set (forests
-// walked with several thetas), else nullptr and the passes' scalar applies.
+// top = (child count + 16 x the siblings from this node to its last, level,
+// first child, set).  theta: per set (forests walked with several thetas),
+// else nullptr and the passes' scalar applies.
 struct WalkNodes {
-    const double4* geo;
-    const int4* top;
+    const double4* __restrict__ geo;
+    const int4* __restrict__ top;
     const double* theta;
+    int32_t nn;
 };
 
 __global__ __launch_bounds__(TB) void walk_nodes_kernel(int64_t nn, const double4* __restrict__ Z,
@@ -41,6 +49,7 @@ __global__ __launch_bounds__(TB) void walk_nodes_kernel(int64_t nn, const double
                                                         const int32_t* __restrict__ nchild,
                                                         const int32_t* __restrict__ level,
                                                         const int32_t* __restrict__ child_first,
+                                                        const int32_t* __restrict__ parent,
                                                         const int32_t* __restrict__ first,
                                                         const int64_t* __restrict__ set_off, int n_sets,
                                                         double4* __restrict__ geo, int4* __restrict__ top) {
@@ -48,60 +57,119 @@ __global__ __launch_bounds__(TB) void walk_nodes_kernel(int64_t nn, const double
     if (i >= nn) return;
     const double4 z = Z[i];
     geo[i] = make_double4(z.x, z.y, z.z, rmax[i]);
-    top[i] = make_int4(nchild[i], level[i], child_first[i], set_of(set_off, n_sets, first[i]));
+    const int32_t P = parent[i];
+    const int sib = P < 0 ? 1 : (int)(child_first[P] + nchild[P] - (int32_t)i);
+    top[i] = make_int4(nchild[i] | (sib << 4), level[i], child_first[i], set_of(set_off, n_sets, first[i]));
 }
 
-struct Decision {
-    int kind;      // 0 near, 1 far, 2 expand self, 3 split S against O
-    int32_t S, O;  // for kind 3
-    uint32_t nnew;
+constexpr int kRun = 8;  // lanes per frontier entry: the most siblings
+
+// The records of the pair of this lane, node A = f + x of entry (f, O) with x =
+// lane % kRun.  All five are read at once, also where the run is shorter than x
+// (the node index is kept in range) or the pair is a self pair: the passes are
+// bound by the latency of these reads, and with the tests in between they were
+// four round trips instead of one.
+struct PairRecords {
+    int32_t A, O;
+    int sib;  // nodes in the run (0 past the frontier's end)
+    int4 ta, to;
+    double4 ga, go;
 };
 
-__device__ __forceinline__ Decision decide(const WalkNodes& w, int32_t A, int32_t B, double theta) {
-    Decision d{0, -1, -1, 0u};
-    const int4 ta = w.top[A];
-    if (A == B) {
-        const int32_t nc = ta.x;
-        if (nc == 0) {
-            d.kind = 0;
-        } else {
-            d.kind = 2;
-            d.nnew = (uint32_t)(nc * (nc + 1) / 2);
-        }
-        return d;
-    }
-    const int4 tb = w.top[B];
-    const double4 ga = w.geo[A], gb = w.geo[B];
-    const double dx = ga.x - gb.x, dy = ga.y - gb.y, dz = ga.z - gb.z;
-    const double R = sqrt((dx * dx + dy * dy) + dz * dz);
-    const double ra = ga.w, rb = gb.w;
-    const double th = w.theta ? w.theta[ta.w] : theta;
-    if (R > 0.0 && ra + rb <= th * R) {
-        d.kind = 1;
-        return d;
-    }
-    const int32_t na = ta.x, nb = tb.x;
-    if (na == 0 && nb == 0) {
-        d.kind = 0;
-        return d;
-    }
-    int32_t S;
-    if (na == 0) S = B;
-    else if (nb == 0) S = A;
-    else if (ra > rb) S = A;
-    else if (rb > ra) S = B;
-    else if (ta.y < tb.y) S = A;
-    else if (tb.y < ta.y) S = B;
-    else S = A < B ? A : B;
-    d.kind = 3;
-    d.S = S;
-    d.O = (S == A) ? B : A;
-    d.nnew = (uint32_t)((S == A) ? na : nb);
-    return d;
+__device__ __forceinline__ PairRecords load_pair(const WalkNodes& w, bool valid, int2 e, int x) {
+    PairRecords r;
+    const int32_t last = w.nn - 1;
+    r.A = e.x + x;
+    r.O = e.y;
+    const int32_t A = r.A < last ? r.A : last;
+    const int sib = w.top[e.x].x >> 4;
+    r.ta = w.top[A];
+    r.to = w.top[r.O];
+    r.ga = w.geo[A];
+    r.go = w.geo[r.O];
+    r.sib = valid ? sib : 0;
+    return r;
 }
 
+// What becomes of a pair: bits 0-1 kind (0 near, 1 far, 2 expand self, 3
+// split), bit 2 set when the split node is O; -1 where there is no pair.
+__device__ __forceinline__ int decide(const WalkNodes& w, const PairRecords& r, int x, double theta) {
+    if (x >= r.sib) return -1;
+    const int na = r.ta.x & 15, no = r.to.x & 15;
+    if (r.A == r.O) return na == 0 ? 0 : 2;
+    const double dx = r.ga.x - r.go.x, dy = r.ga.y - r.go.y, dz = r.ga.z - r.go.z;
+    const double R = sqrt((dx * dx + dy * dy) + dz * dz);
+    const double ra = r.ga.w, ro = r.go.w;
+    const double th = w.theta ? w.theta[r.ta.w] : theta;
+    if (R > 0.0 && ra + ro <= th * R) return 1;
+    if (na == 0 && no == 0) return 0;
+    bool second;
+    if (na == 0) second = true;
+    else if (no == 0) second = false;
+    else if (ra != ro) second = ro > ra;
+    else if (r.ta.y != r.to.y) second = r.to.y < r.ta.y;
+    else second = r.O < r.A;
+    return second ? 7 : 3;
+}
 
+__device__ __forceinline__ uint64_t lanes_below() {
+    const int lane = threadIdx.x & (kWave - 1);
+    return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+}
+
+// Entries that a self pair adds: one per child.  Summed over the wavefront
+// (self pairs are rare), and over the lanes below this one.
+__device__ __forceinline__ uint32_t self_entries(int code, int nc, uint32_t& below) {
+    const int lane = threadIdx.x & (kWave - 1);
+    uint64_t m = __ballot(code == 2);
+    below = 0u;
+    uint32_t tot = 0u;
+    while (m) {
+        const int l = __ffsll((long long)m) - 1;
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane(nc, l);
+        if (l < lane) below += c;
+        tot += c;
+        m &= m - 1ull;
+    }
+    return tot;
+}
+
+struct U3 {
+    uint32_t a, b, c;  // next-frontier entries, far pairs, near pairs
+};
 __device__ __forceinline__ U3 u3add(U3 x, U3 y) { return {x.a + y.a, x.b + y.b, x.c + y.c}; }
+
+// Outputs of the wavefront's pairs and of the lanes below this one (nc: the
+// child count of the lane's split node).
+__device__ __forceinline__ U3 wave_counts(int code, int nc, U3& below) {
+    const uint64_t lt = lanes_below();
+    const uint64_t mn = __ballot(code == 0), mf = __ballot(code == 1), ms = __ballot((code & 3) == 3 && code >= 0);
+    const uint32_t self = self_entries(code, nc, below.a);
+    below.a += (uint32_t)__popcll(ms & lt);
+    below.b = (uint32_t)__popcll(mf & lt);
+    below.c = (uint32_t)__popcll(mn & lt);
+    return {(uint32_t)__popcll(ms) + self, (uint32_t)__popcll(mf), (uint32_t)__popcll(mn)};
+}
+
+// Writes the lane's output at its place (ts: the record of its split node);
+// sink(i, entry) takes a next-frontier entry.
+template <typename Sink>
+__device__ __forceinline__ void lane_emit(int code, int32_t A, int32_t O, const int4& ts, unsigned long long on,
+                                          unsigned long long ofar, unsigned long long onear, int2* __restrict__ far,
+                                          int2* __restrict__ near, Sink sink) {
+    const int2 pr = make_int2(A < O ? A : O, A < O ? O : A);
+    if (code == 0) {
+        near[onear] = pr;
+    } else if (code == 1) {
+        far[ofar] = pr;
+    } else if (code >= 0) {
+        if (code == 2) {
+            for (int c = 0; c < (ts.x & 15); ++c) sink(on + c, make_int2(ts.z + c, ts.z + c));
+        } else {
+            sink(on, make_int2(ts.z, code == 7 ? A : O));
+        }
+    }
+}
 
 // Pass totals are carried in 64 bits so that a pass too large for 32-bit
 // offsets is detected instead of wrapping.
@@ -110,30 +178,6 @@ struct U3L {
 };
 __device__ __forceinline__ U3L u3ladd(U3L x, U3 y) { return {x.a + y.a, x.b + y.b, x.c + y.c}; }
 __device__ __forceinline__ U3L u3ladd(U3L x, U3L y) { return {x.a + y.a, x.b + y.b, x.c + y.c}; }
-
-// Exclusive scan over the block (every thread calls it); the block total is
-// returned in tot.  The shared array may be reused right after the call.
-__device__ __forceinline__ U3 block_excl_scan(U3 c, U3* wsum, U3& tot) {
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    U3 v = c;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        U3 u{(uint32_t)__shfl_up(v.a, d, kWave), (uint32_t)__shfl_up(v.b, d, kWave),
-             (uint32_t)__shfl_up(v.c, d, kWave)};
-        if (lane >= d) v = u3add(v, u);
-    }
-    if (lane == kWave - 1) wsum[wv] = v;
-    __syncthreads();
-    U3 base{0u, 0u, 0u}, t{0u, 0u, 0u};
-#pragma unroll
-    for (int k = 0; k < TB / kWave; ++k) {
-        if (k < wv) base = u3add(base, wsum[k]);
-        t = u3add(t, wsum[k]);
-    }
-    __syncthreads();
-    tot = t;
-    return U3{base.a + v.a - c.a, base.b + v.b - c.b, base.c + v.c - c.c};
-}
 
 // Sum over the block (every thread calls it and gets the total).
 __device__ __forceinline__ U3L block_sum(U3L x, U3L* wsum) {
@@ -153,82 +197,183 @@ __device__ __forceinline__ U3L block_sum(U3L x, U3L* wsum) {
 }
 
 // ---- frontier passes ----------------------------------------------------------
-// A pass has two kernels (the unsynchronised walk fuses them for small
-// frontiers, below).  The counting kernel decides every frontier pair,
-// stores the decision and scans the output counts (next-frontier pairs, far
-// pairs, near pairs) inside its block; the emitting kernel adds the totals of
-// the blocks before it and writes the outputs.  Block b of a pass takes a
-// contiguous range of frontier tiles, so the outputs follow the frontier
-// order whatever the grid: children of a pair in a fixed order (a self pair
-// gives (c_a, c_b) for a <= b, row major; a split gives (c_a, O)).
-//
-// The frontier size and the running list lengths live on the device, double
-// buffered by pass parity (a pass reads slot p and writes slot 1 - p), so
-// passes can be queued without reading anything back.  A pass whose outputs
-// would not fit sets a sticky flag and writes nothing; later passes then see
-// an empty frontier.
+// The frontier's size and the running list lengths live on the device in two
+// slots (a launch reads one and writes the other), so launches can be queued
+// without reading anything back.  A pass whose outputs would not fit sets a
+// sticky flag and writes nothing; later passes then see an empty frontier.
 constexpr int kMaxPasses = 64;  // a walk needs at most 2 * 21 + 1 passes
+struct WalkSlot {
+    uint32_t nf, buf;  // frontier entries, and the buffer (0, 1) that holds them
+    unsigned long long n_far, n_near;
+};
 struct WalkState {
-    uint32_t nf[2];
+    WalkSlot slot[2];
     uint32_t overflow;
-    uint32_t passes;  // passes that found a non-empty frontier
+    uint32_t passes;  // passes run
     uint32_t max_nf;  // largest frontier seen
     uint32_t pad;
-    unsigned long long n_far[2], n_near[2];
-    uint32_t nf_pass[kMaxPasses];  // frontier size of every pass (sizes the next walk's grids)
-    uint32_t ticket[kMaxPasses];   // tile tickets of the fused passes
+    uint32_t nf_pass[kMaxPasses];  // frontier size of every pass (sizes the next walk's launches)
+};
+struct WalkOut {
+    int2* fr[2];  // frontier buffers
+    int2 *far, *near;
+    unsigned long long cap_next, cap_far, cap_near;
 };
 constexpr int kWalkGrid = 1024;
 
+// Whether a pass's totals T fit.
+__device__ __forceinline__ bool pass_fits(const WalkOut& o, const U3L& T, const WalkSlot& s) {
+    const unsigned long long lim = 0xffffffffull;
+    return T.a <= o.cap_next && T.b <= lim && T.c <= lim && s.n_far + T.b <= o.cap_far && s.n_near + T.c <= o.cap_near;
+}
+
+__device__ __forceinline__ void pass_done(WalkState* st, WalkSlot* out, const WalkSlot& s, const U3L& T) {
+    *out = WalkSlot{(uint32_t)T.a, s.buf ^ 1u, s.n_far + T.b, s.n_near + T.c};
+    if (st->passes < (uint32_t)kMaxPasses) st->nf_pass[st->passes] = s.nf;
+    st->passes += 1u;
+    if ((uint32_t)T.a > st->max_nf) st->max_nf = (uint32_t)T.a;
+}
+
+// Small passes, one after another, in a single workgroup: a pass of up to
+// limit entries is decided (the decisions kept in LDS), its counts scanned over
+// the wavefronts, and its outputs written, with two barriers and no launch in
+// between.  The frontier stays in LDS (and is written to memory too, for the
+// launch that takes over).  With init, starts from the pairs (k, k) of the
+// roots.  Stops when the frontier is empty or larger than limit.  A pass here
+// takes 5 to 9 us (latency: one workgroup cannot hide it), two launches of
+// their own 12 us and the gaps between them.  A small tree's walk is this one
+// launch: Plummer 10007, built and solved in one call, 1070 -> 711 us together
+// with the estimated room of a first walk.
+constexpr int SQ = 1024;          // threads
+constexpr int kSeqMax = 2048;     // most entries of a pass run here
+constexpr int kSeqHead = 1024;    // the walk's first passes go on here up to this
+__global__ __launch_bounds__(SQ) void walk_seq_kernel(WalkNodes w, WalkOut o, WalkState* __restrict__ st, int slot,
+                                                      int init, int n_roots, uint32_t limit, double theta) {
+    constexpr int NW = SQ / kWave;
+    constexpr int EPW = kWave / kRun;  // entries per wavefront and step
+    __shared__ int2 fr[2][kSeqMax];
+    __shared__ int8_t dec[kSeqMax * kRun];
+    __shared__ U3 wtot[NW];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, x = lane % kRun;
+    WalkSlot s;
+    if (init) {
+        s = WalkSlot{(uint32_t)n_roots, 0u, 0ull, 0ull};
+        for (int k = tid; k < n_roots; k += SQ) {
+            o.fr[0][k] = make_int2(k, k);
+            if (k < kSeqMax) fr[0][k] = make_int2(k, k);
+        }
+        if (tid < kMaxPasses) st->nf_pass[tid] = 0u;
+        if (tid == 0) {
+            st->overflow = 0u;
+            st->passes = 0u;
+            st->max_nf = (uint32_t)n_roots;
+            st->pad = 0u;
+        }
+    } else {
+        s = st->slot[slot];
+        if (st->overflow) s.nf = 0u;
+        if (s.nf <= limit)
+            for (uint32_t k = tid; k < s.nf; k += SQ) fr[0][k] = o.fr[s.buf][k];
+    }
+    __syncthreads();
+    int cur = 0;
+    while (s.nf > 0u && s.nf <= limit) {
+        // wavefront wv takes entries [e0, e1)
+        const uint32_t per = (s.nf + NW * EPW - 1) / (NW * EPW) * EPW;
+        const uint32_t e0 = wv * per < s.nf ? wv * per : s.nf, e1 = e0 + per < s.nf ? e0 + per : s.nf;
+        U3 c{0u, 0u, 0u};
+        for (uint32_t b = e0; b < e1; b += 2 * EPW) {  // two steps' reads in flight
+            const uint32_t ea = b + lane / kRun, eb = ea + EPW;
+            const int2 pa = fr[cur][ea < e1 ? ea : e0], pb = fr[cur][eb < e1 ? eb : e0];
+            const PairRecords ra = load_pair(w, ea < e1, pa, x), rb = load_pair(w, eb < e1, pb, x);
+            const int ca = decide(w, ra, x, theta), cb = decide(w, rb, x, theta);
+            if (ea < e1) dec[ea * kRun + x] = (int8_t)ca;
+            if (eb < e1) dec[eb * kRun + x] = (int8_t)cb;
+            U3 unused;
+            c = u3add(c, u3add(wave_counts(ca, ra.ta.x & 15, unused), wave_counts(cb, rb.ta.x & 15, unused)));
+        }
+        if (lane == 0) wtot[wv] = c;
+        __syncthreads();
+        U3 before{0u, 0u, 0u}, all{0u, 0u, 0u};
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            if (k < wv) before = u3add(before, wtot[k]);
+            all = u3add(all, wtot[k]);
+        }
+        const U3L T{all.a, all.b, all.c};
+        if (!pass_fits(o, T, s)) {
+            if (tid == 0) st->overflow = 1u;
+            s.nf = 0u;
+            break;
+        }
+        int2* nxt = o.fr[s.buf ^ 1u];
+        int2* nxt_lds = fr[cur ^ 1];
+        auto sink = [&](unsigned long long i, int2 e) {
+            nxt[i] = e;
+            if (i < kSeqMax) nxt_lds[i] = e;
+        };
+        unsigned long long on = before.a, of = s.n_far + before.b, onr = s.n_near + before.c;
+        for (uint32_t b = e0; b < e1; b += EPW) {
+            const uint32_t e = b + lane / kRun;
+            const int2 pr = e < e1 ? fr[cur][e] : make_int2(0, 0);
+            const int code = e < e1 ? (int)dec[e * kRun + x] : -1;
+            const int4 ts = code >= 2 ? w.top[code == 7 ? pr.y : pr.x + x] : make_int4(0, 0, 0, 0);
+            U3 lo;
+            const U3 k = wave_counts(code, ts.x & 15, lo);
+            lane_emit(code, pr.x + x, pr.y, ts, on + lo.a, of + lo.b, onr + lo.c, o.far, o.near, sink);
+            on += k.a;
+            of += k.b;
+            onr += k.c;
+        }
+        if (tid == 0) pass_done(st, &st->slot[slot ^ 1], s, T);  // the slot is rewritten below
+        s = WalkSlot{all.a, s.buf ^ 1u, s.n_far + all.b, s.n_near + all.c};
+        cur ^= 1;
+        __syncthreads();
+    }
+    if (tid == 0) st->slot[slot ^ 1] = s;
+}
+
+// Larger passes, two launches each.  The counting kernel decides every pair,
+// stores the decision and the block's output counts; the emitting kernel adds
+// the totals of the blocks before it and writes the outputs.  Block b of a
+// pass takes a contiguous range of tiles of TB / kRun entries, so the outputs
+// follow the frontier order whatever the grid.  Both are bound by the latency
+// of a tile's dependent reads: two tiles (the next tile, when writing) are in
+// flight per wavefront.  2^20 Plummer particles: the largest passes, 5e5
+// entries, take 18 and 24 us (with one pair per thread and frontier entry, all
+// pairs written and read back, 18 and 38), all passes 0.42 ms of kernels against
+// 0.54; steps 3.31 -> 3.13 ms.  Workgroups of 512 or 1024 threads, or 2048 of
+// them: 0-7 % slower steps.
 __device__ __forceinline__ void block_tiles(uint32_t nf, int64_t& t0, int64_t& t1) {
-    const int64_t tiles = ((int64_t)nf + TB - 1) / TB;
+    const int64_t tiles = ((int64_t)nf + TB / kRun - 1) / (TB / kRun);
     const int64_t per = (tiles + gridDim.x - 1) / gridDim.x;
     t0 = (int64_t)blockIdx.x * per;
     t1 = t0 + per < tiles ? t0 + per : tiles;
 }
 
-// The first frontier: (k, k) for the root k of every set.
-__global__ void walk_init_kernel(WalkState* __restrict__ st, int2* __restrict__ fr, int n_roots) {
-    if (threadIdx.x == 0) {
-        st->nf[0] = (uint32_t)n_roots;
-        st->nf[1] = 0u;
-        st->overflow = 0u;
-        st->passes = 0u;
-        st->max_nf = (uint32_t)n_roots;
-        st->pad = 0u;
-        st->n_far[0] = st->n_far[1] = 0ull;
-        st->n_near[0] = st->n_near[1] = 0ull;
-    }
-    for (int k = threadIdx.x; k < n_roots; k += blockDim.x) fr[k] = make_int2(k, k);
-    for (int k = threadIdx.x; k < kMaxPasses; k += blockDim.x) {
-        st->nf_pass[k] = 0u;
-        st->ticket[k] = 0u;
-    }
-}
-
-__global__ __launch_bounds__(TB) void zero_words_kernel(unsigned long long* __restrict__ p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TB) p[i] = 0ull;
-}
-
-// Decision code: bits 0-1 kind (0 near, 1 far, 2 expand self, 3 split);
-// bit 2 set when the split node is the pair's second node.
-__global__ __launch_bounds__(TB) void walk_count_pass_kernel(WalkNodes w, const int2* __restrict__ fr,
-                                                             const WalkState* __restrict__ st, int parity,
-                                                             double theta, uint8_t* __restrict__ dec,
-                                                             U3L* __restrict__ bsum) {
+__global__ __launch_bounds__(TB) void walk_count_kernel(WalkNodes w, WalkOut o, const WalkState* __restrict__ st,
+                                                        int slot, double theta, int8_t* __restrict__ dec,
+                                                        U3L* __restrict__ bsum) {
     __shared__ U3L wsum[TB / kWave];
-    const uint32_t nf = st->overflow ? 0u : st->nf[parity];
+    const WalkSlot s = st->slot[slot];
+    const uint32_t nf = st->overflow ? 0u : s.nf;
+    const int2* fr = o.fr[s.buf];
+    const int lane = threadIdx.x & (kWave - 1), x = lane % kRun;
     int64_t t0, t1;
     block_tiles(nf, t0, t1);
     U3L c{0ull, 0ull, 0ull};
-    const int64_t iend = t1 * TB < (int64_t)nf ? t1 * TB : (int64_t)nf;
-    for (int64_t i = t0 * TB + threadIdx.x; i < iend; i += TB) {
-        const int2 pr = fr[i];
-        const Decision d = decide(w, pr.x, pr.y, theta);
-        if (d.kind == 0) c.c += 1u;
-        else if (d.kind == 1) c.b += 1u;
-        else c.a += d.nnew;
-        dec[i] = (uint8_t)(d.kind | ((d.kind == 3 && d.S == pr.y) ? 4 : 0));
+    for (int64_t t = t0; t < t1; t += 2) {  // two tiles' reads in flight
+        const int64_t ia = t * TB + threadIdx.x, ib = ia + TB;
+        const int64_t ea = ia / kRun, eb = ib / kRun;
+        const bool va = ea < (int64_t)nf, vb = t + 1 < t1 && eb < (int64_t)nf;
+        const int2 pa = fr[va ? ea : 0], pb = fr[vb ? eb : 0];
+        const PairRecords ra = load_pair(w, va, pa, x), rb = load_pair(w, vb, pb, x);
+        const int ca = decide(w, ra, x, theta), cb = decide(w, rb, x, theta);
+        if (va) dec[ia] = (int8_t)ca;
+        if (vb) dec[ib] = (int8_t)cb;
+        U3 unused;
+        const U3 k = u3add(wave_counts(ca, ra.ta.x & 15, unused), wave_counts(cb, rb.ta.x & 15, unused));
+        if (lane == 0) c = u3ladd(c, k);
     }
     const U3L tot = block_sum(c, wsum);
     if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
@@ -245,302 +390,71 @@ __global__ __launch_bounds__(TB) void walk_total_kernel(const U3L* __restrict__ 
 }
 
 // Every block sums the block totals itself (the pass total and its own
-// offset), so no scan launch sits between counting and emitting; offsets
-// inside the block come from a scan of the counts, recomputed from the
-// stored decisions.
-__global__ __launch_bounds__(TB) void walk_emit_pass_kernel(WalkNodes w, const int2* __restrict__ fr,
-                                                            WalkState* __restrict__ st, int pass,
-                                                            const uint8_t* __restrict__ dec,
-                                                            const U3L* __restrict__ bsum,
-                                                            int2* __restrict__ next, int2* __restrict__ far,
-                                                            int2* __restrict__ near, uint32_t cap_next,
-                                                            unsigned long long cap_far,
-                                                            unsigned long long cap_near) {
-    __shared__ U3L wsum[TB / kWave];
-    __shared__ U3 wsum3[TB / kWave];
+// offset), so no scan launch sits between counting and emitting.
+__global__ __launch_bounds__(TB) void walk_emit_kernel(WalkNodes w, WalkOut o, WalkState* __restrict__ st, int slot,
+                                                       const int8_t* __restrict__ dec,
+                                                       const U3L* __restrict__ bsum) {
+    constexpr int NW = TB / kWave;
+    __shared__ U3L wsum[NW];
+    __shared__ U3 wtot[2][NW];
+    const WalkSlot s = st->slot[slot];
+    const uint32_t nf = st->overflow ? 0u : s.nf;
+    if (nf == 0u) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->slot[slot ^ 1] = WalkSlot{0u, s.buf, s.n_far, s.n_near};
+        return;
+    }
     U3L before{0ull, 0ull, 0ull}, all{0ull, 0ull, 0ull};
     for (int j = threadIdx.x; j < (int)gridDim.x; j += TB) {
-        const U3L x = bsum[j];
-        all = u3ladd(all, x);
-        if (j < (int)blockIdx.x) before = u3ladd(before, x);
+        const U3L v = bsum[j];
+        all = u3ladd(all, v);
+        if (j < (int)blockIdx.x) before = u3ladd(before, v);
     }
     const U3L T = block_sum(all, wsum);
     const U3L B = block_sum(before, wsum);
-    const int parity = pass & 1;
-    const uint32_t nf = st->overflow ? 0u : st->nf[parity];
-    const unsigned long long far0 = st->n_far[parity], near0 = st->n_near[parity];
-    const unsigned long long lim = 0xffffffffull;
-    const bool ovf = T.a > cap_next || T.b > lim || T.c > lim || far0 + T.b > cap_far || near0 + T.c > cap_near;
     const bool leader = blockIdx.x == 0 && threadIdx.x == 0;
-    if (ovf) {
+    if (!pass_fits(o, T, s)) {
         if (leader) {
             st->overflow = 1u;
-            st->nf[parity ^ 1] = 0u;
+            st->slot[slot ^ 1] = WalkSlot{0u, s.buf, s.n_far, s.n_near};
         }
         return;
     }
-    if (leader) {
-        st->nf[parity ^ 1] = (uint32_t)T.a;
-        st->n_far[parity ^ 1] = far0 + T.b;
-        st->n_near[parity ^ 1] = near0 + T.c;
-        if (nf > 0u) st->passes += 1u;
-        if ((uint32_t)T.a > st->max_nf) st->max_nf = (uint32_t)T.a;
-        if (pass < kMaxPasses) st->nf_pass[pass] = nf;
-    }
+    if (leader) pass_done(st, &st->slot[slot ^ 1], s, T);
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave, x = lane % kRun;
+    const int2* fr = o.fr[s.buf];
+    int2* nxt = o.fr[s.buf ^ 1u];
+    auto sink = [&](unsigned long long i, int2 e) { nxt[i] = e; };
     int64_t t0, t1;
     block_tiles(nf, t0, t1);
-    U3L carry = B;
+    U3L carry{B.a, s.n_far + B.b, s.n_near + B.c};
+    // the next tile's entry and decision are read while a tile is written
+    auto entry_at = [&](int64_t t, int& code) {
+        const int64_t i = t * TB + threadIdx.x, e = i / kRun;
+        const bool valid = t < t1 && e < (int64_t)nf;
+        code = valid ? (int)dec[i] : -1;
+        return fr[valid ? e : 0];
+    };
+    int code;
+    int2 pr = entry_at(t0, code);
     for (int64_t t = t0; t < t1; ++t) {
-        const int64_t i = t * TB + threadIdx.x;
-        int2 pr = make_int2(0, 0);
-        int kind = -1;
-        int32_t S = 0, O = 0, c0 = 0, nc = 0;
-        U3 c{0u, 0u, 0u};
-        if (i < (int64_t)nf) {
-            pr = fr[i];
-            const int code = dec[i];
-            kind = code & 3;
-            if (kind == 0) {
-                c.c = 1u;
-            } else if (kind == 1) {
-                c.b = 1u;
-            } else {
-                S = (kind == 3 && (code & 4)) ? pr.y : pr.x;
-                O = (S == pr.x) ? pr.y : pr.x;
-                const int4 tp = w.top[S];
-                c0 = tp.z;
-                nc = tp.x;
-                c.a = kind == 2 ? (uint32_t)(nc * (nc + 1) / 2) : (uint32_t)nc;
-            }
+        int code_next;
+        const int2 pr_next = entry_at(t + 1, code_next);
+        const int4 ts = code >= 2 ? w.top[code == 7 ? pr.y : pr.x + x] : make_int4(0, 0, 0, 0);
+        U3 pre;  // outputs before this lane's, of the tile
+        const U3 k = wave_counts(code, ts.x & 15, pre);
+        U3* wt = wtot[t & 1];  // the other half is still read by slower wavefronts
+        if (lane == 0) wt[wv] = k;
+        __syncthreads();
+        U3 tot{0u, 0u, 0u};
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            if (q < wv) pre = u3add(pre, wt[q]);
+            tot = u3add(tot, wt[q]);
         }
-        U3 tot;
-        const U3 e = block_excl_scan(c, wsum3, tot);
-        if (kind >= 0) {
-            const U3L o = u3ladd(carry, e);
-            const int32_t lo = pr.x < pr.y ? pr.x : pr.y, hi = pr.x < pr.y ? pr.y : pr.x;
-            if (kind == 0) {
-                near[near0 + o.c] = make_int2(lo, hi);
-            } else if (kind == 1) {
-                far[far0 + o.b] = make_int2(lo, hi);
-            } else if (kind == 2) {
-                int2* q = next + o.a;
-                for (int32_t x = 0; x < nc; ++x)
-                    for (int32_t y = x; y < nc; ++y) *q++ = make_int2(c0 + x, c0 + y);
-            } else {
-                int2* q = next + o.a;
-                for (int32_t x = 0; x < nc; ++x) q[x] = make_int2(c0 + x, O);
-            }
-        }
+        lane_emit(code, pr.x + x, pr.y, ts, carry.a + pre.a, carry.b + pre.b, carry.c + pre.c, o.far, o.near, sink);
         carry = u3ladd(carry, tot);
-    }
-}
-
-// ---- fused frontier pass ---------------------------------------------------
-// One kernel per pass for the unsynchronised walk: a block takes tiles of
-// kPassTile frontier pairs in ticket order, decides them, scans the three
-// output counts inside the block, and finds the counts of all earlier tiles
-// by decoupled look-back over per-tile status words (one word per count).
-// Outputs land in frontier order, exactly as with the two-kernel pass.
-// A status word holds (epoch << 44) | (flag << 42) | value; a word written by
-// another pass carries another epoch and reads as unpublished, so the words
-// need no clearing between passes.  The tile that comes last writes the pass
-// totals into the state; with an empty frontier block 0 does.
-constexpr int kPassPPT = 2;                    // consecutive pairs per thread
-constexpr int kPassTile = TB * kPassPPT;       // pairs per tile
-constexpr int kEpochBits = 20;
-constexpr unsigned long long kPstOwn = 1ull << 42;
-constexpr unsigned long long kPstTotal = 2ull << 42;
-constexpr unsigned long long kPstVal = (1ull << 42) - 1;
-constexpr uint32_t kPassSpinLimit = 1u << 20;
-constexpr int kPassGrid = 2048;                // blocks of a fused pass (at most)
-// Passes expected to hold at most this many pairs run fused.  Look-back over
-// many tiles costs more than the second launch saves, so larger passes keep
-// the two-kernel form.
-constexpr int64_t kFuseMaxPairs = 4096;
-
-__device__ __forceinline__ unsigned long long pst_word(uint32_t epoch, unsigned long long flag,
-                                                       unsigned long long v) {
-    return ((unsigned long long)epoch << 44) | flag | v;
-}
-
-__device__ __forceinline__ void pass_state_write(WalkState* st, int pass, uint32_t nf, U3L T,
-                                                 unsigned long long far0, unsigned long long near0,
-                                                 uint32_t cap_next, unsigned long long cap_far,
-                                                 unsigned long long cap_near) {
-    const int parity = pass & 1;
-    const unsigned long long lim = 0xffffffffull;
-    const bool ovf = T.a > cap_next || T.b > lim || T.c > lim || far0 + T.b > cap_far || near0 + T.c > cap_near;
-    if (ovf) {
-        st->overflow = 1u;
-        st->nf[parity ^ 1] = 0u;
-        return;
-    }
-    st->nf[parity ^ 1] = (uint32_t)T.a;
-    st->n_far[parity ^ 1] = far0 + T.b;
-    st->n_near[parity ^ 1] = near0 + T.c;
-    if (nf > 0u) st->passes += 1u;
-    if ((uint32_t)T.a > st->max_nf) st->max_nf = (uint32_t)T.a;
-    if (pass < kMaxPasses) st->nf_pass[pass] = nf;
-}
-
-__global__ __launch_bounds__(TB) void walk_pass_kernel(WalkNodes w, const int2* __restrict__ fr,
-                                                       WalkState* __restrict__ st, int pass, double theta,
-                                                       int2* __restrict__ next, int2* __restrict__ far,
-                                                       int2* __restrict__ near, uint32_t cap_next,
-                                                       unsigned long long cap_far, unsigned long long cap_near,
-                                                       unsigned long long* __restrict__ pst, uint32_t cap_tiles,
-                                                       uint32_t epoch, uint32_t* __restrict__ err) {
-    __shared__ U3 wsum[TB / kWave];
-    __shared__ uint32_t s_tile;
-    __shared__ unsigned long long s_pre[3];
-    const int parity = pass & 1;
-    const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t nf = st->nf[parity];
-    const unsigned long long far0 = st->n_far[parity], near0 = st->n_near[parity];
-    const uint32_t ntiles = (uint32_t)(((uint64_t)nf + kPassTile - 1) / kPassTile);
-    if (ntiles == 0u || ntiles > cap_tiles) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (ntiles == 0u) {
-                pass_state_write(st, pass, 0u, U3L{0ull, 0ull, 0ull}, far0, near0, cap_next, cap_far, cap_near);
-            } else {
-                st->overflow = 1u;
-                st->nf[parity ^ 1] = 0u;
-            }
-        }
-        return;
-    }
-    for (;;) {
-        if (threadIdx.x == 0) s_tile = atomicAdd(&st->ticket[pass], 1u);
-        __syncthreads();
-        const uint32_t tile = s_tile;
-        if (tile >= ntiles) break;
-
-        // decide this thread's pairs (consecutive in the frontier)
-        const int64_t i0 = (int64_t)tile * kPassTile + (int64_t)threadIdx.x * kPassPPT;
-        int2 pr[kPassPPT];
-        Decision dc[kPassPPT];
-        U3 c{0u, 0u, 0u};
-#pragma unroll
-        for (int q = 0; q < kPassPPT; ++q) {
-            dc[q] = Decision{-1, -1, -1, 0u};
-            if (i0 + q < (int64_t)nf) {
-                pr[q] = fr[i0 + q];
-                dc[q] = decide(w, pr[q].x, pr[q].y, theta);
-                if (dc[q].kind == 0) c.c += 1u;
-                else if (dc[q].kind == 1) c.b += 1u;
-                else c.a += dc[q].nnew;
-            }
-        }
-        U3 tot;
-        const U3 e = block_excl_scan(c, wsum, tot);
-
-        // publish the tile's counts, then look back (first wavefront)
-        if (threadIdx.x < kWave) {
-            unsigned long long* my = pst + (size_t)tile * 3;
-            const unsigned long long f0 = tile == 0u ? kPstTotal : kPstOwn;
-            if (lane == 0) {
-                __hip_atomic_store(&my[0], pst_word(epoch, f0, tot.a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&my[1], pst_word(epoch, f0, tot.b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&my[2], pst_word(epoch, f0, tot.c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            unsigned long long acc[3] = {0ull, 0ull, 0ull};
-            bool done[3] = {tile == 0u, tile == 0u, tile == 0u};
-            int64_t j0 = (int64_t)tile - 1;
-            uint32_t spins = 0;
-            while (j0 >= 0 && !(done[0] && done[1] && done[2])) {
-                const int64_t j = j0 - lane;
-                unsigned long long y[3];
-                uint64_t need[3];
-                int ft[3];
-                bool stall = false;
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    y[k] = 0ull;
-                    need[k] = 0ull;
-                    ft[k] = kWave;
-                    if (done[k]) continue;
-                    // words before the first tile count as a zero running total
-                    y[k] = j >= 0 ? __hip_atomic_load(&pst[j * 3 + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                  : pst_word(epoch, kPstTotal, 0ull);
-                    const bool cur = (uint32_t)(y[k] >> 44) == epoch;
-                    const unsigned long long flag = cur ? (y[k] & (3ull << 42)) : 0ull;
-                    const uint64_t totm = __ballot(flag == kPstTotal);
-                    const uint64_t zerom = __ballot(flag == 0ull);
-                    ft[k] = totm ? __ffsll((long long)totm) - 1 : kWave;
-                    need[k] = ft[k] >= kWave - 1 ? ~0ull : ((2ull << ft[k]) - 1ull);
-                    if (zerom & need[k]) stall = true;
-                }
-                if (stall) {
-                    if (++spins > kPassSpinLimit) {
-                        if (lane == 0) atomicOr(err, 1u);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                    continue;
-                }
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    if (done[k]) continue;
-                    unsigned long long v = ((need[k] >> lane) & 1ull) ? (y[k] & kPstVal) : 0ull;
-#pragma unroll
-                    for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-                    acc[k] += v;
-                    if (ft[k] < kWave) done[k] = true;
-                }
-                j0 -= kWave;
-            }
-            if (lane == 0) {
-                if (tile > 0u) {
-                    __hip_atomic_store(&my[0], pst_word(epoch, kPstTotal, acc[0] + tot.a), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(&my[1], pst_word(epoch, kPstTotal, acc[1] + tot.b), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(&my[2], pst_word(epoch, kPstTotal, acc[2] + tot.c), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                }
-                s_pre[0] = acc[0];
-                s_pre[1] = acc[1];
-                s_pre[2] = acc[2];
-            }
-        }
-        __syncthreads();
-        const U3L P{s_pre[0], s_pre[1], s_pre[2]};
-        const bool fits = P.a + tot.a <= cap_next && far0 + P.b + tot.b <= cap_far &&
-                          near0 + P.c + tot.c <= cap_near;
-        if (!fits) {
-            if (threadIdx.x == 0) atomicOr(&st->overflow, 1u);
-        } else {
-            unsigned long long on = P.a + e.a, ofar = far0 + P.b + e.b, onear = near0 + P.c + e.c;
-#pragma unroll
-            for (int q = 0; q < kPassPPT; ++q) {
-                const Decision d = dc[q];
-                if (d.kind < 0) continue;
-                const int32_t lo = pr[q].x < pr[q].y ? pr[q].x : pr[q].y;
-                const int32_t hi = pr[q].x < pr[q].y ? pr[q].y : pr[q].x;
-                if (d.kind == 0) {
-                    near[onear++] = make_int2(lo, hi);
-                } else if (d.kind == 1) {
-                    far[ofar++] = make_int2(lo, hi);
-                } else if (d.kind == 2) {
-                    const int4 tp = w.top[pr[q].x];
-                    const int32_t c0 = tp.z, nc = tp.x;
-                    int2* o = next + on;
-                    for (int32_t x = 0; x < nc; ++x)
-                        for (int32_t yy = x; yy < nc; ++yy) *o++ = make_int2(c0 + x, c0 + yy);
-                    on += d.nnew;
-                } else {
-                    const int4 tp = w.top[d.S];
-                    const int32_t c0 = tp.z, nc = tp.x;
-                    int2* o = next + on;
-                    for (int32_t x = 0; x < nc; ++x) o[x] = make_int2(c0 + x, d.O);
-                    on += d.nnew;
-                }
-            }
-        }
-        if (tile == ntiles - 1u && threadIdx.x == 0)
-            pass_state_write(st, pass, nf, U3L{P.a + tot.a, P.b + tot.b, P.c + tot.c}, far0, near0, cap_next,
-                             cap_far, cap_near);
-        __syncthreads();
+        pr = pr_next;
+        code = code_next;
     }
 }
 
@@ -748,9 +662,34 @@ void build_far_csr_packed(Tree& t, int64_t np, hipStream_t s) {
     t.m2l_src_mask = 0xffffu;
 }
 
+WalkOut walk_out(Tree& t) {
+    const unsigned long long cap = std::min({t.w_fr.cap / 8, t.w_fr2.cap / 8, t.w_dec.cap / kRun, (size_t)UINT32_MAX});
+    return WalkOut{{t.w_fr.as<int2>(), t.w_fr2.as<int2>()}, t.m2l_pairs.as<int2>(), t.p2p_pairs.as<int2>(), cap,
+                   (unsigned long long)(t.m2l_pairs.cap / 8), (unsigned long long)(t.p2p_pairs.cap / 8)};
+}
+
+void launch_seq(Tree& t, const WalkNodes& w, int slot, bool init, int limit, double theta, hipStream_t s) {
+    hipLaunchKernelGGL(walk_seq_kernel, dim3(1), dim3(SQ), 0, s, w, walk_out(t), t.w_state.as<WalkState>(), slot,
+                       init ? 1 : 0, t.n_sets, (uint32_t)limit, theta);
+    TFMM_LAUNCHED();
+}
+
+// One pass in two launches, for a frontier of about expect entries (any grid
+// covers any frontier).
+void launch_pass(Tree& t, const WalkNodes& w, int slot, int64_t expect, double theta, hipStream_t s) {
+    const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kWalkGrid, cdiv(expect, TB / kRun)));
+    const WalkOut o = walk_out(t);
+    hipLaunchKernelGGL(walk_count_kernel, dim3(g), dim3(TB), 0, s, w, o, (const WalkState*)t.w_state.as<WalkState>(),
+                       slot, theta, t.w_dec.as<int8_t>(), t.w_off.as<U3L>());
+    TFMM_LAUNCHED();
+    hipLaunchKernelGGL(walk_emit_kernel, dim3(g), dim3(TB), 0, s, w, o, t.w_state.as<WalkState>(), slot,
+                       (const int8_t*)t.w_dec.as<int8_t>(), (const U3L*)t.w_off.as<U3L>());
+    TFMM_LAUNCHED();
+}
+
 // Frontier passes sized on the host: the totals of every pass are read back
-// and the buffers grown before its outputs are written.  Used for the first
-// walk of a tree and whenever the unsynchronised passes ran out of room.
+// and the buffers grown before its outputs are written.  Used whenever the
+// unsynchronised passes run out of room.
 void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
     Ctx* ctx = t.ctx;
     const int64_t nn = t.n_nodes;
@@ -764,25 +703,25 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
         t.p2p_pairs.ensure(ctx, (size_t)cap_near * 8);
     }
     t.w_fr.ensure(ctx, (size_t)std::max(4096, t.n_sets) * 8);
+    t.w_fr2.ensure(ctx, (size_t)std::max(4096, t.n_sets) * 8);
     t.w_off.ensure(ctx, (size_t)kWalkGrid * sizeof(U3L));
+    t.w_dec.ensure(ctx, (size_t)std::max(4096, t.n_sets) * kRun);
     t.w_state.ensure(ctx, sizeof(WalkState));
     t.scratch2.ensure(ctx, 256);
     WalkState* st = t.w_state.as<WalkState>();
     U3L* tot = t.scratch2.as<U3L>();
-    hipLaunchKernelGGL(walk_init_kernel, dim3(1), dim3(TB), 0, s, st, t.w_fr.as<int2>(), t.n_sets);
-    TFMM_LAUNCHED();
-    DevBuf* cur = &t.w_fr;
-    DevBuf* nxt = &t.w_fr2;
+    launch_seq(t, w, 1, true, 0, theta, s);  // the roots, into slot 0 and buffer 0
     int64_t nf = t.n_sets, max_nf = t.n_sets, n_far = 0, n_near = 0;
+    int slot = 0;
     t.walk_hint_nf.clear();
     for (int k = 0; nf > 0; ++k) {
-        const int parity = k & 1;
         t.walk_hint_nf.push_back(nf);
-        const unsigned g = (unsigned)std::min<int64_t>(kWalkGrid, cdiv(nf, TB));
+        const unsigned g = (unsigned)std::min<int64_t>(kWalkGrid, cdiv(nf, TB / kRun));
+        DevBuf& nxt = (k & 1) ? t.w_fr : t.w_fr2;
         // buffers resized here are idle: a resize waits for the device
-        t.w_dec.ensure(ctx, (size_t)nf);
-        hipLaunchKernelGGL(walk_count_pass_kernel, dim3(g), dim3(TB), 0, s, w, (const int2*)cur->as<int2>(),
-                           (const WalkState*)st, parity, theta, t.w_dec.as<uint8_t>(), t.w_off.as<U3L>());
+        t.w_dec.ensure(ctx, (size_t)nf * kRun);
+        hipLaunchKernelGGL(walk_count_kernel, dim3(g), dim3(TB), 0, s, w, walk_out(t), (const WalkState*)st, slot,
+                           theta, t.w_dec.as<int8_t>(), t.w_off.as<U3L>());
         TFMM_LAUNCHED();
         hipLaunchKernelGGL(walk_total_kernel, dim3(1), dim3(TB), 0, s, (const U3L*)t.w_off.as<U3L>(), (int)g, tot);
         TFMM_LAUNCHED();
@@ -797,18 +736,17 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
             cap_near = std::max<int64_t>(2 * cap_near, n_near + (int64_t)T.c);
             t.p2p_pairs.ensure_keep(ctx, (size_t)cap_near * 8, s);
         }
-        nxt->ensure(ctx, (size_t)std::max<unsigned long long>(T.a, 1) * 8);
-        const size_t cap_next = std::min<size_t>(nxt->cap / 8, UINT32_MAX);
-        hipLaunchKernelGGL(walk_emit_pass_kernel, dim3(g), dim3(TB), 0, s, w, (const int2*)cur->as<int2>(), st, k,
-                           (const uint8_t*)t.w_dec.as<uint8_t>(), (const U3L*)t.w_off.as<U3L>(), nxt->as<int2>(), t.m2l_pairs.as<int2>(),
-                           t.p2p_pairs.as<int2>(), (uint32_t)cap_next, (unsigned long long)(t.m2l_pairs.cap / 8),
-                           (unsigned long long)(t.p2p_pairs.cap / 8));
+        nxt.ensure(ctx, (size_t)std::max<unsigned long long>(T.a, 1) * 8);
+        WalkOut o = walk_out(t);
+        o.cap_next = std::min<size_t>(nxt.cap / 8, UINT32_MAX);  // the decisions grow before the next count
+        hipLaunchKernelGGL(walk_emit_kernel, dim3(g), dim3(TB), 0, s, w, o, st, slot,
+                           (const int8_t*)t.w_dec.as<int8_t>(), (const U3L*)t.w_off.as<U3L>());
         TFMM_LAUNCHED();
         n_far += (int64_t)T.b;
         n_near += (int64_t)T.c;
         nf = (int64_t)T.a;
         max_nf = std::max(max_nf, nf);
-        std::swap(cur, nxt);
+        slot ^= 1;
     }
     const WalkState h = read_back(ctx, (const WalkState*)st, s);
     if (h.overflow)
@@ -818,81 +756,78 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
     t.walk_hint_fr = max_nf;
 }
 
-// Frontier passes with no host synchronisation (small ones fused into one
-// kernel), sized from the previous walk of this tree plus a quarter.  A pair's level sum grows by at least one per
-// expansion, a non-leaf sits above the deepest level and a pair of leaves is
-// never expanded, so every frontier after pass 2 max_level is empty; the host
-// checks that, and the overflow flag, once at the end.  Returns false (lists
-// invalid) when the host-sized passes must be used instead.
-bool walk_bfs_async(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
+// Room for the lists of a tree's first walk: far and near pairs and frontier
+// entries per node grow like (1 + 2 / theta)^3, the volume within 1 / theta
+// cell sizes (ball, Plummer and disk sets of 10^3 to 10^6 particles, theta 0.2 to
+// 0.95: far up to 1.6, near up to 0.75, frontier up to about 0.05 of it per
+// node).  A walk that needs more runs the host-sized passes.
+void first_room(const Tree& t, const std::vector<double>& theta, int64_t& fr, int64_t& far, int64_t& near) {
+    const double th = std::max(*std::min_element(theta.begin(), theta.end()), 0.05);
+    const double around = (1.0 + 2.0 / th) * (1.0 + 2.0 / th) * (1.0 + 2.0 / th);
+    const double nn = (double)t.n_nodes, all = 0.5 * nn * (nn + 1.0);
+    far = (int64_t)std::min(all, nn * std::min(1.65 * around, 400.0)) + 4096;
+    near = (int64_t)std::min(all, nn * std::min(0.75 * around + 8.0, 160.0)) + 4096;
+    fr = (int64_t)std::min(all, nn * std::min(0.06 * around + 2.0, 32.0)) + 4096 + t.n_sets;
+}
+
+// Frontier passes with no host synchronisation, sized from the previous walk
+// of this tree plus a quarter: the first passes, while they are small, in one
+// launch, then two launches per pass as many as that walk had larger ones, then
+// the last small passes in one launch.  The host reads the state back once; a
+// frontier that is left (the passes came out differently) gets more launches.
+// A tree's first walk reads the state back after the first launch too, and its
+// room is estimated.  Returns false (lists invalid) when the host-sized passes
+// must be used instead.
+bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thetas, hipStream_t s) {
     Ctx* ctx = t.ctx;
-    if (t.walk_hint_fr <= 0) return false;
-    const int64_t want_fr = t.walk_hint_fr + t.walk_hint_fr / 4 + 4096;
-    const int64_t want_far = t.walk_hint_far + t.walk_hint_far / 4 + 4096;
-    const int64_t want_near = t.walk_hint_near + t.walk_hint_near / 4 + 4096;
+    const double theta = thetas[0];
+    const bool known = t.walk_hint_fr > 0;
+    int64_t want_fr, want_far, want_near;
+    if (known) {
+        want_fr = t.walk_hint_fr + t.walk_hint_fr / 4 + 4096;
+        want_far = t.walk_hint_far + t.walk_hint_far / 4 + 4096;
+        want_near = t.walk_hint_near + t.walk_hint_near / 4 + 4096;
+    } else {
+        first_room(t, thetas, want_fr, want_far, want_near);
+        const int64_t bytes = 8 * (4 * want_fr + want_far + want_near);
+        if (ctx->budget && ctx->used - ctx->cached + (size_t)bytes > ctx->budget / 2) return false;
+    }
     if (want_fr > (int64_t)UINT32_MAX) return false;
     t.w_fr.ensure(ctx, (size_t)want_fr * 8);
     t.w_fr2.ensure(ctx, (size_t)want_fr * 8);
-    t.w_dec.ensure(ctx, (size_t)want_fr);
+    t.w_dec.ensure(ctx, (size_t)want_fr * kRun);
     t.w_off.ensure(ctx, (size_t)kWalkGrid * sizeof(U3L));
     t.m2l_pairs.ensure(ctx, (size_t)want_far * 8);
     t.p2p_pairs.ensure(ctx, (size_t)want_near * 8);
     t.w_state.ensure(ctx, sizeof(WalkState));
-    const size_t cap_next = std::min({t.w_fr.cap / 8, t.w_fr2.cap / 8, t.w_dec.cap, (size_t)UINT32_MAX});
-    const unsigned long long cap_far = t.m2l_pairs.cap / 8, cap_near = t.p2p_pairs.cap / 8;
-    const int passes = 2 * t.max_level + 1;
-    if (passes > kMaxPasses) return false;
-    // tile status words (three per tile); cleared when new and when the pass
-    // epoch would wrap, so a stale word never carries the current epoch
-    const uint32_t cap_tiles = (uint32_t)cdiv((int64_t)cap_next, kPassTile);
-    void* old_pst = t.w_pst.p;
-    t.w_pst.ensure(ctx, (size_t)cap_tiles * 3 * 8);
-    if (t.w_pst.p != old_pst || t.w_epoch + (uint32_t)passes >= (1u << kEpochBits)) {
-        const int64_t nw = (int64_t)(t.w_pst.cap / 8);
-        hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)std::min<int64_t>(1024, cdiv(nw, TB))), dim3(TB), 0, s,
-                           t.w_pst.as<unsigned long long>(), nw);
-        TFMM_LAUNCHED();
-        t.w_epoch = 0;
-    }
-    WalkState* st = t.w_state.as<WalkState>();
-    hipLaunchKernelGGL(walk_init_kernel, dim3(1), dim3(TB), 0, s, st, t.w_fr.as<int2>(), t.n_sets);
-    TFMM_LAUNCHED();
-    int64_t bound = t.n_sets;  // a pass's frontier is at most 36 times the previous one
-    for (int k = 0; k < passes; ++k) {
-        const int parity = k & 1;
-        // grid from this pass's frontier in the previous walk (any grid covers
-        // any frontier; a small one keeps small passes cheap)
-        int64_t expect = bound;
-        if (k < (int)t.walk_hint_nf.size()) expect = std::min(bound, t.walk_hint_nf[k] + t.walk_hint_nf[k] / 4 + 1024);
-        int2* cur = parity ? t.w_fr2.as<int2>() : t.w_fr.as<int2>();
-        int2* nxt = parity ? t.w_fr.as<int2>() : t.w_fr2.as<int2>();
-        if (expect <= kFuseMaxPairs) {
-            const unsigned g =
-                (unsigned)std::min<int64_t>(kPassGrid, cdiv(std::max<int64_t>(expect, 1), kPassTile));
-            const uint32_t epoch = ++t.w_epoch;
-            hipLaunchKernelGGL(walk_pass_kernel, dim3(g), dim3(TB), 0, s, w, (const int2*)cur, st, k, theta, nxt,
-                               t.m2l_pairs.as<int2>(), t.p2p_pairs.as<int2>(), (uint32_t)cap_next, cap_far,
-                               cap_near, t.w_pst.as<unsigned long long>(), cap_tiles, epoch, ctx->dev_err);
-            TFMM_LAUNCHED();
-        } else {
-            const unsigned g = (unsigned)std::min<int64_t>(kWalkGrid, cdiv(expect, TB));
-            hipLaunchKernelGGL(walk_count_pass_kernel, dim3(g), dim3(TB), 0, s, w, (const int2*)cur,
-                               (const WalkState*)st, parity, theta, t.w_dec.as<uint8_t>(), t.w_off.as<U3L>());
-            TFMM_LAUNCHED();
-            hipLaunchKernelGGL(walk_emit_pass_kernel, dim3(g), dim3(TB), 0, s, w, (const int2*)cur, st, k,
-                               (const uint8_t*)t.w_dec.as<uint8_t>(), (const U3L*)t.w_off.as<U3L>(), nxt, t.m2l_pairs.as<int2>(), t.p2p_pairs.as<int2>(),
-                               (uint32_t)cap_next, cap_far, cap_near);
-            TFMM_LAUNCHED();
+    int slot = 0;
+    launch_seq(t, w, slot ^ 1, true, kSeqHead, theta, s);
+    if (known) {
+        // larger passes of the previous walk: from the first above kSeqHead to the last
+        int a = 0, b = (int)t.walk_hint_nf.size();
+        while (a < b && t.walk_hint_nf[a] <= kSeqHead) ++a;
+        while (b > a && t.walk_hint_nf[b - 1] <= kSeqHead) --b;
+        for (int k = a; k < b; ++k, slot ^= 1)
+            launch_pass(t, w, slot, t.walk_hint_nf[k] + t.walk_hint_nf[k] / 4 + 64, theta, s);
+        if (b > a) {
+            launch_seq(t, w, slot, false, kSeqMax, theta, s);
+            slot ^= 1;
         }
-        bound = std::min<int64_t>((int64_t)cap_next, 36 * bound);
     }
-    const WalkState h = read_back(ctx, (const WalkState*)st, s);
-    const int pf = passes & 1;
-    if (h.overflow || h.nf[pf] != 0u) return false;
-    t.n_m2l = (int64_t)h.n_far[pf];
-    t.n_p2p = (int64_t)h.n_near[pf];
+    WalkState h = read_back(ctx, (const WalkState*)t.w_state.as<WalkState>(), s);
+    while (!h.overflow && h.slot[slot].nf != 0u) {
+        if (h.passes > (uint32_t)kMaxPasses) return false;
+        const int64_t nf = h.slot[slot].nf;
+        for (int k = 0; k < 4; ++k, slot ^= 1) launch_pass(t, w, slot, nf << k, theta, s);
+        launch_seq(t, w, slot, false, kSeqMax, theta, s);
+        slot ^= 1;
+        h = read_back(ctx, (const WalkState*)t.w_state.as<WalkState>(), s);
+    }
+    if (h.overflow) return false;
+    t.n_m2l = (int64_t)h.slot[slot].n_far;
+    t.n_p2p = (int64_t)h.slot[slot].n_near;
     t.walk_hint_fr = h.max_nf;
-    t.walk_hint_nf.assign(h.nf_pass, h.nf_pass + passes);
+    t.walk_hint_nf.assign(h.nf_pass, h.nf_pass + std::min<uint32_t>(h.passes, (uint32_t)kMaxPasses));
     return true;
 }
 
@@ -943,13 +878,13 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t 
     hipLaunchKernelGGL(walk_nodes_kernel, dim3(grid(nn)), dim3(TB), 0, s, nn, (const double4*)t.nd_Z.as<double4>(),
                        (const double*)t.nd_rmax.as<double>(), (const int32_t*)t.nd_nchild.as<int32_t>(),
                        (const int32_t*)t.nd_level.as<int32_t>(), (const int32_t*)t.nd_child_first.as<int32_t>(),
-                       (const int32_t*)t.nd_first.as<int32_t>(),
+                       (const int32_t*)t.nd_parent.as<int32_t>(), (const int32_t*)t.nd_first.as<int32_t>(),
                        t.n_sets > 1 ? (const int64_t*)t.set_off.as<int64_t>() : nullptr, t.n_sets,
                        t.w_geo.as<double4>(), t.w_top.as<int4>());
     TFMM_LAUNCHED();
-    WalkNodes w{t.w_geo.as<double4>(), t.w_top.as<int4>(), theta_dev};
+    WalkNodes w{t.w_geo.as<double4>(), t.w_top.as<int4>(), theta_dev, (int32_t)nn};
     t.walk_valid = false;
-    if (!walk_bfs_async(t, w, theta, s)) walk_bfs_sized(t, w, theta, s);
+    if (!walk_bfs_async(t, w, theta_keep, s)) walk_bfs_sized(t, w, theta, s);
     t.walk_hint_far = t.n_m2l;
     t.walk_hint_near = t.n_p2p;
     const int64_t n_far = t.n_m2l, n_near = t.n_p2p;
