@@ -90,6 +90,34 @@ __device__ __forceinline__ double rsqrt_refined(double x) {
     return y;
 }
 
+// DPP lane moves (no LDS) for reductions: pairs and quads (quad_perm), half
+// rows (row_half_mirror), then rows (row_mirror); every row and bank takes part.
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(dpp_i<CTRL>(__float_as_int(v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const int lo = dpp_i<CTRL>((int)(uint32_t)u);
+    const int hi = dpp_i<CTRL>((int)(uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
+// Sum over each group of 4 or 8 lanes, the result in every lane of the group.
+template <int LANES>
+__device__ __forceinline__ double group_sum(double v) {
+    static_assert(LANES == 4 || LANES == 8, "a quad or a half row");
+    v += dpp<0xB1>(v);  // quad_perm [1,0,3,2]
+    v += dpp<0x4E>(v);  // quad_perm [2,3,0,1]
+    if (LANES == 8) v += dpp<0x141>(v);  // row_half_mirror
+    return v;
+}
+
 // Per-precision scalar types for the interaction kernels.
 template <typename T> struct Vec4;
 template <> struct Vec4<float> { using type = float4; };

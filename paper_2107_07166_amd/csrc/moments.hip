@@ -16,7 +16,32 @@
 namespace tfmm {
 namespace {
 
-constexpr int TB = 128;
+constexpr int TB = 256;
+constexpr int LPL = 4;  // lanes per leaf
+constexpr int LPN = 8;  // lanes per inner node: one per child
+
+// Writes a node's moments, summed over its group of LANES lanes (x: this
+// lane's place), quads of coefficients dealt to the lanes.
+template <int P, int LANES>
+__device__ __forceinline__ void write_moments(const double* w, int32_t node, int x, double* __restrict__ W64,
+                                              float* __restrict__ W32) {
+    constexpr int NC = Expansion<P>::NC;
+    constexpr int NCP = (NC + 3) / 4 * 4;
+    double4* o64 = reinterpret_cast<double4*>(W64 + (int64_t)node * NCP);
+    float4* o32 = reinterpret_cast<float4*>(W32 + (int64_t)node * NCP);
+#pragma unroll
+    for (int q = 0; q < NCP / 4; ++q) {
+        double4 v;
+        v.x = group_sum<LANES>(w[4 * q]);
+        v.y = 4 * q + 1 < NC ? group_sum<LANES>(w[4 * q + 1]) : 0.0;
+        v.z = 4 * q + 2 < NC ? group_sum<LANES>(w[4 * q + 2]) : 0.0;
+        v.w = 4 * q + 3 < NC ? group_sum<LANES>(w[4 * q + 3]) : 0.0;
+        if (x == q % LANES) {
+            o64[q] = v;
+            o32[q] = make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
+        }
+    }
+}
 
 template <int P>
 __global__ __launch_bounds__(TB) void p2m_kernel(int64_t n_leaves, const int32_t* __restrict__ leaves,
@@ -26,32 +51,42 @@ __global__ __launch_bounds__(TB) void p2m_kernel(int64_t n_leaves, const int32_t
                                                  double* __restrict__ W64, float* __restrict__ W32) {
     using E = Expansion<P>;
     constexpr int NC = E::NC;
-    constexpr int NCP = (NC + 3) / 4 * 4;
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i >= n_leaves) return;
-    const int32_t node = leaves[i];
+    const int64_t i = ((int64_t)blockIdx.x * TB + threadIdx.x) / LPL;
+    const int x = threadIdx.x % LPL;
+    const bool live = i < n_leaves;  // the lanes of a group agree; every lane takes part in the sums
+    const int32_t node = leaves[live ? i : 0];
     const double4 z = Z[node];
     double w[NC];
 #pragma unroll
     for (int k = 0; k < NC; ++k) w[k] = 0.0;
-    const int32_t s0 = first[node], s1 = s0 + count[node];
-    for (int32_t s = s0; s < s1; s += 4) {
-        double4 p[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (s + u < s1) p[u] = Xm[s + u];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (s + u < s1) E::p2m(p[u].w, z.x - p[u].x, z.y - p[u].y, z.z - p[u].z, w);
+    const int32_t s0 = first[node], s1 = live ? s0 + count[node] : s0;
+    for (int32_t s = s0 + x; s < s1; s += 2 * LPL) {
+        const bool two = s + LPL < s1;
+        const double4 p = Xm[s], q = Xm[two ? s + LPL : s];
+        E::p2m(p.w, z.x - p.x, z.y - p.y, z.z - p.z, w);
+        if (two) E::p2m(q.w, z.x - q.x, z.y - q.y, z.z - q.z, w);
     }
-    double* o64 = W64 + (int64_t)node * NCP;
-    float* o32 = W32 + (int64_t)node * NCP;
+    if (live) write_moments<P, LPL>(w, node, x, W64, W32);
+}
+
+// One inner node: lane x shifts child x, the group adds up.
+template <int P>
+__device__ __forceinline__ void m2m_node(int32_t node, int x, bool live, const int32_t* __restrict__ child_first,
+                                         const int32_t* __restrict__ nchild, const double4* __restrict__ Z,
+                                         double* __restrict__ W64, float* __restrict__ W32) {
+    using E = Expansion<P>;
+    constexpr int NC = E::NC;
+    constexpr int NCP = (NC + 3) / 4 * 4;
+    const int32_t nc = live ? nchild[node] : 0;
+    double w[NC];
 #pragma unroll
-    for (int k = 0; k < NCP; ++k) {
-        const double v = k < NC ? w[k] : 0.0;
-        o64[k] = v;
-        o32[k] = (float)v;
+    for (int k = 0; k < NC; ++k) w[k] = 0.0;
+    if (x < nc) {
+        const int32_t c = child_first[node] + x;
+        const double4 z = Z[node], zc = Z[c];
+        E::m2m(W64 + (int64_t)c * NCP, z.x - zc.x, z.y - zc.y, z.z - zc.z, w);
     }
+    if (nc > 0) write_moments<P, LPN>(w, node, x, W64, W32);  // leaves: P2M
 }
 
 template <int P>
@@ -59,44 +94,52 @@ __global__ __launch_bounds__(TB) void m2m_kernel(int32_t lb, int32_t le, const i
                                                  const int32_t* __restrict__ nchild,
                                                  const double4* __restrict__ Z, double* __restrict__ W64,
                                                  float* __restrict__ W32) {
-    using E = Expansion<P>;
-    constexpr int NC = E::NC;
-    constexpr int NCP = (NC + 3) / 4 * 4;
-    const int32_t node = lb + (int32_t)(blockIdx.x * TB + threadIdx.x);
-    if (node >= le) return;
-    const int32_t nc = nchild[node];
-    if (nc == 0) return;  // leaves: P2M
-    const double4 z = Z[node];
-    double w[NC];
-#pragma unroll
-    for (int k = 0; k < NC; ++k) w[k] = 0.0;
-    const int32_t c0 = child_first[node];
-    for (int32_t c = c0; c < c0 + nc; ++c) {
-        const double4 zc = Z[c];
-        E::m2m(W64 + (int64_t)c * NCP, z.x - zc.x, z.y - zc.y, z.z - zc.z, w);
-    }
-    double* o64 = W64 + (int64_t)node * NCP;
-    float* o32 = W32 + (int64_t)node * NCP;
-#pragma unroll
-    for (int k = 0; k < NCP; ++k) {
-        const double v = k < NC ? w[k] : 0.0;
-        o64[k] = v;
-        o32[k] = (float)v;
+    const int32_t node = lb + (int32_t)((blockIdx.x * TB + threadIdx.x) / LPN);
+    m2m_node<P>(node < le ? node : lb, threadIdx.x % LPN, node < le, child_first, nchild, Z, W64, W32);
+}
+
+// Consecutive levels top..bottom of at most kFewNodes nodes each, in one block.
+constexpr int kFewNodes = 2 * TB / LPN;
+struct LevelBounds {
+    int32_t b[kLevels + 2];
+};
+template <int P>
+__global__ __launch_bounds__(TB) void m2m_levels_kernel(LevelBounds lv, int bottom, int top,
+                                                        const int32_t* __restrict__ child_first,
+                                                        const int32_t* __restrict__ nchild,
+                                                        const double4* __restrict__ Z, double* W64, float* W32) {
+    for (int L = bottom; L >= top; --L) {
+        const int32_t lb = lv.b[L], le = lv.b[L + 1];
+        for (int32_t base = lb; base < le; base += TB / LPN) {
+            const int32_t node = base + (int32_t)(threadIdx.x / LPN);
+            m2m_node<P>(node < le ? node : lb, threadIdx.x % LPN, node < le, child_first, nchild, Z, W64, W32);
+        }
+        __syncthreads();
     }
 }
 
 template <int P>
 void run(Tree& t, hipStream_t s) {
-    hipLaunchKernelGGL(p2m_kernel<P>, dim3((unsigned)cdiv(t.n_leaves, TB)), dim3(TB), 0, s, t.n_leaves,
+    hipLaunchKernelGGL(p2m_kernel<P>, dim3((unsigned)cdiv(t.n_leaves * LPL, TB)), dim3(TB), 0, s, t.n_leaves,
                        t.leaves.as<int32_t>(), t.nd_first.as<int32_t>(), t.nd_count.as<int32_t>(),
                        t.Xm.as<double4>(), t.nd_Z.as<double4>(), t.W64.as<double>(), t.W32.as<float>());
     TFMM_LAUNCHED();
+    LevelBounds lv{};
+    for (int L = 0; L <= t.max_level + 1; ++L) lv.b[L] = (int32_t)t.level_begin[L];
+    auto nodes = [&](int L) { return lv.b[L + 1] - lv.b[L]; };
     for (int L = t.max_level - 1; L >= 0; --L) {
-        const int32_t b = (int32_t)t.level_begin[L], e = (int32_t)t.level_begin[L + 1];
-        if (e <= b) continue;
-        hipLaunchKernelGGL(m2m_kernel<P>, dim3((unsigned)cdiv(e - b, TB)), dim3(TB), 0, s, b, e,
-                           t.nd_child_first.as<int32_t>(), t.nd_nchild.as<int32_t>(), t.nd_Z.as<double4>(),
-                           t.W64.as<double>(), t.W32.as<float>());
+        int top = L;
+        while (top > 0 && nodes(L) <= kFewNodes && nodes(top - 1) <= kFewNodes) --top;
+        if (top < L) {
+            hipLaunchKernelGGL(m2m_levels_kernel<P>, dim3(1), dim3(TB), 0, s, lv, L, top,
+                               t.nd_child_first.as<int32_t>(), t.nd_nchild.as<int32_t>(), t.nd_Z.as<double4>(),
+                               t.W64.as<double>(), t.W32.as<float>());
+            L = top;
+        } else {
+            hipLaunchKernelGGL(m2m_kernel<P>, dim3((unsigned)cdiv((int64_t)nodes(L) * LPN, TB)), dim3(TB), 0, s,
+                               lv.b[L], lv.b[L + 1], t.nd_child_first.as<int32_t>(), t.nd_nchild.as<int32_t>(),
+                               t.nd_Z.as<double4>(), t.W64.as<double>(), t.W32.as<float>());
+        }
         TFMM_LAUNCHED();
     }
 }
