@@ -187,6 +187,82 @@ __global__ __launch_bounds__(LB) void l2l_level_kernel(int32_t b, int32_t e, con
     l2l_node<P, VAR>((int32_t)i, (int)(t % PARTS), parent, nchild, Z, m2l_off, loc, acc_out, has);
 }
 
+// The level-by-level pass of a small tree in one launch: every leaf carries
+// the expansion down from its topmost ancestor itself, with the same shifts in
+// the same order, so the result is the level launches' bit for bit and the
+// choice between the two may depend on the tree's size.  A shift is done once
+// per leaf below a node instead of once, but a level costs 3 to 4 us of latency
+// here against a launch of 11 us.  The conserving parts of a leaf are
+// neighbouring lanes; P comes from part 0's lane.
+template <int P, int VAR>
+__global__ __launch_bounds__(LB) void l2l_chain_kernel(int64_t n_leaves, const int32_t* __restrict__ leaves,
+                                                       const int32_t* __restrict__ parent,
+                                                       const double4* __restrict__ Z,
+                                                       const uint32_t* __restrict__ m2l_off,
+                                                       const double* __restrict__ loc,
+                                                       double* __restrict__ loc_leaf) {
+    constexpr bool CONS = VAR == TFMM_CONSERVING;
+    constexpr int PARTS = CONS ? 4 : 1;
+    constexpr int NP = CONS ? Expansion<P>::NC1 : Expansion<P>::NC;
+    constexpr int NLOC = CONS ? 4 * NP : NP;
+    static_assert(P >= 2, "an order with shifts");
+    __shared__ int32_t path[kLevels + 1][LB];
+    const int64_t t = (int64_t)blockIdx.x * LB + threadIdx.x;
+    const int part = (int)(t % PARTS);
+    if (t / PARTS >= n_leaves) return;  // the lanes of a leaf agree
+    const int32_t leaf = leaves[t / PARTS];
+    int depth = 0;
+    for (int32_t A = leaf; A >= 0; A = parent[A]) path[depth++][threadIdx.x] = A;
+    double acc[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) acc[k] = 0.0;
+    bool have = false;
+    int32_t par = 0;
+    for (int l = depth - 1; l >= 0; --l) {
+        const int32_t i = path[l][threadIdx.x];
+        const bool own = m2l_off[i + 1] > m2l_off[i];
+        if (own || have) {
+            double next[NP];
+            if (own) {
+                const double* lo = loc + (int64_t)i * NLOC + part * NP;
+#pragma unroll
+                for (int k = 0; k < NP; ++k) next[k] = lo[k];
+            } else {
+#pragma unroll
+                for (int k = 0; k < NP; ++k) next[k] = 0.0;
+            }
+            if (have) {
+                const double4 zi = Z[i], zp = Z[par];
+                const double d[3] = {zi.x - zp.x, zi.y - zp.y, zi.z - zp.z};
+                if constexpr (CONS) {
+                    const double de = part == 0 ? 0.0 : d[part == 0 ? 0 : part - 1];
+#pragma unroll
+                    for (int k = 0; k < NP; ++k) {
+                        const double pk = dpp<0x00>(acc[k]);  // quad_perm [0,0,0,0]
+                        if (part != 0) acc[k] = fma(-de, pk, acc[k]);
+                    }
+                    Expansion<P - 1>::shift_std(acc, d[0], d[1], d[2], next);
+                } else {
+                    Expansion<P>::shift_std(acc, d[0], d[1], d[2], next);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NP; ++k) acc[k] = next[k];
+            have = true;
+        }
+        par = i;
+    }
+    double* out = loc_leaf + (int64_t)leaf * NLOC + part * NP;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) out[k] = acc[k];
+}
+
+// Trees of at most this many (leaf, part) threads run the chain, a round of
+// one wavefront on every SIMD: disk of 10^5 (p = 6, 2.5e3 leaves, conserving) 783 ->
+// 728 us per step, Plummer 2^18 with the raised scalar degree (7.3e3 leaves) 2737
+// -> 2670; the disk of 2^22 (1.2e5 leaves) would go from 6.78 to 6.87 ms.
+constexpr int64_t kChainThreads = 65536;
+
 struct LevelRange {
     int32_t b[kLevels + 2];
 };
@@ -213,6 +289,13 @@ template <int P, int VAR>
 void l2l_levels(Tree& t, hipStream_t s) {
     constexpr int PARTS = VAR == TFMM_CONSERVING ? 4 : 1;
     constexpr int64_t kTopNodes = LB;
+    if (t.n_leaves * PARTS <= kChainThreads) {
+        hipLaunchKernelGGL((l2l_chain_kernel<P, VAR>), dim3((unsigned)cdiv(t.n_leaves * PARTS, LB)), dim3(LB), 0, s,
+                           t.n_leaves, t.leaves.as<int32_t>(), t.nd_parent.as<int32_t>(), t.nd_Z.as<double4>(),
+                           t.m2l_off.as<uint32_t>(), t.loc.as<double>(), t.loc_leaf.as<double>());
+        TFMM_LAUNCHED();
+        return;
+    }
     t.loc_has.ensure(t.ctx, (size_t)std::max<int64_t>(t.n_nodes, 1));
     int top = -1;
     while (top + 1 <= t.max_level && t.level_begin[(size_t)top + 2] <= kTopNodes) ++top;
