@@ -278,6 +278,14 @@ void radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* 
                     int64_t n, int bits, void* scratch, uint32_t* err, hipStream_t s);
 void radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                     int64_t n, int bits, void* scratch, uint32_t* err, hipStream_t s);
+// The single-kernel-per-pass route of radix_sort_u64 with the digit totals
+// counted by the caller: sort_counts gives their place in the scratch (8
+// passes of 256 words, then the words the passes need cleared up to
+// *clear_words from the start), or nullptr when n takes the other route, which
+// counts by itself.
+uint32_t* sort_counts(void* scratch, int64_t n, int bits, int64_t* clear_words);
+void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
+                            int bits, void* scratch, uint32_t* err, hipStream_t s);
 // Stable sort by key of the 2 np directed entries of np node pairs: entry 2i
 // is (key x_i, value y_i), entry 2i + 1 is (y_i, x_i); with self_dummy, the
 // second entry of a pair (x, x) gets key self_key instead.  The sorted
@@ -299,6 +307,27 @@ constexpr size_t kBoxBytes = kBoxHeaderWords * 4 + kBoxPayload;
 // out once the work queued on s before it is done; with check_err, fails if a
 // kernel set the context's device error word.
 void read_back_bytes(Ctx* ctx, const void* dev, size_t bytes, void* out, bool check_err, hipStream_t s);
+
+// The same in two halves, for a producer that writes the mailbox itself (its
+// last block calls mailbox_write) instead of a launch of its own.
+struct Mailbox {
+    uint32_t* box;        // as the device sees it; nullptr: write nothing
+    const uint32_t* err;  // the context's device error word
+    uint32_t seq;
+};
+Mailbox mailbox_next(Ctx* ctx);
+void mailbox_wait(Ctx* ctx, uint32_t seq, size_t bytes, void* out, bool check_err, hipStream_t s);
+
+// Called by every thread of one block: nwords words of src, which this block
+// wrote before a barrier (or an earlier kernel did), then the sequence number.
+__device__ __forceinline__ void mailbox_write(const Mailbox& m, const void* src, int nwords) {
+    const uint32_t* w = static_cast<const uint32_t*>(src);
+    for (int i = threadIdx.x; i < nwords; i += blockDim.x) m.box[kBoxHeaderWords + i] = w[i];
+    if (threadIdx.x == 0) m.box[1] = *m.err;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(m.box, m.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 template <typename V>
 V read_back(Ctx* ctx, const V* dev, hipStream_t s) {

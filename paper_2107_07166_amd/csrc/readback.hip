@@ -20,26 +20,20 @@ namespace {
 constexpr int kBoxBlock = 256;
 constexpr int64_t kSpinNs = 20'000'000;  // 20 ms of polling, then block
 
-__global__ __launch_bounds__(kBoxBlock) void mailbox_kernel(const uint32_t* __restrict__ src, int nwords,
-                                                            const uint32_t* __restrict__ err,
-                                                            uint32_t* __restrict__ box, uint32_t seq) {
-    for (int i = threadIdx.x; i < nwords; i += kBoxBlock) box[kBoxHeaderWords + i] = src[i];
-    if (threadIdx.x == 0) box[1] = *err;
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(box, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+__global__ __launch_bounds__(kBoxBlock) void mailbox_kernel(Mailbox m, const uint32_t* __restrict__ src, int nwords) {
+    mailbox_write(m, src, nwords);
 }
 
 }  // namespace
 
-void read_back_bytes(Ctx* ctx, const void* dev, size_t bytes, void* out, bool check_err, hipStream_t s) {
-    if (bytes % 4 != 0 || bytes > kBoxPayload) fail(TFMM_EINVAL, "read-back size");
-    uint32_t* box = ctx->mbox;
+Mailbox mailbox_next(Ctx* ctx) {
     uint32_t seq = ++ctx->mbox_seq;
     if (seq == 0u) seq = ++ctx->mbox_seq;  // 0 is the mailbox's initial value
-    hipLaunchKernelGGL(mailbox_kernel, dim3(1), dim3(kBoxBlock), 0, s, static_cast<const uint32_t*>(dev),
-                       (int)(bytes / 4), (const uint32_t*)ctx->dev_err, ctx->mbox_dev, seq);
-    TFMM_LAUNCHED();
+    return Mailbox{ctx->mbox_dev, (const uint32_t*)ctx->dev_err, seq};
+}
+
+void mailbox_wait(Ctx* ctx, uint32_t seq, size_t bytes, void* out, bool check_err, hipStream_t s) {
+    uint32_t* box = ctx->mbox;
     const auto t0 = std::chrono::steady_clock::now();
     for (uint32_t k = 1; __atomic_load_n(box, __ATOMIC_ACQUIRE) != seq; ++k) {
         _mm_pause();
@@ -55,6 +49,15 @@ void read_back_bytes(Ctx* ctx, const void* dev, size_t bytes, void* out, bool ch
     std::memcpy(out, box + kBoxHeaderWords, bytes);
     if (check_err && box[1] != 0u)
         fail(TFMM_EDEVICE, "a device-side wait ran past its bound (internal error); results are invalid");
+}
+
+void read_back_bytes(Ctx* ctx, const void* dev, size_t bytes, void* out, bool check_err, hipStream_t s) {
+    if (bytes % 4 != 0 || bytes > kBoxPayload) fail(TFMM_EINVAL, "read-back size");
+    const Mailbox m = mailbox_next(ctx);
+    hipLaunchKernelGGL(mailbox_kernel, dim3(1), dim3(kBoxBlock), 0, s, m, static_cast<const uint32_t*>(dev),
+                       (int)(bytes / 4));
+    TFMM_LAUNCHED();
+    mailbox_wait(ctx, m.seq, bytes, out, check_err, s);
 }
 
 }  // namespace tfmm

@@ -483,9 +483,10 @@ SortScratch carve(void* scratch, int64_t n, int passes, int rtile) {
 // pass ps writes (kout, vout) when the number of passes after it is even,
 // else the alternate arrays, so the last pass always lands in (kout, vout).
 // Without values (HV false) the value arrays are not touched.
+// counted: the scratch is cleared and the digit totals are in place.
 template <typename K, bool HV, typename Src>
 void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int64_t n, int shift0, int bits,
-                    void* scratch, uint32_t* err, hipStream_t s) {
+                    void* scratch, uint32_t* err, hipStream_t s, bool counted = false) {
     constexpr int RTILE = tile_keys<K, HV>();
     const int passes = (bits + 7) / 8;
     const int nb = (int)cdiv(n, RTILE);
@@ -532,14 +533,16 @@ void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int
         return;
     }
     const SortScratch sc = carve(scratch, n, passes, RTILE);
-    const unsigned zb = (unsigned)std::min<int64_t>(2048, cdiv(sc.zero_words, RB));
-    hipLaunchKernelGGL(zero_u64_kernel, dim3(zb), dim3(RB), 0, s, static_cast<unsigned long long*>(scratch),
-                       sc.zero_words);
-    TFMM_LAUNCHED();
-    const unsigned hb = (unsigned)std::min<int64_t>(kHistBlocks, cdiv(n, RB * kHistKeysPerThread));
-    hipLaunchKernelGGL((radix_hist_all_kernel<K, Src>), dim3(hb), dim3(RB), 0, s, src, n, shift0, passes,
-                       sc.dcount);
-    TFMM_LAUNCHED();
+    if (!counted) {
+        const unsigned zb = (unsigned)std::min<int64_t>(2048, cdiv(sc.zero_words, RB));
+        hipLaunchKernelGGL(zero_u64_kernel, dim3(zb), dim3(RB), 0, s, static_cast<unsigned long long*>(scratch),
+                           sc.zero_words);
+        TFMM_LAUNCHED();
+        const unsigned hb = (unsigned)std::min<int64_t>(kHistBlocks, cdiv(n, RB * kHistKeysPerThread));
+        hipLaunchKernelGGL((radix_hist_all_kernel<K, Src>), dim3(hb), dim3(RB), 0, s, src, n, shift0, passes,
+                           sc.dcount);
+        TFMM_LAUNCHED();
+    }
     for (int ps = 0; ps < passes; ++ps) {
         const bool to_out = ((passes - 1 - ps) & 1) == 0;
         K* ko = to_out ? kout : kalt;
@@ -583,6 +586,22 @@ void radix_sort_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int
 }
 
 }  // namespace
+
+uint32_t* sort_counts(void* scratch, int64_t n, int bits, int64_t* clear_words) {
+    const int rtile = tile_keys<uint64_t, true>();
+    if (cdiv(n, rtile) >= kRtsMinTiles) return nullptr;
+    const SortScratch sc = carve(scratch, n, (bits + 7) / 8, rtile);
+    *clear_words = sc.zero_words;
+    return sc.dcount;
+}
+
+void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
+                            int bits, void* scratch, uint32_t* err, hipStream_t s) {
+    if (n <= 1 || bits <= 0) return;
+    if (((bits + 7) / 8) & 1) fail(TFMM_EINVAL, "a counted sort takes an even number of passes");
+    radix_sort_run<uint64_t, true>(ArraySrc<uint64_t>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits,
+                                   scratch, err, s, true);
+}
 
 size_t sort_scratch_bytes(int64_t n, int bits) {
     const int passes = bits <= 0 ? 1 : (bits + 7) / 8;

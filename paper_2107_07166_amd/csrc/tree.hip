@@ -26,8 +26,11 @@ namespace {
 constexpr int TB = 256;
 constexpr uint32_t QMAX = (1u << kLevels) - 1u;
 
+// Also clears the digit totals of the sort (counts: words to clear, or 0).
 __global__ __launch_bounds__(TB) void bbox_partial_kernel(const double* __restrict__ pos, int64_t n,
-                                                          double* __restrict__ part) {
+                                                          double* __restrict__ part,
+                                                          unsigned long long* __restrict__ clear, int64_t words) {
+    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < words; i += (int64_t)gridDim.x * TB) clear[i] = 0ull;
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     int bad = 0;
     for (int64_t a = (int64_t)blockIdx.x * TB + threadIdx.x; a < n; a += (int64_t)gridDim.x * TB) {
@@ -83,14 +86,17 @@ __device__ void write_cube(const double* lo, const double* hi, bool bad, double*
     out[8] = (bad || !isfinite(ext) || !isfinite(scale)) ? 1.0 : 0.0;
 }
 
-__global__ __launch_bounds__(TB) void bbox_final_kernel(const double* __restrict__ part, int nb,
-                                                        double* __restrict__ out) {
-    __shared__ double sh[6][TB];
+// The cube from the nb partial boxes, by every block that needs it (the
+// result lands in LDS; block 0 also writes it to out).
+__device__ void cube_of_parts(const double* __restrict__ part, int nb, double* __restrict__ out, double* cube) {
+    constexpr int NW = TB / kWave;
+    __shared__ double sh[NW][6];
     __shared__ int s_bad;
-    if (threadIdx.x == 0) s_bad = 0;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    if (tid == 0) s_bad = 0;
     __syncthreads();
     double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    for (int b = threadIdx.x; b < nb; b += TB) {
+    for (int b = tid; b < nb; b += TB) {
         if (part[7 * b + 6] != 0.0) s_bad = 1;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -100,23 +106,32 @@ __global__ __launch_bounds__(TB) void bbox_final_kernel(const double* __restrict
         }
     }
 #pragma unroll
-    for (int d = 0; d < 6; ++d) sh[d][threadIdx.x] = v[d];
-    __syncthreads();
-    for (int s = TB / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
+    for (int o = kWave / 2; o > 0; o >>= 1) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const double a = sh[d][threadIdx.x + s], b = sh[3 + d][threadIdx.x + s];
-                if (a < sh[d][threadIdx.x]) sh[d][threadIdx.x] = a;
-                if (b > sh[3 + d][threadIdx.x]) sh[3 + d][threadIdx.x] = b;
+        for (int d = 0; d < 3; ++d) {
+            const double lo = __shfl_xor(v[d], o, kWave), hi = __shfl_xor(v[3 + d], o, kWave);
+            v[d] = lo < v[d] ? lo : v[d];
+            v[3 + d] = hi > v[3 + d] ? hi : v[3 + d];
+        }
+    }
+    if (lane == 0)
+        for (int d = 0; d < 6; ++d) sh[wv][d] = v[d];
+    __syncthreads();
+    if (tid == 0) {
+        double lo[3], hi[3];
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = sh[0][d];
+            hi[d] = sh[0][3 + d];
+            for (int w = 1; w < NW; ++w) {
+                lo[d] = sh[w][d] < lo[d] ? sh[w][d] : lo[d];
+                hi[d] = sh[w][3 + d] > hi[d] ? sh[w][3 + d] : hi[d];
             }
         }
-        __syncthreads();
+        write_cube(lo, hi, s_bad != 0, cube);
+        if (blockIdx.x == 0)
+            for (int d = 0; d < 9; ++d) out[d] = cube[d];
     }
-    if (threadIdx.x == 0) {
-        const double lo[3] = {sh[0][0], sh[1][0], sh[2][0]}, hi[3] = {sh[3][0], sh[4][0], sh[5][0]};
-        write_cube(lo, hi, s_bad != 0, out);
-    }
+    __syncthreads();
 }
 
 // The cubes of the sets of a forest, one block per set (cube k at out + 16 k).
@@ -173,23 +188,215 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v) {
     return x;
 }
 
-__global__ __launch_bounds__(TB) void morton_kernel(const double* __restrict__ pos, int64_t n,
-                                                    const double* __restrict__ cubes,
-                                                    const int64_t* __restrict__ set_off, int n_sets,
-                                                    uint64_t* __restrict__ keys, int32_t* __restrict__ idx) {
-    const int64_t a = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (a >= n) return;
-    const double* cube = cubes + 16 * (int64_t)set_of(set_off, n_sets, a);
-    const double lo[3] = {cube[0], cube[1], cube[2]};
-    const double scale = cube[7];
+// The key of position x in a cube.
+__device__ __forceinline__ uint64_t morton_key(const double* __restrict__ x, const double* cube) {
     uint32_t q[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const double f = floor((pos[3 * a + d] - lo[d]) * scale);
+        const double f = floor((x[d] - cube[d]) * cube[7]);
         q[d] = (f >= (double)QMAX) ? QMAX : (uint32_t)f;
     }
-    keys[a] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
-    idx[a] = (int32_t)a;
+    return (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+}
+
+// Keys and input indices; a block takes per * TB consecutive particles.  part:
+// the partial boxes of a single set (a forest's cubes are in cubes already).
+// counts: the sort's digit totals, 8 passes of 256, counted here while the keys
+// are in registers (nullptr: the sort counts by itself).
+__global__ __launch_bounds__(TB) void morton_kernel(const double* __restrict__ pos, int64_t n,
+                                                    const double* __restrict__ part, int nparts,
+                                                    double* __restrict__ cubes,
+                                                    const int64_t* __restrict__ set_off, int n_sets, int per,
+                                                    uint64_t* __restrict__ keys, int32_t* __restrict__ idx,
+                                                    uint32_t* __restrict__ counts) {
+    __shared__ double cube0[9];
+    __shared__ uint32_t h[8][256];
+    static_assert(TB == 256, "a thread per digit");
+    if (n_sets <= 1) cube_of_parts(part, nparts, cubes, cube0);
+    if (counts) {
+#pragma unroll
+        for (int p = 0; p < 8; ++p) h[p][threadIdx.x] = 0u;
+        __syncthreads();
+    }
+    const int64_t a0 = (int64_t)blockIdx.x * per * TB + threadIdx.x;
+    for (int k = 0; k < per; ++k) {
+        const int64_t a = a0 + (int64_t)k * TB;
+        if (a >= n) break;
+        const double* cube = n_sets <= 1 ? cube0 : cubes + 16 * (int64_t)set_of(set_off, n_sets, a);
+        const uint64_t key = morton_key(pos + 3 * a, cube);
+        keys[a] = key;
+        idx[a] = (int32_t)a;
+        if (counts) {
+#pragma unroll
+            for (int p = 0; p < 8; ++p) atomicAdd(&h[p][(uint32_t)(key >> (8 * p)) & 255u], 1u);
+        }
+    }
+    if (counts) {
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const uint32_t c = h[p][threadIdx.x];
+            if (c) atomicAdd(&counts[p * 256 + threadIdx.x], c);
+        }
+    }
+}
+
+// Level at which a key boundary appears between two sorted neighbours (22 =
+// equal keys, never a boundary).
+__device__ __forceinline__ uint8_t boundary_level(uint64_t a, uint64_t b) {
+    const uint64_t x = a ^ b;
+    return x == 0 ? (uint8_t)(kLevels + 1) : (uint8_t)(kLevels - (63 - __clzll((long long)x)) / 3);
+}
+
+// A small single set in one workgroup: cube, keys, the whole stable sort (eight
+// 8-bit passes in LDS, ranks by wavefront ballots as in the large sorts), the
+// sorted particles and the boundary levels.  KPL keys per lane; keys past n
+// are all ones and stay behind the last real key.  Replaces the cube, key,
+// clearing, counting, eight pass and gather launches (14), each of which costs
+// its launch and little else at these sizes: 31 us for a ball of 2048, where the
+// launches took 80 us of kernels and as much again between them (step 330 -> 255
+// us with the fewer launches of the rest of the build).
+constexpr int ST = 1024;
+constexpr int64_t kSmallSort = 8 * ST;
+template <int KPL>
+__global__ __launch_bounds__(ST) void small_sort_kernel(const double* __restrict__ pos,
+                                                        const double* __restrict__ mass, int n,
+                                                        double* __restrict__ cube_out, uint64_t* __restrict__ keys,
+                                                        int32_t* __restrict__ perm, double4* __restrict__ Xm,
+                                                        uint8_t* __restrict__ lvlb) {
+    constexpr int NW = ST / kWave;
+    __shared__ uint64_t sk[KPL * ST];
+    __shared__ uint16_t sv[KPL * ST];
+    __shared__ uint32_t wcnt[NW][256];
+    __shared__ uint32_t dstart[256];
+    __shared__ uint32_t wsum[4];
+    __shared__ double box[NW][6];
+    __shared__ double cube[9];
+    __shared__ int s_bad;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int base = wv * (kWave * KPL) + lane;  // round r of this lane: base + r kWave
+    if (tid == 0) s_bad = 0;
+    __syncthreads();
+    double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    int bad = 0;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const int a = base + r * kWave;
+        if (a < n) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const double x = pos[3 * a + d];
+                bad |= !isfinite(x);
+                v[d] = x < v[d] ? x : v[d];
+                v[3 + d] = x > v[3 + d] ? x : v[3 + d];
+            }
+        }
+    }
+    if (bad) s_bad = 1;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double lo = __shfl_xor(v[d], o, kWave), hi = __shfl_xor(v[3 + d], o, kWave);
+            v[d] = lo < v[d] ? lo : v[d];
+            v[3 + d] = hi > v[3 + d] ? hi : v[3 + d];
+        }
+    }
+    if (lane == 0)
+        for (int d = 0; d < 6; ++d) box[wv][d] = v[d];
+    __syncthreads();
+    if (tid == 0) {
+        double lo[3], hi[3];
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = box[0][d];
+            hi[d] = box[0][3 + d];
+            for (int w = 1; w < NW; ++w) {
+                lo[d] = box[w][d] < lo[d] ? box[w][d] : lo[d];
+                hi[d] = box[w][3 + d] > hi[d] ? box[w][3 + d] : hi[d];
+            }
+        }
+        write_cube(lo, hi, s_bad != 0, cube);
+        for (int d = 0; d < 9; ++d) cube_out[d] = cube[d];
+    }
+    __syncthreads();
+    uint64_t k[KPL];
+    uint16_t id[KPL];
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const int a = base + r * kWave;
+        id[r] = (uint16_t)a;
+        k[r] = a < n ? morton_key(pos + 3 * a, cube) : ~0ull;
+    }
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    for (int pass = 0; pass < 8; ++pass) {
+        const int shift = 8 * pass;
+        for (int i = tid; i < NW * 256; i += ST) (&wcnt[0][0])[i] = 0u;
+        __syncthreads();
+        uint32_t rank[KPL];
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
+            uint64_t peers = ~0ull;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+            const uint32_t below = (uint32_t)__popcll(peers & lt);
+            const uint32_t first = wcnt[wv][d];
+            rank[r] = first + below;
+            if (below == 0) wcnt[wv][d] = first + (uint32_t)__popcll(peers);
+        }
+        __syncthreads();
+        uint32_t tot = 0, incl = 0;
+        if (tid < 256) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const uint32_t c = wcnt[w][tid];
+                wcnt[w][tid] = tot;
+                tot += c;
+            }
+            incl = tot;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const uint32_t u = (uint32_t)__shfl_up((int)incl, o, kWave);
+                if (lane >= o) incl += u;
+            }
+            if (lane == kWave - 1) wsum[wv] = incl;
+        }
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t off = 0;
+            for (int w = 0; w < wv; ++w) off += wsum[w];
+            dstart[tid] = off + incl - tot;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
+            const uint32_t p = dstart[d] + wcnt[wv][d] + rank[r];
+            sk[p] = k[r];
+            sv[p] = id[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) {
+            k[r] = sk[base + r * kWave];
+            id[r] = sv[base + r * kWave];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const int j = base + r * kWave;
+        if (j < n) {
+            const int a = id[r];
+            keys[j] = k[r];
+            perm[j] = a;
+            Xm[j] = make_double4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], mass[a]);
+            lvlb[j] = j > 0 ? boundary_level(sk[j - 1], k[r]) : (uint8_t)0;
+        }
+    }
 }
 
 // Forest: after the sort by key, a stable sort by set puts every set's
@@ -229,10 +436,7 @@ __global__ __launch_bounds__(TB) void gather_kernel(const double* __restrict__ p
     const int64_t a = perm[j];
     Xm[j] = make_double4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], mass[a]);
     uint8_t lb = 0;
-    if (j > 0 && (n_sets <= 1 || set_off[set_of(set_off, n_sets, j)] != j)) {
-        const uint64_t x = keys[j - 1] ^ keys[j];
-        lb = (x == 0) ? (uint8_t)(kLevels + 1) : (uint8_t)(kLevels - (63 - __clzll((long long)x)) / 3);
-    }
+    if (j > 0 && (n_sets <= 1 || set_off[set_of(set_off, n_sets, j)] != j)) lb = boundary_level(keys[j - 1], keys[j]);
     lvlb[j] = lb;
 }
 
@@ -261,27 +465,24 @@ struct NodeArrays {
 constexpr int NSLOT = kLevels + 2;  // levels 0..21 and a slot for the leaf count
 constexpr int kMaxLeafWindow = 4096;
 
-// cl[i] = deepest level shared by keys[i] and keys[i + n_leaf] (21 if equal,
-// -1 if the two belong to different sets).
-__global__ __launch_bounds__(TB) void window_level_kernel(const uint64_t* __restrict__ keys, int64_t nw, int n_leaf,
-                                                          const int64_t* __restrict__ set_off, int n_sets,
-                                                          int8_t* __restrict__ cl) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i >= nw) return;
-    if (n_sets > 1 && set_off[set_of(set_off, n_sets, i) + 1] <= i + n_leaf) {
-        cl[i] = (int8_t)-1;
-        return;
-    }
+// Deepest level shared by keys[i] and keys[i + n_leaf] (21 if equal, -1 if the
+// two belong to different sets).
+__device__ __forceinline__ int8_t window_level(const uint64_t* __restrict__ keys, int64_t i, int n_leaf,
+                                               const int64_t* __restrict__ set_off, int n_sets) {
+    if (n_sets > 1 && set_off[set_of(set_off, n_sets, i) + 1] <= i + n_leaf) return (int8_t)-1;
     const uint64_t x = keys[i] ^ keys[i + n_leaf];
-    cl[i] = (x == 0) ? (int8_t)kLevels : (int8_t)(kLevels - (63 - __clzll((long long)x)) / 3 - 1);
+    return (x == 0) ? (int8_t)kLevels : (int8_t)(kLevels - (63 - __clzll((long long)x)) / 3 - 1);
 }
 
-// lambda(j) from the largest cl over the n_leaf + 1 windows that contain j
+// lambda(j) from the largest window level over the n_leaf + 1 windows that contain j
 // (a sparse-table maximum in LDS), and per-level counts of node starts and of
 // leaf starts for the block.
-__global__ __launch_bounds__(TB) void leaf_level_kernel(const int8_t* __restrict__ cl, int64_t n, int n_leaf,
+__global__ __launch_bounds__(TB) void leaf_level_kernel(const uint64_t* __restrict__ keys, int64_t n, int n_leaf,
+                                                        const int64_t* __restrict__ set_off, int n_sets,
                                                         const uint8_t* __restrict__ lvlb, uint8_t* __restrict__ lam,
-                                                        uint32_t* __restrict__ cnt, int64_t nblk) {
+                                                        uint32_t* __restrict__ cnt, int64_t nblk,
+                                                        uint32_t* __restrict__ done) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0u;
     constexpr int VMAX = (TB + kMaxLeafWindow + TB - 1) / TB;
     __shared__ int8_t m[TB + kMaxLeafWindow];
     __shared__ uint32_t wc[TB / kWave][NSLOT];
@@ -291,7 +492,7 @@ __global__ __launch_bounds__(TB) void leaf_level_kernel(const int8_t* __restrict
     const int TL = TB + n_leaf;
     for (int t = tid; t < TL; t += TB) {
         const int64_t i = j0 - n_leaf + t;
-        m[t] = (i >= 0 && i < nw) ? cl[i] : (int8_t)-1;
+        m[t] = (i >= 0 && i < nw) ? window_level(keys, i, n_leaf, set_off, n_sets) : (int8_t)-1;
     }
     __syncthreads();
     const int w = n_leaf + 1;
@@ -341,13 +542,24 @@ __global__ __launch_bounds__(TB) void leaf_level_kernel(const int8_t* __restrict
     }
 }
 
+// Level boundaries and sizes of the octree (read back by the host once).
+struct TreeHeader {
+    int64_t LB[kLevels + 2];  // first node id of levels 0..21, then the node count
+    int64_t max_level, n_nodes, n_leaves;
+    int64_t nonfinite;        // a coordinate was not finite
+};
+
 // Exclusive scan over the blocks of one slot's counts (one block per slot):
 // every thread takes a contiguous run of the counts, the run totals are
 // scanned across the block (wave scans, then the waves' totals), and each
-// thread writes its run's exclusive prefixes.
-__global__ __launch_bounds__(TB) void slot_scan_kernel(uint32_t* __restrict__ cnt, int64_t nblk,
-                                                       uint32_t* __restrict__ tot) {
+// thread writes its run's exclusive prefixes.  The block that finishes last
+// (done: a counter that starts at zero) writes the header and the mailbox.
+__global__ __launch_bounds__(TB) void slot_scan_kernel(uint32_t* __restrict__ cnt, int64_t nblk, uint32_t* tot,
+                                                       uint32_t* done, const double* __restrict__ cubes, int n_sets,
+                                                       TreeHeader* __restrict__ h, Mailbox mb) {
     __shared__ uint32_t wsum[TB / kWave];
+    __shared__ int s_last;
+    __shared__ int s_bad;
     uint32_t* c = cnt + (int64_t)blockIdx.x * nblk;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int64_t per = (nblk + TB - 1) / TB;
@@ -362,6 +574,7 @@ __global__ __launch_bounds__(TB) void slot_scan_kernel(uint32_t* __restrict__ cn
         if (lane >= d) v += u;
     }
     if (lane == kWave - 1) wsum[wv] = v;
+    if (tid == 0) s_bad = 0;
     __syncthreads();
     uint32_t base = 0, all = 0;
 #pragma unroll
@@ -375,31 +588,32 @@ __global__ __launch_bounds__(TB) void slot_scan_kernel(uint32_t* __restrict__ cn
         c[i] = acc;
         acc += x;
     }
-    if (tid == 0) tot[blockIdx.x] = all;
-}
-
-// Level boundaries and sizes of the octree (read back by the host once).
-struct TreeHeader {
-    int64_t LB[kLevels + 2];  // first node id of levels 0..21, then the node count
-    int64_t max_level, n_nodes, n_leaves;
-    int64_t nonfinite;        // a coordinate was not finite
-};
-
-__global__ void tree_header_kernel(const uint32_t* __restrict__ tot, const double* __restrict__ cubes, int n_sets,
-                                   TreeHeader* __restrict__ h) {
-    if (threadIdx.x != 0) return;
-    int64_t bad = 0;
-    for (int k = 0; k < n_sets; ++k) bad |= cubes[16 * k + 8] != 0.0 ? 1 : 0;
-    h->nonfinite = bad;
-    h->LB[0] = 0;
-    int64_t ml = 0;
-    for (int l = 0; l <= kLevels; ++l) {
-        h->LB[l + 1] = h->LB[l] + tot[l];
-        if (tot[l] > 0) ml = l;
+    if (tid == 0) {
+        __hip_atomic_store(&tot[blockIdx.x], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t before = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = before == gridDim.x - 1u;
     }
-    h->max_level = ml;
-    h->n_nodes = h->LB[kLevels + 1];
-    h->n_leaves = (int64_t)tot[NSLOT - 1];
+    __syncthreads();
+    if (!s_last) return;
+    for (int k = tid; k < n_sets; k += TB)
+        if (cubes[16 * k + 8] != 0.0) s_bad = 1;
+    __syncthreads();
+    if (tid == 0) {
+        h->nonfinite = s_bad;
+        int64_t lb = 0, ml = 0;
+        h->LB[0] = 0;
+        for (int l = 0; l <= kLevels; ++l) {
+            const uint32_t x = __hip_atomic_load(&tot[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            lb += x;
+            h->LB[l + 1] = lb;
+            if (x > 0) ml = l;
+        }
+        h->max_level = ml;
+        h->n_nodes = lb;
+        h->n_leaves = (int64_t)__hip_atomic_load(&tot[NSLOT - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    mailbox_write(mb, h, (int)(sizeof(TreeHeader) / 4));
 }
 
 __global__ __launch_bounds__(TB) void node_create_kernel(NodeArrays nd, int64_t n, const uint64_t* __restrict__ keys,
@@ -408,7 +622,9 @@ __global__ __launch_bounds__(TB) void node_create_kernel(NodeArrays nd, int64_t 
                                                          const uint32_t* __restrict__ boff, int64_t nblk,
                                                          const TreeHeader* __restrict__ h,
                                                          int32_t* __restrict__ leaf_of,
-                                                         int32_t* __restrict__ leaves) {
+                                                         int32_t* __restrict__ leaves,
+                                                         uint32_t* __restrict__ n_items) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_items = 0u;
     __shared__ unsigned long long bal[TB / kWave][NSLOT];
     __shared__ uint32_t woff[TB / kWave][NSLOT];
     __shared__ int64_t sLB[kLevels + 2];
@@ -463,10 +679,7 @@ __global__ __launch_bounds__(TB) void node_create_kernel(NodeArrays nd, int64_t 
 // that node has the same parent, else where its parent ends; the roots,
 // parent -1, end where the next root starts) and child counts (written by the
 // last child).
-__global__ __launch_bounds__(TB) void node_finish_kernel(NodeArrays nd, int64_t nn, int64_t n,
-                                                         const TreeHeader* __restrict__ h) {
-    const int64_t c = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (c >= nn) return;
+__device__ __forceinline__ void node_finish(NodeArrays nd, int64_t c, int64_t n, const TreeHeader* __restrict__ h) {
     const int l = nd.level[c];
     const int32_t P = nd.parent[c];
     int64_t x = c, end = n;
@@ -483,18 +696,16 @@ __global__ __launch_bounds__(TB) void node_finish_kernel(NodeArrays nd, int64_t 
         nd.nchild[P] = (int32_t)(c - nd.child_first[P] + 1);
 }
 
-// Mass and centre of mass of the leaves (all levels in one launch).
-__global__ __launch_bounds__(TB) void geometry_leaf_kernel(const int32_t* __restrict__ leaves, int64_t n_leaves,
-                                                           const int32_t* __restrict__ first,
-                                                           const int32_t* __restrict__ count,
-                                                           const double4* __restrict__ Xm, double4* __restrict__ S,
-                                                           double4* __restrict__ Z) {
-    const int64_t l = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (l >= n_leaves) return;
+// Mass and centre of mass of leaf l of the list (a leaf ends where the next
+// one starts: the list is in particle order).
+__device__ __forceinline__ void geometry_leaf(const int32_t* __restrict__ leaves, int64_t l, int64_t n_leaves,
+                                              const int32_t* __restrict__ first, int64_t n,
+                                              const double4* __restrict__ Xm, double4* __restrict__ S,
+                                              double4* __restrict__ Z) {
     const int32_t i = leaves[l];
     double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
     // loads issued eight at a time, sums kept strictly left to right
-    const int32_t s0 = first[i], s1 = s0 + count[i];
+    const int32_t s0 = first[i], s1 = l + 1 < n_leaves ? first[leaves[l + 1]] : (int32_t)n;
     for (int32_t q = s0; q < s1; q += 8) {
         double4 p[8];
 #pragma unroll
@@ -512,6 +723,21 @@ __global__ __launch_bounds__(TB) void geometry_leaf_kernel(const int32_t* __rest
     }
     S[i] = make_double4(sx, sy, sz, M);
     Z[i] = make_double4(sx / M, sy / M, sz / M, M);
+}
+
+// The first gl blocks: leaf geometry; the others: particle and child counts.
+__global__ __launch_bounds__(TB) void node_finish_kernel(NodeArrays nd, int64_t nn, int64_t n,
+                                                         const TreeHeader* __restrict__ h,
+                                                         const int32_t* __restrict__ leaves, int64_t n_leaves,
+                                                         unsigned gl, const double4* __restrict__ Xm,
+                                                         double4* __restrict__ S, double4* __restrict__ Z) {
+    if (blockIdx.x < gl) {
+        const int64_t l = (int64_t)blockIdx.x * TB + threadIdx.x;
+        if (l < n_leaves) geometry_leaf(leaves, l, n_leaves, nd.first, n, Xm, S, Z);
+    } else {
+        const int64_t c = (int64_t)(blockIdx.x - gl) * TB + threadIdx.x;
+        if (c < nn) node_finish(nd, c, n, h);
+    }
 }
 
 // Inner node: sums over its children in digit order.
@@ -555,46 +781,40 @@ __global__ __launch_bounds__(TB) void geometry_top_kernel(const int32_t* __restr
     }
 }
 
-__global__ __launch_bounds__(TB) void fill_u64_kernel(uint64_t* __restrict__ p, int64_t n, uint64_t v) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-// Exact r_max: the maximum squared distance of a node's particles from its
-// centre of mass.  Work items are (node, chunk of at most RCH particles) so the
-// root does not serialise on one wavefront; each item reduces its chunk across
-// the wave and issues one atomicMax on the bits of the (non-negative) double.
-// A maximum does not depend on the order of the atomics: deterministic.
+// Exact r_max, the maximum squared distance of a node's particles from its
+// centre of mass, and the walk's packed record of the node: geo = (centre of
+// mass, r_max), top = (child count + 16 x the siblings from this node to its
+// last, level, first child, set).  One wavefront per node; nodes of more than
+// RCH particles are cut into chunks of RCH, listed in items (in any order: the
+// chunks' maxima meet in an atomicMax on the bits of the non-negative double),
+// and finished by rmax_large_kernel and rmax_final_kernel.  Three launches (one
+// up to RCH particles) where a list of all (node, chunk) items took seven and
+// the walk's records one more.
 constexpr int RCH = 4096;
 
-__global__ __launch_bounds__(TB) void rmax_chunks_kernel(const int32_t* __restrict__ count, int64_t nn,
-                                                         uint32_t* __restrict__ c) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i < nn) c[i] = (uint32_t)((count[i] + RCH - 1) / RCH);
+struct NodePack {
+    const int64_t* set_off;
+    int n_sets;
+    double* rmax;
+    double4* geo;
+    int4* top;
+};
+
+__device__ __forceinline__ void pack_node(const NodeArrays& nd, const NodePack& pk, int32_t i, const double4& z,
+                                          double r2) {
+    const double r = sqrt(r2);
+    const int32_t P = nd.parent[i];
+    const int sib = P < 0 ? 1 : (int)(nd.child_first[P] + nd.nchild[P] - i);
+    pk.rmax[i] = r;
+    pk.geo[i] = make_double4(z.x, z.y, z.z, r);
+    pk.top[i] = make_int4(nd.nchild[i] | (sib << 4), nd.level[i], nd.child_first[i],
+                          set_of(pk.set_off, pk.n_sets, nd.first[i]));
 }
 
-__global__ __launch_bounds__(TB) void rmax_items_kernel(int64_t nn, const uint32_t* __restrict__ c,
-                                                        const uint32_t* __restrict__ base,
-                                                        int2* __restrict__ items) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i >= nn) return;
-    for (uint32_t k = 0; k < c[i]; ++k) items[base[i] + k] = make_int2((int32_t)i, (int32_t)k);
-}
-
-__global__ __launch_bounds__(kWave) void rmax_kernel(const uint32_t* __restrict__ n_items,
-                                                     const int2* __restrict__ items,
-                                                     const int32_t* __restrict__ first,
-                                                     const int32_t* __restrict__ count,
-                                                     const double4* __restrict__ Xm, const double4* __restrict__ Z,
-                                                     unsigned long long* __restrict__ r2bits) {
-    if (blockIdx.x >= *n_items) return;
-    const int2 it = items[blockIdx.x];
-    const int32_t s0 = first[it.x] + it.y * RCH;
-    const int32_t e = first[it.x] + count[it.x];
-    const int32_t s1 = (s0 + RCH < e) ? s0 + RCH : e;
-    const double4 z = Z[it.x];
+__device__ __forceinline__ double max_r2(const double4* __restrict__ Xm, int32_t s0, int32_t s1, const double4& z) {
+    const int lane = threadIdx.x & (kWave - 1);
     double m = 0.0;
-    for (int32_t s = s0 + (int32_t)threadIdx.x; s < s1; s += kWave) {
+    for (int32_t s = s0 + lane; s < s1; s += kWave) {
         const double4 x = Xm[s];
         const double dx = x.x - z.x, dy = x.y - z.y, dz = x.z - z.z;
         const double d2 = (dx * dx + dy * dy) + dz * dz;
@@ -605,13 +825,58 @@ __global__ __launch_bounds__(kWave) void rmax_kernel(const uint32_t* __restrict_
         const double u = __shfl_xor(m, o, kWave);
         m = u > m ? u : m;
     }
+    return m;
+}
+
+__global__ __launch_bounds__(TB) void rmax_kernel(NodeArrays nd, int64_t nn, const double4* __restrict__ Xm,
+                                                  const double4* __restrict__ Z, NodePack pk,
+                                                  unsigned long long* __restrict__ r2bits, int2* __restrict__ items,
+                                                  uint32_t* __restrict__ n_items) {
+    const int64_t i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (TB / kWave) + threadIdx.x / kWave));
+    if (i >= nn) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int32_t s0 = nd.first[i], cnt = nd.count[i];
+    if (cnt > RCH) {
+        const int nc = (cnt + RCH - 1) / RCH;
+        uint32_t at = 0;
+        if (lane == 0) {
+            r2bits[i] = 0ull;
+            at = atomicAdd(n_items, (uint32_t)nc);
+        }
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        for (int k = lane; k < nc; k += kWave) items[at + k] = make_int2((int32_t)i, k);
+        return;
+    }
+    const double4 z = Z[i];
+    const double m = max_r2(Xm, s0, s0 + cnt, z);
+    if (lane == 0) pack_node(nd, pk, (int32_t)i, z, m);
+}
+
+__global__ __launch_bounds__(kWave) void rmax_large_kernel(const uint32_t* __restrict__ n_items,
+                                                           const int2* __restrict__ items,
+                                                           const int32_t* __restrict__ first,
+                                                           const int32_t* __restrict__ count,
+                                                           const double4* __restrict__ Xm,
+                                                           const double4* __restrict__ Z,
+                                                           unsigned long long* __restrict__ r2bits) {
+    if (blockIdx.x >= *n_items) return;
+    const int2 it = items[blockIdx.x];
+    const int32_t s0 = first[it.x] + it.y * RCH;
+    const int32_t e = first[it.x] + count[it.x];
+    const double4 z = Z[it.x];
+    const double m = max_r2(Xm, s0, (s0 + RCH < e) ? s0 + RCH : e, z);
     if (threadIdx.x == 0) atomicMax(&r2bits[it.x], (unsigned long long)__double_as_longlong(m));
 }
 
-__global__ __launch_bounds__(TB) void rmax_final_kernel(const unsigned long long* __restrict__ r2bits,
-                                                        int64_t nn, double* __restrict__ rmax) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i < nn) rmax[i] = sqrt(__longlong_as_double((long long)r2bits[i]));
+__global__ __launch_bounds__(TB) void rmax_final_kernel(const uint32_t* __restrict__ n_items,
+                                                        const int2* __restrict__ items, NodeArrays nd,
+                                                        const double4* __restrict__ Z, NodePack pk,
+                                                        const unsigned long long* __restrict__ r2bits) {
+    const uint32_t ni = *n_items;
+    for (uint32_t k = blockIdx.x * TB + threadIdx.x; k < ni; k += gridDim.x * TB) {
+        const int2 it = items[k];
+        if (it.y == 0) pack_node(nd, pk, it.x, Z[it.x], __longlong_as_double((long long)r2bits[it.x]));
+    }
 }
 
 template <typename T>
@@ -674,91 +939,105 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     const int64_t n = t.n;
     const size_t un = (size_t)n;
 
-    // bounding cube and key scale of every set, on the device (no read-back)
     const int ns = t.n_sets;
     const int64_t* soff = ns > 1 ? t.set_off.as<int64_t>() : nullptr;
-    const int nbb = (int)std::min<int64_t>(1024, cdiv(n, TB));
-    t.scratch.ensure(ctx, std::max<size_t>({(size_t)nbb * 7 * 8 + 64, sort_scratch_bytes(n, 3 * kLevels) + 256,
-                                            scan_scratch_bytes(n) + 256}));
-    t.cube.ensure(ctx, (size_t)ns * 16 * sizeof(double));
-    double* part = t.scratch.as<double>();
+    const int64_t nblk = cdiv(n, TB);
+    const int nbb = (int)std::min<int64_t>(256, nblk);
+    t.scratch.ensure(ctx, std::max<size_t>(sort_scratch_bytes(n, 3 * kLevels) + 256, scan_scratch_bytes(n) + 256));
+    // the key cubes, then the partial boxes of a single set
+    t.cube.ensure(ctx, (size_t)(ns * 16 + nbb * 7) * sizeof(double));
     double* cube = t.cube.as<double>();
-    if (ns > 1) {
-        hipLaunchKernelGGL(bbox_sets_kernel, dim3((unsigned)ns), dim3(TB), 0, s, pos, soff, cube);
-        TFMM_LAUNCHED();
-    } else {
-        hipLaunchKernelGGL(bbox_partial_kernel, dim3(nbb), dim3(TB), 0, s, pos, n, part);
-        TFMM_LAUNCHED();
-        hipLaunchKernelGGL(bbox_final_kernel, dim3(1), dim3(TB), 0, s, (const double*)part, nbb, cube);
-        TFMM_LAUNCHED();
-    }
-
-    // keys and stable order (by set, then by key)
+    double* part = cube + ns * 16;
     t.keys.ensure(ctx, un * 8);
-    t.keys2.ensure(ctx, un * 8);
     t.perm.ensure(ctx, un * 4);
-    t.perm2.ensure(ctx, un * 4);
-    hipLaunchKernelGGL(morton_kernel, dim3(grid(n)), dim3(TB), 0, s, pos, n, (const double*)cube, soff, ns,
-                       t.keys.as<uint64_t>(), t.perm.as<int32_t>());
-    TFMM_LAUNCHED();
-    radix_sort_u64(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(), t.perm2.as<int32_t>(),
-                   n, 3 * kLevels, t.scratch.p, ctx->dev_err, s);
-    if (ns > 1) {
-        int bits = 1;
-        while ((1 << bits) < ns) ++bits;
-        t.set_sort.ensure(ctx, un * 16);
-        uint32_t* skey = t.set_sort.as<uint32_t>();
-        int32_t* spos = reinterpret_cast<int32_t*>(skey + n);
-        uint32_t* skey2 = skey + 2 * n;
-        int32_t* spos2 = reinterpret_cast<int32_t*>(skey + 3 * n);
-        hipLaunchKernelGGL(set_keys_kernel, dim3(grid(n)), dim3(TB), 0, s, (const int32_t*)t.perm.as<int32_t>(), n,
-                           soff, ns, skey, spos);
-        TFMM_LAUNCHED();
-        radix_sort_u32(skey, spos, skey2, spos2, n, bits, t.scratch.p, ctx->dev_err, s);
-        hipLaunchKernelGGL(set_apply_kernel, dim3(grid(n)), dim3(TB), 0, s, (const int32_t*)spos, n,
-                           (const uint64_t*)t.keys.as<uint64_t>(), (const int32_t*)t.perm.as<int32_t>(),
-                           t.keys2.as<uint64_t>(), t.perm2.as<int32_t>());
-        TFMM_LAUNCHED();
-        std::swap(t.keys.p, t.keys2.p);
-        std::swap(t.keys.cap, t.keys2.cap);
-        std::swap(t.perm.p, t.perm2.p);
-        std::swap(t.perm.cap, t.perm2.cap);
-    }
-
-    // sorted particles, boundary levels
     t.Xm.ensure(ctx, un * 32);
     t.lvlb.ensure(ctx, un);
-    t.owner.ensure(ctx, un * 2);
+    t.owner.ensure(ctx, un);
     t.leaf_of.ensure(ctx, un * 4);
-    hipLaunchKernelGGL(gather_kernel, dim3(grid(n)), dim3(TB), 0, s, pos, mass, t.keys.as<uint64_t>(),
-                       t.perm.as<int32_t>(), n, soff, ns, t.Xm.as<double4>(), t.lvlb.as<uint8_t>());
-    TFMM_LAUNCHED();
-
-    // octree: leaf level of every particle, node starts per level, node table
-    const int64_t nblk = cdiv(n, TB);
-    const int64_t nw = n - t.n_leaf;  // windows of n_leaf + 1 consecutive keys
-    // cl (int8, n) and lambda (uint8, n) share the owner buffer
-    int8_t* cl = reinterpret_cast<int8_t*>(t.owner.as<int32_t>());
-    uint8_t* lam = reinterpret_cast<uint8_t*>(cl + n);
-    t.flags.ensure(ctx, std::max<size_t>(un * 8, (size_t)(NSLOT * nblk + NSLOT) * 4));
-    uint32_t* cnt = t.flags.as<uint32_t>();
-    uint32_t* tot = cnt + NSLOT * nblk;
+    // header, a counter of finished blocks, the count of r_max items
     t.scratch2.ensure(ctx, sizeof(TreeHeader) + 256);
     TreeHeader* hdr = t.scratch2.as<TreeHeader>();
-    if (nw > 0) {
-        hipLaunchKernelGGL(window_level_kernel, dim3(grid(nw)), dim3(TB), 0, s, (const uint64_t*)t.keys.as<uint64_t>(),
-                           nw, t.n_leaf, soff, ns, cl);
+    uint32_t* done = reinterpret_cast<uint32_t*>(hdr + 1);
+    uint32_t* n_items = done + 1;
+    uint8_t* lam = t.owner.as<uint8_t>();
+    t.flags.ensure(ctx, (size_t)(NSLOT * nblk + NSLOT) * 4);
+    uint32_t* cnt = t.flags.as<uint32_t>();
+    uint32_t* tot = cnt + NSLOT * nblk;
+
+    // cubes, keys, stable order (by set, then by key), sorted particles and
+    // boundary levels, on the device (no read-back)
+    if (ns == 1 && n <= kSmallSort) {
+        auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(1), dim3(ST), 0, s, pos, mass, (int)n, cube, t.keys.as<uint64_t>(),
+                               t.perm.as<int32_t>(), t.Xm.as<double4>(), t.lvlb.as<uint8_t>());
+            TFMM_LAUNCHED();
+        };
+        if (n <= 2 * ST) run(small_sort_kernel<2>);
+        else if (n <= 4 * ST) run(small_sort_kernel<4>);
+        else run(small_sort_kernel<8>);
+    } else {
+        t.keys2.ensure(ctx, un * 8);
+        t.perm2.ensure(ctx, un * 4);
+        int64_t words = 0;
+        uint32_t* counts = sort_counts(t.scratch.p, n, 3 * kLevels, &words);
+        if (ns > 1) {
+            counts = nullptr;
+            hipLaunchKernelGGL(bbox_sets_kernel, dim3((unsigned)ns), dim3(TB), 0, s, pos, soff, cube);
+        } else {
+            hipLaunchKernelGGL(bbox_partial_kernel, dim3(nbb), dim3(TB), 0, s, pos, n, part,
+                               t.scratch.as<unsigned long long>(), words);
+        }
+        TFMM_LAUNCHED();
+        // blocks of 1024 particles, of 4096 when there are many (a block adds up
+        // to 2048 digit totals)
+        const int per = !counts ? 1 : (n < (1 << 19) ? 4 : 16);
+        hipLaunchKernelGGL(morton_kernel, dim3((unsigned)cdiv(n, (int64_t)per * TB)), dim3(TB), 0, s, pos, n,
+                           (const double*)part, nbb, cube, soff, ns, per, t.keys.as<uint64_t>(),
+                           t.perm.as<int32_t>(), counts);
+        TFMM_LAUNCHED();
+        if (counts)
+            radix_sort_u64_counted(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(),
+                                   t.perm2.as<int32_t>(), n, 3 * kLevels, t.scratch.p, ctx->dev_err, s);
+        else
+            radix_sort_u64(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(),
+                           t.perm2.as<int32_t>(), n, 3 * kLevels, t.scratch.p, ctx->dev_err, s);
+        if (ns > 1) {
+            int bits = 1;
+            while ((1 << bits) < ns) ++bits;
+            t.set_sort.ensure(ctx, un * 16);
+            uint32_t* skey = t.set_sort.as<uint32_t>();
+            int32_t* spos = reinterpret_cast<int32_t*>(skey + n);
+            uint32_t* skey2 = skey + 2 * n;
+            int32_t* spos2 = reinterpret_cast<int32_t*>(skey + 3 * n);
+            hipLaunchKernelGGL(set_keys_kernel, dim3(grid(n)), dim3(TB), 0, s, (const int32_t*)t.perm.as<int32_t>(),
+                               n, soff, ns, skey, spos);
+            TFMM_LAUNCHED();
+            radix_sort_u32(skey, spos, skey2, spos2, n, bits, t.scratch.p, ctx->dev_err, s);
+            hipLaunchKernelGGL(set_apply_kernel, dim3(grid(n)), dim3(TB), 0, s, (const int32_t*)spos, n,
+                               (const uint64_t*)t.keys.as<uint64_t>(), (const int32_t*)t.perm.as<int32_t>(),
+                               t.keys2.as<uint64_t>(), t.perm2.as<int32_t>());
+            TFMM_LAUNCHED();
+            std::swap(t.keys.p, t.keys2.p);
+            std::swap(t.keys.cap, t.keys2.cap);
+            std::swap(t.perm.p, t.perm2.p);
+            std::swap(t.perm.cap, t.perm2.cap);
+        }
+        hipLaunchKernelGGL(gather_kernel, dim3(grid(n)), dim3(TB), 0, s, pos, mass, t.keys.as<uint64_t>(),
+                           t.perm.as<int32_t>(), n, soff, ns, t.Xm.as<double4>(), t.lvlb.as<uint8_t>());
         TFMM_LAUNCHED();
     }
-    hipLaunchKernelGGL(leaf_level_kernel, dim3((unsigned)nblk), dim3(TB), 0, s, (const int8_t*)cl, n, t.n_leaf,
-                       (const uint8_t*)t.lvlb.as<uint8_t>(), lam, cnt, nblk);
+
+    // octree: leaf level of every particle, node starts per level, node table
+    hipLaunchKernelGGL(leaf_level_kernel, dim3((unsigned)nblk), dim3(TB), 0, s,
+                       (const uint64_t*)t.keys.as<uint64_t>(), n, t.n_leaf, soff, ns,
+                       (const uint8_t*)t.lvlb.as<uint8_t>(), lam, cnt, nblk, done);
     TFMM_LAUNCHED();
-    hipLaunchKernelGGL(slot_scan_kernel, dim3(NSLOT), dim3(TB), 0, s, cnt, nblk, tot);
+    const Mailbox mb = mailbox_next(ctx);
+    hipLaunchKernelGGL(slot_scan_kernel, dim3(NSLOT), dim3(TB), 0, s, cnt, nblk, tot, done, (const double*)cube, ns,
+                       hdr, mb);
     TFMM_LAUNCHED();
-    hipLaunchKernelGGL(tree_header_kernel, dim3(1), dim3(kWave), 0, s, (const uint32_t*)tot, (const double*)cube, ns,
-                       hdr);
-    TFMM_LAUNCHED();
-    const TreeHeader H = read_back_checked(ctx, (const TreeHeader*)hdr, s);
+    TreeHeader H;
+    mailbox_wait(ctx, mb.seq, sizeof(TreeHeader), &H, true, s);
     if (H.nonfinite) fail(TFMM_EINVAL, "positions contain non-finite values");
     t.n_nodes = H.n_nodes;
     t.max_level = (int)H.max_level;
@@ -769,25 +1048,21 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     ensure_nodes(t, std::max<int64_t>(nn, 1), 0, s);
     NodeArrays nd = node_arrays(t);
     t.leaves.ensure(ctx, (size_t)std::max<int64_t>(t.n_leaves, 1) * 4);
+    t.nd_S.ensure(ctx, (size_t)nn * 32);
+    t.nd_Z.ensure(ctx, (size_t)nn * 32);
     hipLaunchKernelGGL(node_create_kernel, dim3((unsigned)nblk), dim3(TB), 0, s, nd, n,
                        (const uint64_t*)t.keys.as<uint64_t>(), (const uint8_t*)t.lvlb.as<uint8_t>(),
                        (const uint8_t*)lam, (const uint32_t*)cnt, nblk, (const TreeHeader*)hdr,
-                       t.leaf_of.as<int32_t>(), t.leaves.as<int32_t>());
+                       t.leaf_of.as<int32_t>(), t.leaves.as<int32_t>(), n_items);
     TFMM_LAUNCHED();
-    hipLaunchKernelGGL(node_finish_kernel, dim3(grid(nn)), dim3(TB), 0, s, nd, nn, n, (const TreeHeader*)hdr);
-    TFMM_LAUNCHED();
-    t.flags.ensure(ctx, (size_t)std::max<int64_t>(n, nn) * 4 * 2);
-    t.scratch.ensure(ctx, scan_scratch_bytes(std::max<int64_t>(n, nn)) + 256);
-    uint32_t* total = reinterpret_cast<uint32_t*>(t.scratch2.as<char>() + sizeof(TreeHeader));
-
-    // geometry: leaves, then inner nodes level by level, deepest first; the
-    // top levels (at most kTopNodes nodes together) in a single block
-    t.nd_S.ensure(ctx, (size_t)nn * 32);
-    t.nd_Z.ensure(ctx, (size_t)nn * 32);
-    hipLaunchKernelGGL(geometry_leaf_kernel, dim3(grid(t.n_leaves)), dim3(TB), 0, s,
-                       (const int32_t*)t.leaves.as<int32_t>(), t.n_leaves, nd.first, nd.count, t.Xm.as<double4>(),
+    const unsigned gl = grid(t.n_leaves);
+    hipLaunchKernelGGL(node_finish_kernel, dim3(gl + grid(nn)), dim3(TB), 0, s, nd, nn, n, (const TreeHeader*)hdr,
+                       (const int32_t*)t.leaves.as<int32_t>(), t.n_leaves, gl, (const double4*)t.Xm.as<double4>(),
                        t.nd_S.as<double4>(), t.nd_Z.as<double4>());
     TFMM_LAUNCHED();
+
+    // geometry of the inner nodes level by level, deepest first; the
+    // top levels (at most kTopNodes nodes together) in a single block
     {
         constexpr int64_t kTopNodes = 1024;
         int top = -1;
@@ -807,32 +1082,29 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
             TFMM_LAUNCHED();
         }
     }
-    t.nd_r2bits.ensure(ctx, (size_t)nn * 8);
     t.nd_rmax.ensure(ctx, (size_t)nn * 8);
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(grid(nn)), dim3(TB), 0, s, t.nd_r2bits.as<uint64_t>(), nn,
-                       (uint64_t)0);
+    t.w_geo.ensure(ctx, (size_t)nn * sizeof(double4));
+    t.w_top.ensure(ctx, (size_t)nn * sizeof(int4));
+    t.nd_r2bits.ensure(ctx, (size_t)nn * 8);
+    // chunks of large nodes: every level's hold each particle at most once
+    const int64_t ub = n > RCH ? 2 * (n * (t.max_level + 1) / RCH) + 1 : 0;
+    t.rmax_items.ensure(ctx, (size_t)std::max<int64_t>(ub, 1) * 8);
+    const NodePack pk{soff, ns, t.nd_rmax.as<double>(), t.w_geo.as<double4>(), t.w_top.as<int4>()};
+    hipLaunchKernelGGL(rmax_kernel, dim3((unsigned)cdiv(nn, TB / kWave)), dim3(TB), 0, s, nd, nn,
+                       (const double4*)t.Xm.as<double4>(), (const double4*)t.nd_Z.as<double4>(), pk,
+                       t.nd_r2bits.as<unsigned long long>(), t.rmax_items.as<int2>(), n_items);
     TFMM_LAUNCHED();
-    {
-        // items (node, chunk); the launch covers an upper bound and reads the count on the device
-        const int64_t ub = nn + (int64_t)n * (t.max_level + 1) / RCH + 1;
-        t.flags.ensure(ctx, (size_t)std::max<int64_t>(n, nn) * 4 * 2);
-        uint32_t* c = t.flags.as<uint32_t>();
-        uint32_t* base = c + std::max<int64_t>(n, nn);
-        t.rmax_items.ensure(ctx, (size_t)ub * 8);
-        hipLaunchKernelGGL(rmax_chunks_kernel, dim3(grid(nn)), dim3(TB), 0, s, nd.count, nn, c);
-        TFMM_LAUNCHED();
-        exclusive_scan_u32(c, base, nn, t.scratch.p, total, s);
-        hipLaunchKernelGGL(rmax_items_kernel, dim3(grid(nn)), dim3(TB), 0, s, nn, (const uint32_t*)c,
-                           (const uint32_t*)base, t.rmax_items.as<int2>());
-        TFMM_LAUNCHED();
-        hipLaunchKernelGGL(rmax_kernel, dim3((unsigned)ub), dim3(kWave), 0, s, (const uint32_t*)total,
+    if (ub > 0) {
+        hipLaunchKernelGGL(rmax_large_kernel, dim3((unsigned)ub), dim3(kWave), 0, s, (const uint32_t*)n_items,
                            (const int2*)t.rmax_items.as<int2>(), nd.first, nd.count, t.Xm.as<double4>(),
                            t.nd_Z.as<double4>(), t.nd_r2bits.as<unsigned long long>());
         TFMM_LAUNCHED();
+        hipLaunchKernelGGL(rmax_final_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(ub, TB))), dim3(TB), 0, s,
+                           (const uint32_t*)n_items, (const int2*)t.rmax_items.as<int2>(), nd,
+                           (const double4*)t.nd_Z.as<double4>(), pk,
+                           (const unsigned long long*)t.nd_r2bits.as<unsigned long long>());
+        TFMM_LAUNCHED();
     }
-    hipLaunchKernelGGL(rmax_final_kernel, dim3(grid(nn)), dim3(TB), 0, s, t.nd_r2bits.as<unsigned long long>(),
-                       nn, t.nd_rmax.as<double>());
-    TFMM_LAUNCHED();
 
     t.walk_valid = false;
     t.mom_p = -1;

@@ -33,7 +33,7 @@ namespace {
 
 constexpr int TB = 256;
 
-// Per node, packed for the walk: geo = (centre of mass x, y, z, r_max),
+// Per node, packed for the walk by the tree build: geo = (centre of mass x, y, z, r_max),
 // top = (child count + 16 x the siblings from this node to its last, level,
 // first child, set).  theta: per set (forests walked with several thetas),
 // else nullptr and the passes' scalar applies.
@@ -43,24 +43,6 @@ struct WalkNodes {
     const double* theta;
     int32_t nn;
 };
-
-__global__ __launch_bounds__(TB) void walk_nodes_kernel(int64_t nn, const double4* __restrict__ Z,
-                                                        const double* __restrict__ rmax,
-                                                        const int32_t* __restrict__ nchild,
-                                                        const int32_t* __restrict__ level,
-                                                        const int32_t* __restrict__ child_first,
-                                                        const int32_t* __restrict__ parent,
-                                                        const int32_t* __restrict__ first,
-                                                        const int64_t* __restrict__ set_off, int n_sets,
-                                                        double4* __restrict__ geo, int4* __restrict__ top) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i >= nn) return;
-    const double4 z = Z[i];
-    geo[i] = make_double4(z.x, z.y, z.z, rmax[i]);
-    const int32_t P = parent[i];
-    const int sib = P < 0 ? 1 : (int)(child_first[P] + nchild[P] - (int32_t)i);
-    top[i] = make_int4(nchild[i] | (sib << 4), level[i], child_first[i], set_of(set_off, n_sets, first[i]));
-}
 
 constexpr int kRun = 8;  // lanes per frontier entry: the most siblings
 
@@ -873,15 +855,6 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t 
         upload(t, t.set_theta, theta_keep.data(), theta_keep.size() * sizeof(double), 1, s);
         theta_dev = t.set_theta.as<double>();
     }
-    t.w_geo.ensure(ctx, (size_t)std::max<int64_t>(nn, 1) * sizeof(double4));
-    t.w_top.ensure(ctx, (size_t)std::max<int64_t>(nn, 1) * sizeof(int4));
-    hipLaunchKernelGGL(walk_nodes_kernel, dim3(grid(nn)), dim3(TB), 0, s, nn, (const double4*)t.nd_Z.as<double4>(),
-                       (const double*)t.nd_rmax.as<double>(), (const int32_t*)t.nd_nchild.as<int32_t>(),
-                       (const int32_t*)t.nd_level.as<int32_t>(), (const int32_t*)t.nd_child_first.as<int32_t>(),
-                       (const int32_t*)t.nd_parent.as<int32_t>(), (const int32_t*)t.nd_first.as<int32_t>(),
-                       t.n_sets > 1 ? (const int64_t*)t.set_off.as<int64_t>() : nullptr, t.n_sets,
-                       t.w_geo.as<double4>(), t.w_top.as<int4>());
-    TFMM_LAUNCHED();
     WalkNodes w{t.w_geo.as<double4>(), t.w_top.as<int4>(), theta_dev, (int32_t)nn};
     t.walk_valid = false;
     if (!walk_bfs_async(t, w, theta_keep, s)) walk_bfs_sized(t, w, theta, s);

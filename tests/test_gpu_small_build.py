@@ -1,0 +1,74 @@
+"""The tree build's routes: a small single set is sorted by one workgroup, a
+larger one and every forest by the radix passes; nodes of more than 4096
+particles take their r_max in chunks.  Checked where the routes change against
+numpy's stable sort and exact maxima, and against the same set in a forest.
+"""
+import numpy as np
+import pytest
+
+from paper_2107_07166_amd import generators as g
+
+pytestmark = pytest.mark.gpu
+
+
+def _set(n, kind):
+    pos, mass = g.plummer(n, 31 + n)
+    if kind == "ties":  # coincident particles: equal keys keep their input order
+        pos[n // 3:] = pos[np.arange(n - n // 3) % max(n // 5, 1)]
+    return pos, mass
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 20000])
+@pytest.mark.parametrize("kind", ["plummer", "ties"])
+def test_build_routes(n, kind):
+    import torch
+
+    from paper_2107_07166_amd import api
+
+    dev = torch.device("cuda:0")
+    pos, mass = _set(n, kind)
+    ctx = api.Context(0)
+    tree = api.Tree(ctx, torch.from_numpy(pos).to(dev), torch.from_numpy(mass).to(dev), n_leaf=16)
+    a = tree.export()
+    tree.close()
+    np.testing.assert_array_equal(a["order"], np.argsort(a["keys"], kind="stable"))
+    # r_max: the largest distance from the exported centre, operations in the build's order
+    x = pos[a["order"]]
+    for i in range(0, len(a["first"]), max(1, len(a["first"]) // 50)):
+        d = x[a["first"][i]:a["first"][i] + a["count"][i]] - a["com"][i]
+        r2 = ((d[:, 0] * d[:, 0] + d[:, 1] * d[:, 1]) + d[:, 2] * d[:, 2]).max()
+        assert a["rmax"][i] == np.sqrt(r2)
+    # the same set as the first of a forest
+    fill, fmass = g.uniform_ball(100, 1)
+    tree = api.Tree(ctx, torch.from_numpy(np.concatenate([pos, fill])).to(dev),
+                    torch.from_numpy(np.concatenate([mass, fmass])).to(dev), n_leaf=16, offsets=[0, n, n + 100])
+    b = tree.export()
+    tree.close()
+    ctx.close()
+    mine = b["first"] < n
+    np.testing.assert_array_equal(a["keys"], b["keys"][:n])
+    np.testing.assert_array_equal(a["order"], b["order"][:n])
+    for k in ("level", "prefix", "first", "count", "nchild", "com", "mass", "rmax"):
+        np.testing.assert_array_equal(a[k], b[k][mine], err_msg=k)
+
+
+@pytest.mark.parametrize("n", [3000, 30000])
+def test_nonfinite_is_refused_and_the_tree_survives(n):
+    import torch
+
+    from paper_2107_07166_amd import api
+    from paper_2107_07166_amd._lib import TfmmError
+
+    dev = torch.device("cuda:0")
+    pos, mass = (torch.from_numpy(a).to(dev) for a in g.plummer(n, 4))
+    ctx = api.Context(0)
+    tree = api.Tree(ctx, pos, mass)
+    f = tree.evaluate(p=2).clone()
+    bad = pos.clone()
+    bad[n // 2, 1] = float("nan")
+    with pytest.raises(TfmmError):
+        tree.rebuild(bad, mass)
+    tree.rebuild(pos, mass)
+    assert torch.equal(f, tree.evaluate(p=2))
+    tree.close()
+    ctx.close()
