@@ -251,6 +251,7 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     compute_moments(t, pe, a);
     if (t.timing) TFMM_HIP(hipEventRecord(t.ev[1], a));
     prepare_sources(t, prm->precision, s);
+    PendingLists pending(t, s);
     if (need_walk) {
         t.walk_valid = false;
         if (t.timing) TFMM_HIP(hipEventRecord(t.ev[11], s));

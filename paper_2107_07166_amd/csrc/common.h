@@ -108,6 +108,39 @@ __device__ __forceinline__ double dpp(double v) {
     return __longlong_as_double((long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
+// Lanes of the wavefront (all of which call it) that are valid and agree with
+// this one in the low bits of d.  Per bit one ballot and one three-input logic
+// operation per half: keep the peers whose bit equals this lane's.
+template <int BITS>
+__device__ __forceinline__ uint64_t same_lanes(bool valid, uint32_t d) {
+    const uint64_t v = __ballot(valid);
+    uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const uint32_t mine = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // all ones if bit b is set
+        const uint64_t m = __ballot(mine != 0u);
+        lo &= ~((uint32_t)m ^ mine);
+        hi &= ~((uint32_t)(m >> 32) ^ mine);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+// The same for a number of bits known at run time (up to 10).
+__device__ __forceinline__ uint64_t same_lanes(bool valid, uint32_t d, int bits) {
+    switch (bits) {
+        case 0: return same_lanes<0>(valid, d);
+        case 1: return same_lanes<1>(valid, d);
+        case 2: return same_lanes<2>(valid, d);
+        case 3: return same_lanes<3>(valid, d);
+        case 4: return same_lanes<4>(valid, d);
+        case 5: return same_lanes<5>(valid, d);
+        case 6: return same_lanes<6>(valid, d);
+        case 7: return same_lanes<7>(valid, d);
+        case 8: return same_lanes<8>(valid, d);
+        case 9: return same_lanes<9>(valid, d);
+        default: return same_lanes<10>(valid, d);
+    }
+}
+
 // Sum over each group of 4 or 8 lanes, the result in every lane of the group.
 template <int LANES>
 __device__ __forceinline__ double group_sum(double v) {
@@ -201,10 +234,11 @@ struct Tree {
     std::vector<double> walk_theta;  // theta of the last walk: one value, or one per set
     int64_t n_m2l = -1, n_p2p = -1, n_near_int = -1;
     DevBuf m2l_pairs, p2p_pairs;  // int2, lower node id first
-    DevBuf m2l_off, m2l_src;      // per-target CSR, directed: source = m2l_src[q] & m2l_src_mask
-    uint32_t m2l_src_mask = 0xffffffffu;  // 0xffff when entries are packed (target << 16) | source
-    DevBuf p2p_off, p2p_src;
-    DevBuf w_fr, w_fr2, w_cnt, w_off, w_tg, w_sr, w_fl, w_c;  // walk and list-building scratch
+    DevBuf m2l_off, m2l_src;      // far lists: sources m2l_src[m2l_off[t]] .. [m2l_off[t + 1]]
+    DevBuf p2p_off, p2p_src;      // near lists: sources p2p_src[p2p_off[t]] .. [p2p_l1[t]]
+    const uint32_t* p2p_l1 = nullptr;  // the lists' ends (inside p2p_off)
+    uint32_t list_mb = 0;         // read-back of the list totals under way (0: none)
+    DevBuf w_fr, w_fr2, w_off, w_tg, w_fl, w_c;  // walk and list-building scratch
     DevBuf w_state, w_res, w_dec; // device-side walk counters, list totals, pair decisions
     DevBuf w_geo, w_top;          // per node, packed for the walk (COM + r_max; children, level)
     // sizes seen by the previous walk of this tree (capacity hints for the
@@ -240,7 +274,7 @@ struct Tree {
     // stream with events; default priority
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-    DevBuf scratch_b, scratch2_b, w_tg_b, w_sr_b;  // the near-list chain's own scratch
+    DevBuf scratch_b, scratch2_b, w_tg_b;  // the near-list chain's own scratch
 
     // timing: events of the latest timed evaluation, and the phase times of
     // the earlier ones added up (taken at the next timed evaluation, when its
@@ -293,11 +327,6 @@ void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, i
 void radix_sort_pairs(const int2* pairs, int64_t np, bool self_dummy, uint32_t self_key, uint32_t* keys,
                       int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int bits, void* scratch,
                       uint32_t* err, hipStream_t s);
-// The same entries packed as (x << 16) | y words (node ids below 2^16),
-// stably sorted by their high half (its low `bits` bits); no values.
-void radix_sort_pairs_packed16(const int2* pairs, int64_t np, uint32_t* keys, uint32_t* keys_alt, int bits,
-                               void* scratch, uint32_t* err, hipStream_t s);
-
 // Mailbox layout: word 0 the sequence number of the last read-back, word 1
 // the device error word, the payload from word kBoxHeaderWords on.
 constexpr int kBoxHeaderWords = 16;
@@ -358,6 +387,21 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta, hipStream_t s, 
 void walk_lists_end(Tree& t, hipStream_t s);
 void aux_fork(Tree& t, hipStream_t s);
 void aux_join(Tree& t, hipStream_t s);
+void build_far_lists(Tree& t, hipStream_t s);
+void build_near_lists(Tree& t, hipStream_t s);
+void near_lists_end(Tree& t, hipStream_t s);
+// From walk_lists_begin to walk_lists_end the list totals may be on their way
+// to the mailbox; if that stretch is left by an error, they have to arrive
+// before the mailbox serves another read-back.
+struct PendingLists {
+    Tree& t;
+    hipStream_t s;
+    PendingLists(Tree& tree, hipStream_t stream) : t(tree), s(stream) { t.list_mb = 0u; }
+    ~PendingLists() {
+        if (t.list_mb) (void)hipStreamSynchronize(s);
+        t.list_mb = 0u;
+    }
+};
 int64_t near_interactions(Tree& t);
 void compute_moments(Tree& t, int p, hipStream_t s);
 void prepare_sources(Tree& t, int precision, hipStream_t s);

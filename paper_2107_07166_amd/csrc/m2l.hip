@@ -59,7 +59,7 @@ __device__ __forceinline__ T row_sum(T v) {
 template <int P, int VAR, typename T, bool POTL = false>
 __global__ __launch_bounds__(MB) void m2l_kernel(int64_t n_targets,
                                                  const uint32_t* __restrict__ off,
-                                                 const uint32_t* __restrict__ src, uint32_t src_mask,
+                                                 const uint32_t* __restrict__ src,
                                                  const double4* __restrict__ Z, const T* __restrict__ W,
                                                  int64_t wstride, double eps2, double* __restrict__ loc) {
     using E = Expansion<P>;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(MB) void m2l_kernel(int64_t n_targets,
     for (int k = 0; k < NOUT; ++k) acc[k] = T(0);
     const uint32_t q0 = has ? off[A] : 0u, q1 = has ? off[A + 1] : 0u;
     for (uint32_t q = q0 + sl; q < q1; q += LPT) {
-        const int32_t B = (int32_t)(src[q] & src_mask);
+        const int32_t B = (int32_t)src[q];
         const double4 zb = Z[B];
         const T Rx = (T)(za.x - zb.x), Ry = (T)(za.y - zb.y), Rz = (T)(za.z - zb.z);
         const T s = Rx * Rx + Ry * Ry + Rz * Rz + (T)eps2;
@@ -155,7 +155,7 @@ constexpr int cons_pass_waves(int P, int PS, int MASK, int tsize) {
 template <int P, int PS, int MASK, typename T>
 __global__ __launch_bounds__(MB) __attribute__((amdgpu_waves_per_eu(cons_pass_waves(P, PS, MASK, sizeof(T)))))
 void m2l_cons_pass_kernel(int64_t n_targets, const uint32_t* __restrict__ off,
-                          const uint32_t* __restrict__ src, uint32_t src_mask,
+                          const uint32_t* __restrict__ src,
                           const double4* __restrict__ Z, const T* __restrict__ W,
                           double eps2, double* __restrict__ loc) {
     using E = Expansion<P>;
@@ -177,7 +177,7 @@ void m2l_cons_pass_kernel(int64_t n_targets, const uint32_t* __restrict__ off,
     for (int k = 0; k < NPOLY * NC1; ++k) acc[k] = T(0);
     const uint32_t q0 = has ? off[A] : 0u, q1 = has ? off[A + 1] : 0u;
     for (uint32_t q = q0 + sl; q < q1; q += LPT) {
-        const int32_t B = (int32_t)(src[q] & src_mask);
+        const int32_t B = (int32_t)src[q];
         const double4 zb = Z[B];
         const T Rx = (T)(za.x - zb.x), Ry = (T)(za.y - zb.y), Rz = (T)(za.z - zb.z);
         const T s = Rx * Rx + Ry * Ry + Rz * Rz + (T)eps2;
@@ -254,7 +254,7 @@ void launch(Tree& t, double eps2, hipStream_t s) {
     if constexpr (VAR == TFMM_CONSERVING && P >= kConsSplitP) {
         auto pass = [&](auto kern) {
             hipLaunchKernelGGL(kern, grid, dim3(mb), 0, s, nt, t.m2l_off.template as<uint32_t>(),
-                               t.m2l_src.template as<uint32_t>(), t.m2l_src_mask, t.nd_Z.template as<double4>(), W,
+                               t.m2l_src.template as<uint32_t>(), t.nd_Z.template as<double4>(), W,
                                eps2, t.loc.template as<double>());
             TFMM_LAUNCHED();
         };
@@ -264,7 +264,7 @@ void launch(Tree& t, double eps2, hipStream_t s) {
         pass(m2l_cons_pass_kernel<P, P, 0x8, T>);
     } else {
         hipLaunchKernelGGL((m2l_kernel<P, VAR, T>), grid, dim3(mb), 0, s, nt,
-                           t.m2l_off.as<uint32_t>(), t.m2l_src.as<uint32_t>(), t.m2l_src_mask, t.nd_Z.as<double4>(), W,
+                           t.m2l_off.as<uint32_t>(), t.m2l_src.as<uint32_t>(), t.nd_Z.as<double4>(), W,
                            (int64_t)round_up(c_le(P), 4), eps2, t.loc.as<double>());
         TFMM_LAUNCHED();
     }
@@ -283,7 +283,7 @@ void launch_knob(Tree& t, double eps2, hipStream_t s) {
     const dim3 grid((unsigned)cdiv(cdiv(nt, TPW) * kWave, mb));
     auto pass = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, dim3(mb), 0, s, nt, t.m2l_off.template as<uint32_t>(),
-                           t.m2l_src.template as<uint32_t>(), t.m2l_src_mask, t.nd_Z.template as<double4>(), W, eps2,
+                           t.m2l_src.template as<uint32_t>(), t.nd_Z.template as<double4>(), W, eps2,
                            t.loc.template as<double>());
         TFMM_LAUNCHED();
     };
@@ -328,7 +328,7 @@ void launch_pot(Tree& t, int mom_p, double eps2, hipStream_t s) {
     const T* W = (sizeof(T) == 4) ? reinterpret_cast<const T*>(t.W32.p) : reinterpret_cast<const T*>(t.W64.p);
     const dim3 grid((unsigned)cdiv(cdiv(nt, TPW) * kWave, MB));
     hipLaunchKernelGGL((m2l_kernel<P, TFMM_STANDARD, T, true>), grid, dim3(MB), 0, s, nt, t.m2l_off.as<uint32_t>(),
-                       t.m2l_src.as<uint32_t>(), t.m2l_src_mask, t.nd_Z.as<double4>(), W,
+                       t.m2l_src.as<uint32_t>(), t.nd_Z.as<double4>(), W,
                        (int64_t)round_up(c_le(mom_p), 4), eps2, t.loc_pot.as<double>());
     TFMM_LAUNCHED();
 }

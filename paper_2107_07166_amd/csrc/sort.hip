@@ -58,16 +58,7 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 }
 
 // Lanes holding the same 8-bit digit (all 64 lanes must be active).
-__device__ __forceinline__ uint64_t digit_peers(uint32_t d) {
-    uint64_t peers = ~0ull;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = __ballot(bit);
-        peers &= bit ? m : ~m;
-    }
-    return peers;
-}
+__device__ __forceinline__ uint64_t digit_peers(uint32_t d) { return same_lanes<8>(true, d); }
 
 // Input sources.  load(i) gives entry i's key and value.
 template <typename K>
@@ -96,28 +87,6 @@ struct PairSrc {
             key = (uint32_t)q.x;
             val = q.y;
         }
-    }
-};
-
-// Keys alone.
-template <typename K>
-struct KeySrc {
-    const K* k;
-    __device__ __forceinline__ void load(int64_t i, K& key, int32_t& val) const {
-        key = k[i];
-        val = 0;
-    }
-};
-
-// Directed entries of node pairs packed into one word, (target << 16) |
-// source, for node ids below 2^16; no values.
-struct PairPack16Src {
-    const int2* p;
-    __device__ __forceinline__ void load(int64_t i, uint32_t& key, int32_t& val) const {
-        const int2 q = p[i >> 1];
-        const uint32_t x = (uint32_t)q.x, y = (uint32_t)q.y;
-        key = (i & 1) ? ((y << 16) | x) : ((x << 16) | y);
-        val = 0;
     }
 };
 
@@ -510,22 +479,13 @@ void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int
                 hipLaunchKernelGGL((radix_down_kernel<K, HV, Src>), dim3(nb), dim3(RB), 0, s, src, ko, vo, n, shift,
                                    (int64_t)nb, (const uint32_t*)cnt);
                 TFMM_LAUNCHED();
-            } else if constexpr (HV) {
+            } else {
                 const ArraySrc<K> prev{to_out ? kalt : kout, to_out ? valt : vout};
                 hipLaunchKernelGGL((radix_up_kernel<K, HV, false, ArraySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, n, shift,
                                    (int64_t)nb, cnt);
                 TFMM_LAUNCHED();
                 exclusive_scan_u32(cnt, cnt, nc, sscr, total, s);
                 hipLaunchKernelGGL((radix_down_kernel<K, HV, ArraySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, ko, vo, n,
-                                   shift, (int64_t)nb, (const uint32_t*)cnt);
-                TFMM_LAUNCHED();
-            } else {
-                const KeySrc<K> prev{to_out ? kalt : kout};
-                hipLaunchKernelGGL((radix_up_kernel<K, HV, false, KeySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, n, shift,
-                                   (int64_t)nb, cnt);
-                TFMM_LAUNCHED();
-                exclusive_scan_u32(cnt, cnt, nc, sscr, total, s);
-                hipLaunchKernelGGL((radix_down_kernel<K, HV, KeySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, ko, vo, n,
                                    shift, (int64_t)nb, (const uint32_t*)cnt);
                 TFMM_LAUNCHED();
             }
@@ -553,14 +513,10 @@ void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int
         if (ps == 0) {
             hipLaunchKernelGGL((radix_pass_kernel<K, HV, Src>), dim3(nb), dim3(RB), 0, s, src, ko, vo, n, shift,
                                db, st, sc.ticket, err);
-        } else if constexpr (HV) {
+        } else {
             // the previous pass wrote the other pair of arrays
             const ArraySrc<K> prev{to_out ? kalt : kout, to_out ? valt : vout};
             hipLaunchKernelGGL((radix_pass_kernel<K, HV, ArraySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, ko, vo, n,
-                               shift, db, st, sc.ticket + ps, err);
-        } else {
-            const KeySrc<K> prev{to_out ? kalt : kout};
-            hipLaunchKernelGGL((radix_pass_kernel<K, HV, KeySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, ko, vo, n,
                                shift, db, st, sc.ticket + ps, err);
         }
         TFMM_LAUNCHED();
@@ -629,14 +585,6 @@ void radix_sort_pairs(const int2* pairs, int64_t np, bool self_dummy, uint32_t s
     if (n <= 0) return;
     radix_sort_run<uint32_t, true>(PairSrc{pairs, self_key, self_dummy ? 1 : 0}, keys, vals, keys_alt, vals_alt, n,
                                    0, bits > 0 ? bits : 1, scratch, err, s);
-}
-
-void radix_sort_pairs_packed16(const int2* pairs, int64_t np, uint32_t* keys, uint32_t* keys_alt, int bits,
-                               void* scratch, uint32_t* err, hipStream_t s) {
-    const int64_t n = 2 * np;
-    if (n <= 0) return;
-    radix_sort_run<uint32_t, false>(PairPack16Src{pairs}, keys, nullptr, keys_alt, nullptr, n, 16,
-                                    bits > 0 ? std::min(bits, 16) : 1, scratch, err, s);
 }
 
 }  // namespace tfmm

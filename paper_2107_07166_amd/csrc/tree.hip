@@ -336,13 +336,7 @@ __global__ __launch_bounds__(ST) void small_sort_kernel(const double* __restrict
 #pragma unroll
         for (int r = 0; r < KPL; ++r) {
             const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
-            uint64_t peers = ~0ull;
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t m = __ballot(bit);
-                peers &= bit ? m : ~m;
-            }
+            const uint64_t peers = same_lanes<8>(true, d);
             const uint32_t below = (uint32_t)__popcll(peers & lt);
             const uint32_t first = wcnt[wv][d];
             rank[r] = first + below;

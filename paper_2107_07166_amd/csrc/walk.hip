@@ -1,4 +1,4 @@
-// Mutual dual-tree walk and per-target interaction lists.
+// Mutual dual-tree walk (the per-target interaction lists: lists.hip).
 //
 // The walk decides unordered node pairs level-synchronously from (root, root)
 // (one such pair per set of a forest; the children of a pair belong to its
@@ -230,7 +230,7 @@ constexpr int SQ = 1024;          // threads
 constexpr int kSeqMax = 2048;     // most entries of a pass run here
 constexpr int kSeqHead = 1024;    // the walk's first passes go on here up to this
 __global__ __launch_bounds__(SQ) void walk_seq_kernel(WalkNodes w, WalkOut o, WalkState* __restrict__ st, int slot,
-                                                      int init, int n_roots, uint32_t limit, double theta) {
+                                                      int init, int n_roots, uint32_t limit, double theta, Mailbox mb) {
     constexpr int NW = SQ / kWave;
     constexpr int EPW = kWave / kRun;  // entries per wavefront and step
     __shared__ int2 fr[2][kSeqMax];
@@ -313,6 +313,10 @@ __global__ __launch_bounds__(SQ) void walk_seq_kernel(WalkNodes w, WalkOut o, Wa
         __syncthreads();
     }
     if (tid == 0) st->slot[slot ^ 1] = s;
+    if (mb.box) {
+        __syncthreads();
+        mailbox_write(mb, st, (int)(sizeof(WalkState) / 4));
+    }
 }
 
 // Larger passes, two launches each.  The counting kernel decides every pair,
@@ -440,220 +444,24 @@ __global__ __launch_bounds__(TB) void walk_emit_kernel(WalkNodes w, WalkOut o, W
     }
 }
 
-// CSR offsets from targets sorted ascending (target = keys[i] >> shift):
-// off[t] = first entry with target >= t, for t = 0..nn.  Entry boundary i
-// (0..ne) writes off[t] for targets t in (target[i-1], target[i]], so each t
-// is written by exactly one boundary, which also copies off[nn] (the number
-// of entries below nn) to *below_nn if given.  Targets may equal nn (entries
-// sorted after every real one).  A thread takes four boundaries and reads
-// their keys with one 16-byte load.
-__global__ __launch_bounds__(TB) void csr_offsets_kernel(const uint32_t* __restrict__ keys, int64_t ne,
-                                                         int64_t nn, int shift, uint32_t* __restrict__ off,
-                                                         uint32_t* __restrict__ below_nn) {
-    const int64_t i0 = ((int64_t)blockIdx.x * TB + threadIdx.x) * 4;
-    if (i0 > ne) return;
-    int64_t kv[5];  // targets of entries i0 - 1 .. i0 + 3 (-1 before the first, nn after the last)
-    kv[0] = i0 == 0 ? -1 : (int64_t)(keys[i0 - 1] >> shift);
-    if (i0 + 4 <= ne) {
-        const uint4 q = *reinterpret_cast<const uint4*>(keys + i0);
-        kv[1] = q.x >> shift;
-        kv[2] = q.y >> shift;
-        kv[3] = q.z >> shift;
-        kv[4] = q.w >> shift;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) kv[j + 1] = i0 + j < ne ? (int64_t)(keys[i0 + j] >> shift) : nn;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int64_t i = i0 + j;
-        if (i > ne) break;
-        const int64_t lo = kv[j] + 1;
-        const int64_t hi = kv[j + 1] < nn ? kv[j + 1] : nn;
-        for (int64_t t = lo; t <= hi; ++t) off[t] = (uint32_t)i;
-        if (below_nn && lo <= nn && nn <= hi) *below_nn = (uint32_t)i;
-    }
-}
-
-__global__ __launch_bounds__(TB) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-// Directed near particle interactions: sum over directed leaf pairs of
-// n_t * n_s (self pairs n (n - 1)).
-__global__ __launch_bounds__(TB) void near_work_kernel(const uint32_t* __restrict__ tgt,
-                                                       const int32_t* __restrict__ src, int64_t ne,
-                                                       const int32_t* __restrict__ count,
-                                                       unsigned long long* __restrict__ out) {
-    __shared__ unsigned long long sh[TB];
-    unsigned long long s = 0;
-    for (int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x; i < ne; i += (int64_t)gridDim.x * TB) {
-        const int32_t a = (int32_t)tgt[i], b = src[i];
-        const unsigned long long na = (unsigned long long)count[a];
-        s += (a == b) ? na * (na - 1) : na * (unsigned long long)count[b];
-    }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = TB / 2; k > 0; k >>= 1) {
-        if (threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicAdd(out, sh[0]);
-}
-
-
-// ---- near-field work items -------------------------------------------------
-// A target leaf's near list is cut before entry q when the number of source
-// particles preceding q in that list crosses a multiple of kItemSources, so no
-// wavefront receives more than about kItemSources sources per target.  (The
-// prefix is taken modulo 2^32; only differences inside one list are used.)
-constexpr uint32_t kItemSources = 4096;
-
-// Items of a node's near list: entry q (list start q0) belongs to item
-// k = floor((P[q] - P[q0]) / kItemSources) of its leaf.  A source leaf holds
-// at most 4096 particles, so k grows by at most one per entry and a list
-// with last entry q1 - 1 has k_last + 1 items.  Only a leaf split into
-// several items needs partial-sum rows (one per item and target particle).
-__global__ __launch_bounds__(TB) void node_items_kernel(const uint32_t* __restrict__ off,
-                                                        const uint32_t* __restrict__ P, int64_t nn,
-                                                        const int32_t* __restrict__ count,
-                                                        uint32_t* __restrict__ nitems, uint32_t* __restrict__ prows) {
-    const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i >= nn) return;
-    const uint32_t q0 = off[i], q1 = off[i + 1];
-    const uint32_t n = (q1 > q0) ? (P[q1 - 1] - P[q0]) / kItemSources + 1u : 0u;
-    nitems[i] = n;
-    prows[i] = n > 1u ? n * (uint32_t)count[i] : 0u;
-}
-
-// One thread per item (grid-stride over the item count on the device): its
-// leaf is the last node whose first item is at or before it (nodes without
-// items share their first-item index with the next node); item k of a list
-// starts at its first entry q with P[q] - P[q0] >= k kItemSources (P grows
-// along a list, by at most kItemSources per entry, so every item has a first
-// entry), found by binary search, and ends where item k + 1 starts.
-__device__ __forceinline__ uint32_t item_start(const uint32_t* __restrict__ P, uint32_t q0, uint32_t q1,
-                                               uint32_t k) {
-    if (k == 0u) return q0;
-    const uint32_t p0 = P[q0], want = k * kItemSources;
-    uint32_t lo = q0 + 1u, hi = q1 - 1u;
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2u;
-        if (P[mid] - p0 >= want) hi = mid;
-        else lo = mid + 1u;
-    }
-    return lo;
-}
-
-__global__ __launch_bounds__(TB) void item_write_kernel(const uint32_t* __restrict__ P,
-                                                        const uint32_t* __restrict__ off, int64_t nn,
-                                                        const uint32_t* __restrict__ nitems,
-                                                        const uint32_t* __restrict__ item0,
-                                                        const uint32_t* __restrict__ n_items,
-                                                        const uint32_t* __restrict__ pbase,
-                                                        const int32_t* __restrict__ count,
-                                                        int32_t* __restrict__ it_leaf, uint32_t* __restrict__ it_q0,
-                                                        uint32_t* __restrict__ it_q1, uint32_t* __restrict__ it_pbase,
-                                                        int32_t* __restrict__ leaf_item0,
-                                                        int32_t* __restrict__ leaf_nitems,
-                                                        int32_t* __restrict__ multi_leaf,
-                                                        uint32_t* __restrict__ multi_count) {
-    const uint32_t total = *n_items;
-    for (uint32_t i = (uint32_t)(blockIdx.x * TB + threadIdx.x); i < total; i += gridDim.x * TB) {
-        int64_t lo = 0, hi = nn - 1;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) / 2;
-            if (item0[mid] <= i) lo = mid;
-            else hi = mid - 1;
-        }
-        const int64_t L = lo;
-        const uint32_t n = nitems[L], k = i - item0[L];
-        const uint32_t q0 = off[L], q1 = off[L + 1];
-        it_leaf[i] = (int32_t)L;
-        it_q0[i] = item_start(P, q0, q1, k);
-        it_q1[i] = k + 1u < n ? item_start(P, q0, q1, k + 1u) : q1;
-        it_pbase[i] = n > 1u ? pbase[L] + k * (uint32_t)count[L] : 0u;
-        if (k == 0u) {
-            leaf_item0[L] = (int32_t)item0[L];
-            leaf_nitems[L] = (int32_t)n;
-            if (n > 1u) multi_leaf[atomicAdd(multi_count, 1u)] = (int32_t)L;
-        }
-    }
-}
-
-unsigned grid(int64_t n) { return (unsigned)cdiv(n > 0 ? n : 1, TB); }
-
-int bits_for(int64_t n) {
-    int b = 1;
-    while (((int64_t)1 << b) < n) ++b;
-    return b;
-}
-
-// Stable sort by target of the directed entries of np node pairs (read
-// straight from the pair array), then CSR offsets from the sorted targets.
-// With self_dummy, the second entry of a self pair gets key nn and sorts
-// last, so the first off[nn] entries are the real ones; off[nn] is also
-// written to *real_out if given.  The sources of every target stay in the
-// walk's emission order.
-void build_csr_pairs(Tree& t, const DevBuf& pairs, int64_t np, bool self_dummy, DevBuf& tgtbuf, DevBuf& srcbuf,
-                     DevBuf& off, DevBuf& srcout, DevBuf& scr, DevBuf& scr2, uint32_t* real_out, hipStream_t s) {
-    Ctx* ctx = t.ctx;
-    const int64_t nn = t.n_nodes;
-    const int64_t ne = 2 * np;
-    const int64_t room = std::max<int64_t>(ne, 1);
-    tgtbuf.ensure(ctx, (size_t)room * 4);
-    srcbuf.ensure(ctx, (size_t)room * 4);
-    scr2.ensure(ctx, (size_t)room * 8 + 256);
-    uint32_t* kalt = scr2.as<uint32_t>();
-    int32_t* valt = reinterpret_cast<int32_t*>(kalt + room);
-    const int bits = bits_for(self_dummy ? nn + 1 : nn);
-    scr.ensure(ctx, sort_scratch_bytes(ne, bits) + 1024);
-    radix_sort_pairs(pairs.as<int2>(), np, self_dummy, (uint32_t)nn, tgtbuf.as<uint32_t>(), srcbuf.as<int32_t>(),
-                     kalt, valt, bits, scr.p, ctx->dev_err, s);
-    off.ensure(ctx, (size_t)(nn + 1) * 4);
-    hipLaunchKernelGGL(csr_offsets_kernel, dim3(grid(cdiv(ne + 1, 4))), dim3(TB), 0, s,
-                       (const uint32_t*)tgtbuf.as<uint32_t>(), ne, nn, 0, off.as<uint32_t>(), real_out);
-    TFMM_LAUNCHED();
-    std::swap(srcbuf.p, srcout.p);
-    std::swap(srcbuf.cap, srcout.cap);
-    std::swap(srcbuf.ctx, srcout.ctx);
-}
-
-// The far lists with node ids below 2^16: entries packed as (target << 16) |
-// source and sorted as single words (half the bytes of separate arrays); the
-// sorted words become the source list, read through the mask 0xffff.
-void build_far_csr_packed(Tree& t, int64_t np, hipStream_t s) {
-    Ctx* ctx = t.ctx;
-    const int64_t nn = t.n_nodes;
-    const int64_t ne = 2 * np;
-    const int64_t room = std::max<int64_t>(ne, 1);
-    t.w_tg.ensure(ctx, (size_t)room * 4);
-    t.scratch2.ensure(ctx, (size_t)room * 4 + 256);
-    const int bits = bits_for(nn);
-    t.scratch.ensure(ctx, sort_scratch_bytes(ne, bits) + 1024);
-    radix_sort_pairs_packed16(t.m2l_pairs.as<int2>(), np, t.w_tg.as<uint32_t>(), t.scratch2.as<uint32_t>(), bits,
-                              t.scratch.p, ctx->dev_err, s);
-    t.m2l_off.ensure(ctx, (size_t)(nn + 1) * 4);
-    hipLaunchKernelGGL(csr_offsets_kernel, dim3(grid(cdiv(ne + 1, 4))), dim3(TB), 0, s,
-                       (const uint32_t*)t.w_tg.as<uint32_t>(), ne, nn, 16, t.m2l_off.as<uint32_t>(), nullptr);
-    TFMM_LAUNCHED();
-    std::swap(t.w_tg.p, t.m2l_src.p);
-    std::swap(t.w_tg.cap, t.m2l_src.cap);
-    std::swap(t.w_tg.ctx, t.m2l_src.ctx);
-    t.m2l_src_mask = 0xffffu;
-}
-
 WalkOut walk_out(Tree& t) {
     const unsigned long long cap = std::min({t.w_fr.cap / 8, t.w_fr2.cap / 8, t.w_dec.cap / kRun, (size_t)UINT32_MAX});
     return WalkOut{{t.w_fr.as<int2>(), t.w_fr2.as<int2>()}, t.m2l_pairs.as<int2>(), t.p2p_pairs.as<int2>(), cap,
                    (unsigned long long)(t.m2l_pairs.cap / 8), (unsigned long long)(t.p2p_pairs.cap / 8)};
 }
 
-void launch_seq(Tree& t, const WalkNodes& w, int slot, bool init, int limit, double theta, hipStream_t s) {
+// mb: the read-back of the state, if this launch is the last before it.
+void launch_seq(Tree& t, const WalkNodes& w, int slot, bool init, int limit, double theta, const Mailbox& mb,
+                hipStream_t s) {
     hipLaunchKernelGGL(walk_seq_kernel, dim3(1), dim3(SQ), 0, s, w, walk_out(t), t.w_state.as<WalkState>(), slot,
-                       init ? 1 : 0, t.n_sets, (uint32_t)limit, theta);
+                       init ? 1 : 0, t.n_sets, (uint32_t)limit, theta, mb);
     TFMM_LAUNCHED();
+}
+
+WalkState wait_state(Tree& t, const Mailbox& mb, hipStream_t s) {
+    WalkState h;
+    mailbox_wait(t.ctx, mb.seq, sizeof(h), &h, false, s);
+    return h;
 }
 
 // One pass in two launches, for a frontier of about expect entries (any grid
@@ -692,7 +500,7 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
     t.scratch2.ensure(ctx, 256);
     WalkState* st = t.w_state.as<WalkState>();
     U3L* tot = t.scratch2.as<U3L>();
-    launch_seq(t, w, 1, true, 0, theta, s);  // the roots, into slot 0 and buffer 0
+    launch_seq(t, w, 1, true, 0, theta, Mailbox{}, s);  // the roots, into slot 0 and buffer 0
     int64_t nf = t.n_sets, max_nf = t.n_sets, n_far = 0, n_near = 0;
     int slot = 0;
     t.walk_hint_nf.clear();
@@ -783,27 +591,28 @@ bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thet
     t.p2p_pairs.ensure(ctx, (size_t)want_near * 8);
     t.w_state.ensure(ctx, sizeof(WalkState));
     int slot = 0;
-    launch_seq(t, w, slot ^ 1, true, kSeqHead, theta, s);
-    if (known) {
-        // larger passes of the previous walk: from the first above kSeqHead to the last
-        int a = 0, b = (int)t.walk_hint_nf.size();
-        while (a < b && t.walk_hint_nf[a] <= kSeqHead) ++a;
-        while (b > a && t.walk_hint_nf[b - 1] <= kSeqHead) --b;
+    // larger passes of the previous walk: from the first above kSeqHead to the last
+    int a = 0, b = (int)t.walk_hint_nf.size();
+    if (!known) b = 0;
+    while (a < b && t.walk_hint_nf[a] <= kSeqHead) ++a;
+    while (b > a && t.walk_hint_nf[b - 1] <= kSeqHead) --b;
+    const Mailbox mb = mailbox_next(ctx);
+    launch_seq(t, w, slot ^ 1, true, kSeqHead, theta, b > a ? Mailbox{} : mb, s);
+    if (b > a) {
         for (int k = a; k < b; ++k, slot ^= 1)
             launch_pass(t, w, slot, t.walk_hint_nf[k] + t.walk_hint_nf[k] / 4 + 64, theta, s);
-        if (b > a) {
-            launch_seq(t, w, slot, false, kSeqMax, theta, s);
-            slot ^= 1;
-        }
+        launch_seq(t, w, slot, false, kSeqMax, theta, mb, s);
+        slot ^= 1;
     }
-    WalkState h = read_back(ctx, (const WalkState*)t.w_state.as<WalkState>(), s);
+    WalkState h = wait_state(t, mb, s);
     while (!h.overflow && h.slot[slot].nf != 0u) {
         if (h.passes > (uint32_t)kMaxPasses) return false;
         const int64_t nf = h.slot[slot].nf;
         for (int k = 0; k < 4; ++k, slot ^= 1) launch_pass(t, w, slot, nf << k, theta, s);
-        launch_seq(t, w, slot, false, kSeqMax, theta, s);
+        const Mailbox more = mailbox_next(ctx);
+        launch_seq(t, w, slot, false, kSeqMax, theta, more, s);
         slot ^= 1;
-        h = read_back(ctx, (const WalkState*)t.w_state.as<WalkState>(), s);
+        h = wait_state(t, more, s);
     }
     if (h.overflow) return false;
     t.n_m2l = (int64_t)h.slot[slot].n_far;
@@ -812,16 +621,6 @@ bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thet
     t.walk_hint_nf.assign(h.nf_pass, h.nf_pass + std::min<uint32_t>(h.passes, (uint32_t)kMaxPasses));
     return true;
 }
-
-// Device slots of the list-building totals, read back together at the end.
-struct WalkTotals {
-    uint32_t multi;        // leaves split into several near-field items
-    uint32_t near_entries; // directed near entries (check of 2 n_near - n_leaves)
-    uint32_t items;        // near-field work items
-    uint32_t partial;      // partial-sum rows of multi-item leaves
-    uint32_t scratch[12];  // totals nobody reads
-    unsigned long long near_int;
-};
 
 }  // namespace
 
@@ -845,7 +644,6 @@ void aux_join(Tree& t, hipStream_t s) {
 // stream (after the passes) and the near-list chain on s.  walk_lists_end
 // reads the totals back once the near chain is done.
 void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t s, hipEvent_t passes_done) {
-    Ctx* ctx = t.ctx;
     const int64_t nn = t.n_nodes;
     if (theta_in.size() != 1 && theta_in.size() != (size_t)t.n_sets) fail(TFMM_EINVAL, "theta: one value or one per set");
     const std::vector<double> theta_keep = theta_in;  // the caller's vector may be the tree's own
@@ -860,112 +658,26 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t 
     if (!walk_bfs_async(t, w, theta_keep, s)) walk_bfs_sized(t, w, theta, s);
     t.walk_hint_far = t.n_m2l;
     t.walk_hint_near = t.n_p2p;
-    const int64_t n_far = t.n_m2l, n_near = t.n_p2p;
     if (passes_done) TFMM_HIP(hipEventRecord(passes_done, s));
-
-    t.w_res.ensure(ctx, sizeof(WalkTotals));
-    WalkTotals* res = t.w_res.as<WalkTotals>();
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(TB), 0, s, reinterpret_cast<int32_t*>(res),
-                       (int64_t)(sizeof(WalkTotals) / 4), 0);
-    TFMM_LAUNCHED();
-    uint32_t* junk = res->scratch;
 
     // The far-list chain runs on the tree's second stream, the near-list chain
     // on s; they share no buffer.
     aux_fork(t, s);
-    // far lists: directed, by target
-    if (nn <= 65536) {
-        build_far_csr_packed(t, n_far, t.aux);
-    } else {
-        build_csr_pairs(t, t.m2l_pairs, n_far, false, t.w_tg, t.w_sr, t.m2l_off, t.m2l_src, t.scratch, t.scratch2,
-                        nullptr, t.aux);
-        t.m2l_src_mask = 0xffffffffu;
-    }
-    DevBuf& tg = t.w_tg_b;
-    DevBuf& sr = t.w_sr_b;
-    // near lists: directed (self pairs once), by target.  Every leaf has
-    // exactly one self pair, so the entry count is 2 n_near - n_leaves (the
-    // count the sort leaves below its dummies is checked at the end).
-    const int64_t ne = 2 * n_near - t.n_leaves;
-    {
-        build_csr_pairs(t, t.p2p_pairs, n_near, true, tg, sr, t.p2p_off, t.p2p_src, t.scratch_b, t.scratch2_b,
-                        &res->near_entries, s);
-        // work items over the sorted near entries (tg holds the sorted targets)
-        t.w_c.ensure(ctx, (size_t)std::max<int64_t>(ne, 1) * 4);
-        uint32_t* P = t.w_c.as<uint32_t>();
-        // the same scratch serves the scan over the entries and the two over the nodes
-        t.scratch_b.ensure(ctx, scan_scratch_bytes(std::max<int64_t>(ne, nn)) + 256);
-        // P[q] = source particles before entry q (gathered from the source leaf counts)
-        exclusive_scan_gather_u32(t.p2p_src.as<int32_t>(), t.nd_count.as<int32_t>(), P, ne, t.scratch_b.p, junk, s);
-        // per node: items and partial rows, then their offsets
-        t.w_fl.ensure(ctx, (size_t)(nn + 1) * 16);
-        uint32_t* nit = t.w_fl.as<uint32_t>();
-        uint32_t* it0 = nit + (nn + 1);
-        uint32_t* prw = it0 + (nn + 1);
-        uint32_t* pbs = prw + (nn + 1);
-        hipLaunchKernelGGL(node_items_kernel, dim3(grid(nn)), dim3(TB), 0, s, (const uint32_t*)t.p2p_off.as<uint32_t>(),
-                           (const uint32_t*)P, nn, t.nd_count.as<int32_t>(), nit, prw);
-        TFMM_LAUNCHED();
-        exclusive_scan2_u32(nit, it0, &res->items, prw, pbs, &res->partial, nn, t.scratch_b.p, s);
-        // there are at most ne items, so every item array is sized by ne
-        const size_t ni = (size_t)std::max<int64_t>(ne, 1);
-        t.it_leaf.ensure(ctx, ni * 4);
-        t.it_q0.ensure(ctx, ni * 4);
-        t.it_q1.ensure(ctx, ni * 4);
-        t.it_pbase.ensure(ctx, ni * 4);
-        t.leaf_item0.ensure(ctx, (size_t)(nn + 1) * 4);
-        t.leaf_nitems.ensure(ctx, (size_t)(nn + 1) * 4);
-        t.multi_leaf.ensure(ctx, (size_t)(nn + 1) * 4);
-        t.multi_count = &res->multi;
-        hipLaunchKernelGGL(item_write_kernel, dim3((unsigned)std::min<int64_t>(2048, grid(ne))), dim3(TB), 0, s,
-                           (const uint32_t*)P, (const uint32_t*)t.p2p_off.as<uint32_t>(), nn, (const uint32_t*)nit,
-                           (const uint32_t*)it0, (const uint32_t*)&res->items, (const uint32_t*)pbs,
-                           t.nd_count.as<int32_t>(),
-                           t.it_leaf.as<int32_t>(), t.it_q0.as<uint32_t>(), t.it_q1.as<uint32_t>(),
-                           t.it_pbase.as<uint32_t>(), t.leaf_item0.as<int32_t>(), t.leaf_nitems.as<int32_t>(),
-                           t.multi_leaf.as<int32_t>(), &res->multi);
-        TFMM_LAUNCHED();
-    }
+    build_far_lists(t, t.aux);
+    build_near_lists(t, s);
     t.walk_theta = theta_keep;
 }
 
 void walk_lists_end(Tree& t, hipStream_t s) {
-    Ctx* ctx = t.ctx;
-    const int64_t ne = 2 * t.n_p2p - t.n_leaves;
-    const WalkTotals h = read_back_checked(ctx, t.w_res.as<WalkTotals>(), s);
-    if ((int64_t)h.near_entries != ne)
-        fail(TFMM_EDEVICE, "walk: near entry count " + std::to_string(h.near_entries) + " differs from " +
-                               std::to_string(ne));
-    t.n_near_int = -1;  // counted on request (near_interactions)
-    t.n_items = h.items;
-    t.n_partial = h.partial;
+    near_lists_end(t, s);
     t.walk_valid = true;
 }
 
 void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s) {
+    PendingLists pending(t, s);
     walk_lists_begin(t, theta, s);
     aux_join(t, s);
     walk_lists_end(t, s);
-}
-
-// Directed near particle interactions of the last walk (throughput
-// accounting): one pass over the sorted near entries, on the null stream
-// after the device is idle, counted once per walk.
-int64_t near_interactions(Tree& t) {
-    if (!t.walk_valid) return -1;
-    if (t.n_near_int >= 0) return t.n_near_int;
-    Ctx* ctx = t.ctx;
-    TFMM_HIP(hipDeviceSynchronize());
-    const int64_t ne = 2 * t.n_p2p - t.n_leaves;
-    unsigned long long* acc = &t.w_res.as<WalkTotals>()->near_int;
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(TB), 0, nullptr, reinterpret_cast<int32_t*>(acc), 2, 0);
-    TFMM_LAUNCHED();
-    const unsigned nb = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(1, cdiv(ne, TB)));
-    hipLaunchKernelGGL(near_work_kernel, dim3(nb), dim3(TB), 0, nullptr, (const uint32_t*)t.w_tg_b.as<uint32_t>(),
-                       (const int32_t*)t.p2p_src.as<int32_t>(), ne, t.nd_count.as<int32_t>(), acc);
-    TFMM_LAUNCHED();
-    t.n_near_int = (int64_t)read_back(ctx, (const unsigned long long*)acc, nullptr);
-    return t.n_near_int;
 }
 
 }  // namespace tfmm
