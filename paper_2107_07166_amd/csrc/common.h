@@ -263,7 +263,7 @@ struct Tree {
     DevBuf near3;                 // FP64 near-field acceleration (3 per sorted particle)
     DevBuf far3;                  // FP64 far-field acceleration (3 per sorted particle)
     DevBuf near_pot, partial_pot; // FP64 near-field potential (per sorted particle / per partial row)
-    DevBuf loc_pot, loc_pot_leaf; // FP64 standard locals with L_0 (potential output only)
+    DevBuf loc_pot, loc_pot_leaf; // FP64 standard locals with L_0 (potential beside conserving forces)
 
     // scratch
     DevBuf scratch;               // scans and sorts
@@ -406,13 +406,16 @@ int64_t near_interactions(Tree& t);
 void compute_moments(Tree& t, int p, hipStream_t s);
 void prepare_sources(Tree& t, int precision, hipStream_t s);
 // kdeg: degree of the conserving projection scalar (p - 1 by default; above
-// it the locals are of order kdeg + 1)
-void run_m2l(Tree& t, int p, int variant, int precision, double eps2, hipStream_t s, int kdeg);
+// it the locals are of order kdeg + 1); pot: with the standard variant, the
+// locals with the potential's constant term
+void run_m2l(Tree& t, int p, int variant, int precision, double eps2, hipStream_t s, int kdeg, bool pot);
 constexpr int kKnobMaxK = 6;  // largest scalar degree built for the GPU
 void run_p2p(Tree& t, int precision, double eps2, bool with_pot, hipStream_t s);
 void run_p2p_reduce(Tree& t, bool with_pot, hipStream_t s);
 void run_m2l_pot(Tree& t, int p, int mom_p, int precision, double eps2, hipStream_t s);
-void run_potential_down(Tree& t, int p, int precision, double eps2, double G, double* pot, hipStream_t s);
+void run_l2l_pot(Tree& t, int p, hipStream_t s);
+void run_l2p_pot(Tree& t, int p, int precision, double eps2, double G, const double* loc_leaf, double* pot,
+                 hipStream_t s);
 void run_l2l(Tree& t, int p, int variant, hipStream_t s);
 // Far-field acceleration of every particle into t.far3 (after L2L, on the
 // stream L2L ran on), then the forces G m (near + far) in caller order.

@@ -465,21 +465,21 @@ __global__ __launch_bounds__(LB) void l2p_pot_kernel(int64_t n, const double4* _
 }
 
 template <int P>
-void potential_down(Tree& t, int precision, double eps2, double G, double* pot, hipStream_t s) {
-    const int64_t nl = t.n_leaves, n = t.n;
+void l2l_pot(Tree& t, hipStream_t s) {
+    const int64_t nl = t.n_leaves;
     t.loc_pot_leaf.ensure(t.ctx, (size_t)t.n_nodes * Expansion<P>::NC * 8);
     hipLaunchKernelGGL(l2l_std_kernel<P>, dim3((unsigned)cdiv(nl, LB)), dim3(LB), 0, s, nl, t.leaves.as<int32_t>(),
                        t.nd_parent.as<int32_t>(), t.nd_Z.as<double4>(), t.m2l_off.as<uint32_t>(),
                        t.loc_pot.as<double>(), t.loc_pot_leaf.as<double>());
     TFMM_LAUNCHED();
-    if (precision == TFMM_MIXED32)
-        hipLaunchKernelGGL((l2p_pot_kernel<P, float>), dim3((unsigned)cdiv(n, LB)), dim3(LB), 0, s, n,
-                           t.Xm.as<double4>(), t.leaf_of.as<int32_t>(), t.perm.as<int32_t>(), t.nd_Z.as<double4>(),
-                           t.loc_pot_leaf.as<double>(), t.near_pot.as<double>(), eps2, G, pot);
-    else
-        hipLaunchKernelGGL((l2p_pot_kernel<P, double>), dim3((unsigned)cdiv(n, LB)), dim3(LB), 0, s, n,
-                           t.Xm.as<double4>(), t.leaf_of.as<int32_t>(), t.perm.as<int32_t>(), t.nd_Z.as<double4>(),
-                           t.loc_pot_leaf.as<double>(), t.near_pot.as<double>(), eps2, G, pot);
+}
+
+template <int P>
+void l2p_pot(Tree& t, int precision, double eps2, double G, const double* loc_leaf, double* pot, hipStream_t s) {
+    const int64_t n = t.n;
+    hipLaunchKernelGGL((precision == TFMM_MIXED32 ? l2p_pot_kernel<P, float> : l2p_pot_kernel<P, double>),
+                       dim3((unsigned)cdiv(n, LB)), dim3(LB), 0, s, n, t.Xm.as<double4>(), t.leaf_of.as<int32_t>(),
+                       t.perm.as<int32_t>(), t.nd_Z.as<double4>(), loc_leaf, t.near_pot.as<double>(), eps2, G, pot);
     TFMM_LAUNCHED();
 }
 
@@ -543,17 +543,33 @@ void run_l2l(Tree& t, int p, int variant, hipStream_t s) {
     }
 }
 
-// L2L of the potential locals (t.loc_pot) and the potential at every particle.
-void run_potential_down(Tree& t, int p, int precision, double eps2, double G, double* pot, hipStream_t s) {
+// L2L of the potential locals (t.loc_pot) into t.loc_pot_leaf.
+void run_l2l_pot(Tree& t, int p, hipStream_t s) {
     switch (p) {
-        case 1: potential_down<1>(t, precision, eps2, G, pot, s); break;
-        case 2: potential_down<2>(t, precision, eps2, G, pot, s); break;
-        case 3: potential_down<3>(t, precision, eps2, G, pot, s); break;
-        case 4: potential_down<4>(t, precision, eps2, G, pot, s); break;
-        case 5: potential_down<5>(t, precision, eps2, G, pot, s); break;
-        case 6: potential_down<6>(t, precision, eps2, G, pot, s); break;
-        case 7: potential_down<7>(t, precision, eps2, G, pot, s); break;
-        case 8: potential_down<8>(t, precision, eps2, G, pot, s); break;
+        case 1: l2l_pot<1>(t, s); break;
+        case 2: l2l_pot<2>(t, s); break;
+        case 3: l2l_pot<3>(t, s); break;
+        case 4: l2l_pot<4>(t, s); break;
+        case 5: l2l_pot<5>(t, s); break;
+        case 6: l2l_pot<6>(t, s); break;
+        case 7: l2l_pot<7>(t, s); break;
+        case 8: l2l_pot<8>(t, s); break;
+        default: fail(TFMM_EINVAL, "p must be in 1..8");
+    }
+}
+
+// The potential at every particle from the leaves' standard locals and the near sums.
+void run_l2p_pot(Tree& t, int p, int precision, double eps2, double G, const double* loc_leaf, double* pot,
+                 hipStream_t s) {
+    switch (p) {
+        case 1: l2p_pot<1>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 2: l2p_pot<2>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 3: l2p_pot<3>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 4: l2p_pot<4>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 5: l2p_pot<5>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 6: l2p_pot<6>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 7: l2p_pot<7>(t, precision, eps2, G, loc_leaf, pot, s); break;
+        case 8: l2p_pot<8>(t, precision, eps2, G, loc_leaf, pot, s); break;
         default: fail(TFMM_EINVAL, "p must be in 1..8");
     }
 }

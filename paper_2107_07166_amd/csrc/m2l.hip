@@ -244,8 +244,9 @@ void m2l_cons_pass_kernel(int64_t n_targets, const uint32_t* __restrict__ off,
 // are two launches of two polynomials (3.84-3.90 against 3.70-3.75 ms).
 constexpr int kConsSplitP = 6;
 
+// pot (standard only): the locals carry the potential's constant term as well.
 template <int P, int VAR, typename T>
-void launch(Tree& t, double eps2, hipStream_t s) {
+void launch(Tree& t, double eps2, bool pot, hipStream_t s) {
     const int64_t nt = t.n_nodes;  // every node; nodes with an empty far list write nothing
     if (nt <= 0) return;
     const T* W = (sizeof(T) == 4) ? reinterpret_cast<const T*>(t.W32.p) : reinterpret_cast<const T*>(t.W64.p);
@@ -263,7 +264,8 @@ void launch(Tree& t, double eps2, hipStream_t s) {
         pass(m2l_cons_pass_kernel<P, P, 0x4, T>);
         pass(m2l_cons_pass_kernel<P, P, 0x8, T>);
     } else {
-        hipLaunchKernelGGL((m2l_kernel<P, VAR, T>), grid, dim3(mb), 0, s, nt,
+        constexpr bool STD = VAR == TFMM_STANDARD;
+        hipLaunchKernelGGL((STD && pot ? m2l_kernel<P, VAR, T, STD> : m2l_kernel<P, VAR, T>), grid, dim3(mb), 0, s, nt,
                            t.m2l_off.as<uint32_t>(), t.m2l_src.as<uint32_t>(), t.nd_Z.as<double4>(), W,
                            (int64_t)round_up(c_le(P), 4), eps2, t.loc.as<double>());
         TFMM_LAUNCHED();
@@ -304,20 +306,20 @@ void dispatch_knob(Tree& t, int precision, double eps2, hipStream_t s) {
 }
 
 template <int P>
-void dispatch_var(Tree& t, int variant, int precision, double eps2, hipStream_t s) {
+void dispatch_var(Tree& t, int variant, int precision, double eps2, bool pot, hipStream_t s) {
     if (variant == TFMM_CONSERVING_R2) {
         if constexpr (P == 2) {
-            if (precision == TFMM_MIXED32) launch<P, TFMM_CONSERVING_R2, float>(t, eps2, s);
-            else launch<P, TFMM_CONSERVING_R2, double>(t, eps2, s);
+            if (precision == TFMM_MIXED32) launch<P, TFMM_CONSERVING_R2, float>(t, eps2, pot, s);
+            else launch<P, TFMM_CONSERVING_R2, double>(t, eps2, pot, s);
         } else {
             fail(TFMM_EINVAL, "conserving_r2 locals are of order 2");
         }
     } else if (variant == TFMM_CONSERVING) {
-        if (precision == TFMM_MIXED32) launch<P, TFMM_CONSERVING, float>(t, eps2, s);
-        else launch<P, TFMM_CONSERVING, double>(t, eps2, s);
+        if (precision == TFMM_MIXED32) launch<P, TFMM_CONSERVING, float>(t, eps2, pot, s);
+        else launch<P, TFMM_CONSERVING, double>(t, eps2, pot, s);
     } else {
-        if (precision == TFMM_MIXED32) launch<P, TFMM_STANDARD, float>(t, eps2, s);
-        else launch<P, TFMM_STANDARD, double>(t, eps2, s);
+        if (precision == TFMM_MIXED32) launch<P, TFMM_STANDARD, float>(t, eps2, pot, s);
+        else launch<P, TFMM_STANDARD, double>(t, eps2, pot, s);
     }
 }
 
@@ -326,8 +328,8 @@ void launch_pot(Tree& t, int mom_p, double eps2, hipStream_t s) {
     const int64_t nt = t.n_nodes;
     if (nt <= 0) return;
     const T* W = (sizeof(T) == 4) ? reinterpret_cast<const T*>(t.W32.p) : reinterpret_cast<const T*>(t.W64.p);
-    const dim3 grid((unsigned)cdiv(cdiv(nt, TPW) * kWave, MB));
-    hipLaunchKernelGGL((m2l_kernel<P, TFMM_STANDARD, T, true>), grid, dim3(MB), 0, s, nt, t.m2l_off.as<uint32_t>(),
+    const dim3 grid((unsigned)cdiv(cdiv(nt, TPW) * kWave, kForceBlock));
+    hipLaunchKernelGGL((m2l_kernel<P, TFMM_STANDARD, T, true>), grid, dim3(kForceBlock), 0, s, nt, t.m2l_off.as<uint32_t>(),
                        t.m2l_src.as<uint32_t>(), t.nd_Z.as<double4>(), W,
                        (int64_t)round_up(c_le(mom_p), 4), eps2, t.loc_pot.as<double>());
     TFMM_LAUNCHED();
@@ -342,8 +344,8 @@ void dispatch_pot(Tree& t, int mom_p, int precision, double eps2, hipStream_t s)
 }  // namespace
 
 // Standard locals with their constant term (the far-field potential of
-// Eq. taylor truncated at degree p) into t.loc_pot, for every variant; the
-// moments on the device are of order mom_p >= p.
+// Eq. taylor truncated at degree p) into t.loc_pot, beside the conserving
+// variants' own locals; the moments on the device are of order mom_p >= p.
 void run_m2l_pot(Tree& t, int p, int mom_p, int precision, double eps2, hipStream_t s) {
     const int64_t tot = t.n_nodes * (int64_t)c_le(p);
     // no clearing: a node's locals are written whole when its far list is not
@@ -362,7 +364,7 @@ void run_m2l_pot(Tree& t, int p, int mom_p, int precision, double eps2, hipStrea
     }
 }
 
-void run_m2l(Tree& t, int p, int variant, int precision, double eps2, hipStream_t s, int kdeg) {
+void run_m2l(Tree& t, int p, int variant, int precision, double eps2, hipStream_t s, int kdeg, bool pot) {
     const bool knob = variant == TFMM_CONSERVING && kdeg > p - 1;
     const int nloc = knob ? n_local(kdeg + 1, variant) : n_local(p, variant);
     const int64_t tot = t.n_nodes * (int64_t)nloc;
@@ -387,14 +389,14 @@ void run_m2l(Tree& t, int p, int variant, int precision, double eps2, hipStream_
         return;
     }
     switch (p) {
-        case 1: dispatch_var<1>(t, variant, precision, eps2, s); break;
-        case 2: dispatch_var<2>(t, variant, precision, eps2, s); break;
-        case 3: dispatch_var<3>(t, variant, precision, eps2, s); break;
-        case 4: dispatch_var<4>(t, variant, precision, eps2, s); break;
-        case 5: dispatch_var<5>(t, variant, precision, eps2, s); break;
-        case 6: dispatch_var<6>(t, variant, precision, eps2, s); break;
-        case 7: dispatch_var<7>(t, variant, precision, eps2, s); break;
-        case 8: dispatch_var<8>(t, variant, precision, eps2, s); break;
+        case 1: dispatch_var<1>(t, variant, precision, eps2, pot, s); break;
+        case 2: dispatch_var<2>(t, variant, precision, eps2, pot, s); break;
+        case 3: dispatch_var<3>(t, variant, precision, eps2, pot, s); break;
+        case 4: dispatch_var<4>(t, variant, precision, eps2, pot, s); break;
+        case 5: dispatch_var<5>(t, variant, precision, eps2, pot, s); break;
+        case 6: dispatch_var<6>(t, variant, precision, eps2, pot, s); break;
+        case 7: dispatch_var<7>(t, variant, precision, eps2, pot, s); break;
+        case 8: dispatch_var<8>(t, variant, precision, eps2, pot, s); break;
         default: fail(TFMM_EINVAL, "p must be in 1..8");
     }
 }
