@@ -312,11 +312,9 @@ void radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* 
                     int64_t n, int bits, void* scratch, uint32_t* err, hipStream_t s);
 void radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
                     int64_t n, int bits, void* scratch, uint32_t* err, hipStream_t s);
-// The single-kernel-per-pass route of radix_sort_u64 with the digit totals
-// counted by the caller: sort_counts gives their place in the scratch (8
-// passes of 256 words, then the words the passes need cleared up to
-// *clear_words from the start), or nullptr when n takes the other route, which
-// counts by itself.
+// radix_sort_u64 with the digit totals counted by the caller: sort_counts gives
+// their place in the scratch (8 passes of 256 words, then the words the passes
+// need cleared up to *clear_words from the start).
 uint32_t* sort_counts(void* scratch, int64_t n, int bits, int64_t* clear_words);
 void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
                             int bits, void* scratch, uint32_t* err, hipStream_t s);

@@ -30,27 +30,36 @@
 namespace tfmm {
 namespace {
 
-constexpr int kLookBack = 8;      // earlier tiles read per look-back step
-constexpr int RB = 256;           // threads per block (one digit per thread)
-constexpr int RW = RB / kWave;    // waves per block
-// keys per lane (16 for every key type: measured against 8 and 32)
-template <typename K, bool HV> constexpr int keys_per_lane() { return 16; }
-template <typename K, bool HV> constexpr int tile_keys() { return RB * keys_per_lane<K, HV>(); }
 constexpr int RADIX = 256;
+constexpr int kLookBack = 4;      // earlier tiles read per look-back step
+constexpr int RB = 256;           // threads per block of the histogram (one digit per thread)
 constexpr int MAXP = 8;          // passes of a 64-bit key
 constexpr int kHistBlocks = 1024;
-// Sorts of at least this many tiles run reduce-then-scan passes (count, scan,
-// scatter), so that no tile waits on another (decoupled look-back over
-// thousands of tiles costs more than the extra launches).
-constexpr int kRtsMinTiles = 1024;
 constexpr int kHistKeysPerThread = 16;  // fewer blocks, fewer global atomics
 constexpr uint32_t kSpinLimit = 1u << 20;
-
-// Tile status word: bits 62..63 flag (0 none, 1 own count, 2 running total
-// including this tile), low 62 bits the value.
-constexpr unsigned long long kFlagOwn = 1ull << 62;
-constexpr unsigned long long kFlagTotal = 2ull << 62;
-constexpr unsigned long long kValMask = (1ull << 62) - 1;
+// A pass: a tile's 4096 keys are ranked by 16 wavefronts, four keys per lane.
+// Up to 2^20 keys a tile runs alone on its compute unit and its serial parts set
+// the pace: the ranking rounds (with four wavefronts, 16 keys per lane, eight
+// passes over 100000 keys took 94 us, over 2^18 111, over 2^20 177; now 76, 90,
+// 153) and the look-back, where reading fewer and smaller words counts more
+// than taking fewer steps (four words a step 153 us on 2^20 keys, eight 154, 16
+// 164, 32 178).  Tiles of 2048 keys halve the ranking but double the look-back:
+// 71 us on 100000 keys, 94 on 2^18, 196 on 2^20; of 8192 keys 97, 109 and 157.
+// Splitting a pass into count, scan and scatter launches, without waits, is
+// slower at every size: 234 against 153 us on 2^20 keys, 418 against 364 on
+// 2^22 and 708 against 663 on 9e6 keys.
+constexpr int kPassThreads = 1024;
+constexpr int kPassKeys = 4;
+constexpr int kPassTile = kPassThreads * kPassKeys;
+// Tile status word: the two highest bits a flag (0 none, 1 own count, 2 running
+// total including this tile), the others the value.  32 bits for sorts of fewer
+// than 2^30 keys.
+template <typename S>
+struct Status {
+    static constexpr int kBits = 8 * sizeof(S) - 2;
+    static constexpr S kOwn = (S)1 << kBits, kTotal = (S)2 << kBits, kValue = ((S)1 << kBits) - 1;
+};
+constexpr int64_t kShortStatus = (int64_t)1 << 30;
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const int lane = threadIdx.x & (kWave - 1);
@@ -127,28 +136,30 @@ __global__ __launch_bounds__(RB) void radix_hist_all_kernel(Src src, int64_t n, 
     }
 }
 
-template <typename K, bool HV, typename Src>
-__global__ __launch_bounds__(RB) void radix_pass_kernel(Src src, K* __restrict__ kout, int32_t* __restrict__ vout,
+template <typename K, typename S, typename Src>
+__global__ __launch_bounds__(kPassThreads) void radix_pass_kernel(Src src, K* __restrict__ kout, int32_t* __restrict__ vout,
                                                         int64_t n,
                                                         int shift, const uint32_t* __restrict__ dcount,
-                                                        unsigned long long* __restrict__ status,
+                                                        S* __restrict__ status,
                                                         uint32_t* __restrict__ ticket, uint32_t* __restrict__ err) {
-    __shared__ uint32_t wcnt[RW][RADIX];
+    using ST = Status<S>;
+    constexpr int T = kPassThreads, RI = kPassKeys, RTILE = kPassTile, PW = T / kWave;
+    static_assert(T >= RADIX, "a thread per digit");
+    __shared__ uint16_t wcnt[PW][RADIX];
     __shared__ uint32_t dstart[RADIX];
-    __shared__ unsigned long long gbase[RADIX];
-    constexpr int RI = keys_per_lane<K, HV>();
-    constexpr int RTILE = tile_keys<K, HV>();
-    __shared__ uint32_t wsum[RW];
-    __shared__ uint32_t hsum[RW];
+    __shared__ S gbase[RADIX];
+    __shared__ uint32_t wsum[RADIX / kWave];
+    __shared__ uint32_t hsum[RADIX / kWave];
     __shared__ K skeys[RTILE];
-    __shared__ int32_t svals[HV ? RTILE : 1];
+    __shared__ int32_t svals[RTILE];
     __shared__ uint32_t s_tile;
 
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x / kWave;
     if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
-    const uint32_t hc = dcount[threadIdx.x];  // all keys with this thread's digit
-    for (int ww = 0; ww < RW; ++ww) wcnt[ww][threadIdx.x] = 0;
+    const int d = threadIdx.x;
+    const uint32_t hc = d < RADIX ? dcount[d] : 0u;  // all keys with this thread's digit
+    for (int x = lane; x < RADIX; x += kWave) wcnt[w][x] = 0;
     __syncthreads();
     const int64_t tile = s_tile;
 
@@ -170,329 +181,148 @@ __global__ __launch_bounds__(RB) void radix_pass_kernel(Src src, K* __restrict__
     for (int r = 0; r < RI; ++r) {
         const int64_t i = wbase + (int64_t)r * kWave + lane;
         const bool valid = i < n;
-        const uint32_t d = valid ? (uint32_t)((k[r] >> shift) & (RADIX - 1)) : (uint32_t)RADIX - 1;
-        dig[r] = d;
-        const uint64_t peers = digit_peers(d);
+        const uint32_t kd = valid ? (uint32_t)((k[r] >> shift) & (RADIX - 1)) : (uint32_t)RADIX - 1;
+        dig[r] = kd;
+        const uint64_t peers = digit_peers(kd);
         const uint32_t below = (uint32_t)__popcll(peers & lt);
-        const uint32_t base = wcnt[w][d];
+        const uint32_t base = wcnt[w][kd];
         rank[r] = base + below;
-        if (below == 0) wcnt[w][d] = base + (uint32_t)__popcll(peers);
+        if (below == 0) wcnt[w][kd] = (uint16_t)(base + (uint32_t)__popcll(peers));
     }
     __syncthreads();
 
-    // per digit: exclusive offsets across waves and the tile's count
-    const int d = threadIdx.x;
-    uint32_t tot = 0;
-    for (int ww = 0; ww < RW; ++ww) {
-        const uint32_t c = wcnt[ww][d];
-        wcnt[ww][d] = tot;
-        tot += c;
-    }
-    // padding keys of the last tile were counted under digit 255: drop them
     const int64_t rem = n - tile0;
     const int valid_count = (int)(rem < RTILE ? rem : RTILE);
-    const uint32_t real = (d == RADIX - 1) ? tot - (uint32_t)(RTILE - valid_count) : tot;
+    uint32_t tot = 0, incl = 0, hincl = 0;
+    S excl = 0;
+    if (d < RADIX) {
+        // per digit: exclusive offsets across waves and the tile's count
+        for (int ww = 0; ww < PW; ++ww) {
+            const uint32_t c = wcnt[ww][d];
+            wcnt[ww][d] = (uint16_t)tot;
+            tot += c;
+        }
+        // padding keys of the last tile were counted under digit 255: drop them
+        const uint32_t real = (d == RADIX - 1) ? tot - (uint32_t)(RTILE - valid_count) : tot;
 
-    // publish, look back over earlier tiles, publish the running total
-    unsigned long long* st = status + tile * RADIX;
-    unsigned long long excl = 0;
-    if (tile == 0) {
-        __hip_atomic_store(&st[d], kFlagTotal | (unsigned long long)real, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        __hip_atomic_store(&st[d], kFlagOwn | (unsigned long long)real, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // earlier tiles' words for this digit, kLook at a time (independent loads)
-        constexpr int kLook = kLookBack;
-        uint32_t spins = 0;
-        int64_t j = tile - 1;
-        bool done = false;
-        while (!done && j >= 0) {
-            unsigned long long y[kLook];
+        // publish, look back over earlier tiles, publish the running total
+        S* st = status + tile * RADIX;
+        if (tile == 0) {
+            __hip_atomic_store(&st[d], ST::kTotal | (S)real, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            __hip_atomic_store(&st[d], ST::kOwn | (S)real, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // earlier tiles' words for this digit, kLook at a time (independent loads)
+            constexpr int kLook = kLookBack;
+            uint32_t spins = 0;
+            int64_t j = tile - 1;
+            bool done = false;
+            while (!done && j >= 0) {
+                S y[kLook];
 #pragma unroll
-            for (int b = 0; b < kLook; ++b)
-                y[b] = (j - b >= 0) ? __hip_atomic_load(&status[(j - b) * RADIX + d], __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT)
-                                    : kFlagTotal;
-            bool stalled = false;
+                for (int b = 0; b < kLook; ++b)
+                    y[b] = (j - b >= 0) ? __hip_atomic_load(&status[(j - b) * RADIX + d], __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT)
+                                        : ST::kTotal;
+                bool stalled = false;
 #pragma unroll
-            for (int b = 0; b < kLook; ++b) {
-                if (done || stalled) continue;
-                const unsigned long long flag = y[b] & ~kValMask;
-                if (flag == 0ull) {
-                    stalled = true;  // reload from tile j
-                } else {
-                    excl += y[b] & kValMask;
-                    --j;
-                    if (flag == kFlagTotal) done = true;
+                for (int b = 0; b < kLook; ++b) {
+                    if (done || stalled) continue;
+                    const S flag = y[b] & ~ST::kValue;
+                    if (flag == 0) {
+                        stalled = true;  // reload from tile j
+                    } else {
+                        excl += y[b] & ST::kValue;
+                        --j;
+                        if (flag == ST::kTotal) done = true;
+                    }
+                }
+                if (stalled) {
+                    if (++spins > kSpinLimit) {
+                        atomicOr(err, 1u);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
                 }
             }
-            if (stalled) {
-                if (++spins > kSpinLimit) {
-                    atomicOr(err, 1u);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
+            __hip_atomic_store(&st[d], ST::kTotal | (excl + real), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // digit starts inside the tile and in the output (scans over digits)
+        incl = tot;
+        hincl = hc;
+#pragma unroll
+        for (int s = 1; s < kWave; s <<= 1) {
+            const uint32_t u = __shfl_up(incl, s, kWave);
+            const uint32_t hu = __shfl_up(hincl, s, kWave);
+            if (lane >= s) {
+                incl += u;
+                hincl += hu;
             }
         }
-        __hip_atomic_store(&st[d], kFlagTotal | (excl + real), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // digit starts inside the tile and in the output (scans over digits)
-    uint32_t incl = tot, hincl = hc;
-#pragma unroll
-    for (int s = 1; s < kWave; s <<= 1) {
-        const uint32_t u = __shfl_up(incl, s, kWave);
-        const uint32_t hu = __shfl_up(hincl, s, kWave);
-        if (lane >= s) {
-            incl += u;
-            hincl += hu;
+        if (lane == kWave - 1) {
+            wsum[w] = incl;
+            hsum[w] = hincl;
         }
-    }
-    if (lane == kWave - 1) {
-        wsum[w] = incl;
-        hsum[w] = hincl;
     }
     __syncthreads();
-    uint32_t woff = 0, hoff = 0;
-    for (int ww = 0; ww < w; ++ww) {
-        woff += wsum[ww];
-        hoff += hsum[ww];
+    if (d < RADIX) {
+        uint32_t woff = 0, hoff = 0;
+        for (int ww = 0; ww < w; ++ww) {
+            woff += wsum[ww];
+            hoff += hsum[ww];
+        }
+        dstart[d] = woff + incl - tot;
+        gbase[d] = (S)(hoff + hincl - hc) + excl;
     }
-    dstart[d] = woff + incl - tot;
-    gbase[d] = (unsigned long long)(hoff + hincl - hc) + excl;
     __syncthreads();
 
 #pragma unroll
     for (int r = 0; r < RI; ++r) {
         const uint32_t pos = dstart[dig[r]] + wcnt[w][dig[r]] + rank[r];
         skeys[pos] = k[r];
-        if constexpr (HV) svals[pos] = v[r];
+        svals[pos] = v[r];
     }
     __syncthreads();
 
-    for (int i = threadIdx.x; i < valid_count; i += RB) {
+    for (int i = threadIdx.x; i < valid_count; i += T) {
         const K kk = skeys[i];
         const uint32_t dd = (uint32_t)((kk >> shift) & (RADIX - 1));
         const int64_t dst = (int64_t)gbase[dd] + (i - (int64_t)dstart[dd]);
         kout[dst] = kk;
-        if constexpr (HV) vout[dst] = svals[i];
-    }
-}
-
-// ---- reduce-then-scan passes (large inputs) --------------------------------
-// With thousands of tiles in flight, the look-back's chain of device-scope
-// reads sets the pace of a pass.  Large sorts therefore split a pass into
-// three launches with no waits: every tile counts its digits
-// (radix_up_kernel), one scan over the counts in digit-major order gives
-// every (digit, tile) run its output start, and every tile ranks its keys
-// again and scatters them (radix_down_kernel).  The tile layout and ranking
-// are those of the single-kernel pass, so the order is the same (stable).
-
-// ATOM: count with LDS adds (for digits that vary across neighbouring keys);
-// otherwise one add per distinct digit of a row, found with ballots (for
-// digits that repeat, where per-lane adds would serialise).
-template <typename K, bool HV, bool ATOM, typename Src>
-__global__ __launch_bounds__(RB) void radix_up_kernel(Src src, int64_t n, int shift, int64_t ntiles,
-                                                      uint32_t* __restrict__ cnt) {
-    constexpr int RI = keys_per_lane<K, HV>();
-    constexpr int RTILE = tile_keys<K, HV>();
-    __shared__ uint32_t wcnt[RW][RADIX];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = threadIdx.x / kWave;
-    for (int ww = 0; ww < RW; ++ww) wcnt[ww][threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t tile = blockIdx.x;
-    const int64_t wbase = tile * RTILE + (int64_t)w * (kWave * RI);
-    K k[RI];
-#pragma unroll
-    for (int r = 0; r < RI; ++r) {
-        const int64_t i = wbase + (int64_t)r * kWave + lane;
-        int32_t unused;
-        k[r] = (K)0;
-        if (i < n) src.load(i, k[r], unused);
-    }
-    if constexpr (ATOM) {
-        // counts only: order does not matter (a row whose lanes all share one
-        // digit adds once)
-#pragma unroll
-        for (int r = 0; r < RI; ++r) {
-            const bool valid = wbase + (int64_t)r * kWave + lane < n;
-            const uint32_t d = (uint32_t)((k[r] >> shift) & (RADIX - 1));
-            const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
-            const uint64_t vm = __ballot(valid);
-            if (__ballot(valid && d != d0) == 0ull) {
-                if (lane == 0 && vm) wcnt[w][d0] += (uint32_t)__popcll(vm);
-            } else if (valid) {
-                atomicAdd(&wcnt[w][d], 1u);
-            }
-        }
-    } else {
-        const uint64_t lt = lanemask_lt();
-#pragma unroll
-        for (int r = 0; r < RI; ++r) {
-            const bool valid = wbase + (int64_t)r * kWave + lane < n;
-            const uint32_t d = (uint32_t)((k[r] >> shift) & (RADIX - 1));
-            const uint64_t peers = digit_peers(d) & __ballot(valid);
-            if (valid && (peers & lt) == 0ull) wcnt[w][d] += (uint32_t)__popcll(peers);
-        }
-    }
-    __syncthreads();
-    uint32_t tot = 0;
-    for (int ww = 0; ww < RW; ++ww) tot += wcnt[ww][threadIdx.x];
-    cnt[(int64_t)threadIdx.x * ntiles + tile] = tot;
-}
-
-template <typename K, bool HV, typename Src>
-__global__ __launch_bounds__(RB) void radix_down_kernel(Src src, K* __restrict__ kout, int32_t* __restrict__ vout,
-                                                        int64_t n, int shift, int64_t ntiles,
-                                                        const uint32_t* __restrict__ off) {
-    constexpr int RI = keys_per_lane<K, HV>();
-    constexpr int RTILE = tile_keys<K, HV>();
-    __shared__ uint32_t wcnt[RW][RADIX];
-    __shared__ uint32_t dstart[RADIX];
-    __shared__ uint32_t gbase[RADIX];
-    __shared__ uint32_t wsum[RW];
-    __shared__ K skeys[RTILE];
-    __shared__ int32_t svals[HV ? RTILE : 1];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = threadIdx.x / kWave;
-    const int64_t tile = blockIdx.x;
-    const uint32_t gb = off[(int64_t)threadIdx.x * ntiles + tile];  // output start of this tile's digit run
-    for (int ww = 0; ww < RW; ++ww) wcnt[ww][threadIdx.x] = 0;
-    __syncthreads();
-
-    const int64_t tile0 = tile * RTILE;
-    const int64_t wbase = tile0 + (int64_t)w * (kWave * RI);
-    K k[RI];
-    int32_t v[RI];
-    uint32_t rank[RI];
-    uint32_t dig[RI];
-#pragma unroll
-    for (int r = 0; r < RI; ++r) {
-        const int64_t i = wbase + (int64_t)r * kWave + lane;
-        k[r] = (K)0;
-        v[r] = 0;
-        if (i < n) src.load(i, k[r], v[r]);
-    }
-    const uint64_t lt = lanemask_lt();
-#pragma unroll
-    for (int r = 0; r < RI; ++r) {
-        const int64_t i = wbase + (int64_t)r * kWave + lane;
-        const uint32_t d = i < n ? (uint32_t)((k[r] >> shift) & (RADIX - 1)) : (uint32_t)RADIX - 1;
-        dig[r] = d;
-        const uint64_t peers = digit_peers(d);
-        const uint32_t below = (uint32_t)__popcll(peers & lt);
-        const uint32_t base = wcnt[w][d];
-        rank[r] = base + below;
-        if (below == 0) wcnt[w][d] = base + (uint32_t)__popcll(peers);
-    }
-    __syncthreads();
-
-    const int d = threadIdx.x;
-    uint32_t tot = 0;
-    for (int ww = 0; ww < RW; ++ww) {
-        const uint32_t c = wcnt[ww][d];
-        wcnt[ww][d] = tot;
-        tot += c;
-    }
-    const int64_t rem = n - tile0;
-    const int valid_count = (int)(rem < RTILE ? rem : RTILE);
-    uint32_t incl = tot;
-#pragma unroll
-    for (int sh = 1; sh < kWave; sh <<= 1) {
-        const uint32_t u = __shfl_up(incl, sh, kWave);
-        if (lane >= sh) incl += u;
-    }
-    if (lane == kWave - 1) wsum[w] = incl;
-    __syncthreads();
-    uint32_t woff = 0;
-    for (int ww = 0; ww < w; ++ww) woff += wsum[ww];
-    dstart[d] = woff + incl - tot;
-    gbase[d] = gb;
-    __syncthreads();
-
-#pragma unroll
-    for (int r = 0; r < RI; ++r) {
-        const uint32_t pos = dstart[dig[r]] + wcnt[w][dig[r]] + rank[r];
-        skeys[pos] = k[r];
-        if constexpr (HV) svals[pos] = v[r];
-    }
-    __syncthreads();
-
-    // padding keys of the last tile sit after every valid key (digit 255, last)
-    for (int i = threadIdx.x; i < valid_count; i += RB) {
-        const K kk = skeys[i];
-        const uint32_t dd = (uint32_t)((kk >> shift) & (RADIX - 1));
-        const int64_t dst = (int64_t)gbase[dd] + (i - (int64_t)dstart[dd]);
-        kout[dst] = kk;
-        if constexpr (HV) vout[dst] = svals[i];
+        vout[dst] = svals[i];
     }
 }
 
 // Scratch layout: digit counts [MAXP][RADIX] u32, tickets [MAXP] u32 (padded),
-// then the tile status words [passes][tiles][RADIX] u64.
+// then the tile status words [passes][tiles][RADIX], u32 or u64.
 struct SortScratch {
     uint32_t* dcount;
     uint32_t* ticket;
-    unsigned long long* status;
+    void* status;
     int64_t zero_words;  // u64 words to clear from the start of the scratch
 };
 
-SortScratch carve(void* scratch, int64_t n, int passes, int rtile) {
-    const int64_t nb = cdiv(n > 0 ? n : 1, rtile);
+SortScratch carve(void* scratch, int64_t n, int passes) {
+    const int64_t nb = cdiv(n > 0 ? n : 1, kPassTile);
     auto* base = static_cast<unsigned long long*>(scratch);
     SortScratch s;
     s.dcount = reinterpret_cast<uint32_t*>(base);                          // MAXP*RADIX u32 = 1024 u64
     s.ticket = reinterpret_cast<uint32_t*>(base + MAXP * RADIX / 2);      // 64 u64 of room
     s.status = base + MAXP * RADIX / 2 + 64;
-    s.zero_words = MAXP * RADIX / 2 + 64 + (int64_t)passes * nb * RADIX;
+    s.zero_words = MAXP * RADIX / 2 + 64 + (int64_t)passes * nb * RADIX / (n < kShortStatus ? 2 : 1);
     return s;
 }
 
 // Sorts n entries read from src by bits [shift0, shift0 + bits) of the key;
 // pass ps writes (kout, vout) when the number of passes after it is even,
 // else the alternate arrays, so the last pass always lands in (kout, vout).
-// Without values (HV false) the value arrays are not touched.
 // counted: the scratch is cleared and the digit totals are in place.
-template <typename K, bool HV, typename Src>
+template <typename K, typename Src>
 void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int64_t n, int shift0, int bits,
                     void* scratch, uint32_t* err, hipStream_t s, bool counted = false) {
-    constexpr int RTILE = tile_keys<K, HV>();
     const int passes = (bits + 7) / 8;
-    const int nb = (int)cdiv(n, RTILE);
-    if (nb >= kRtsMinTiles && (int64_t)nb * RADIX <= (int64_t)UINT32_MAX && n <= (int64_t)UINT32_MAX) {
-        // reduce-then-scan: counts [RADIX][nb] (in place: output starts), then the scan's scratch
-        auto* base = static_cast<uint32_t*>(scratch);
-        uint32_t* total = base;  // the scan's total (unused)
-        uint32_t* cnt = base + 64;
-        void* sscr = cnt + round_up((int64_t)nb * RADIX, 64);
-        const int64_t nc = (int64_t)nb * RADIX;
-        for (int ps = 0; ps < passes; ++ps) {
-            const bool to_out = ((passes - 1 - ps) & 1) == 0;
-            K* ko = to_out ? kout : kalt;
-            int32_t* vo = to_out ? vout : valt;
-            const int shift = shift0 + 8 * ps;
-            if (ps == 0) {
-                hipLaunchKernelGGL((radix_up_kernel<K, HV, true, Src>), dim3(nb), dim3(RB), 0, s, src, n, shift,
-                                   (int64_t)nb, cnt);
-                TFMM_LAUNCHED();
-                exclusive_scan_u32(cnt, cnt, nc, sscr, total, s);
-                hipLaunchKernelGGL((radix_down_kernel<K, HV, Src>), dim3(nb), dim3(RB), 0, s, src, ko, vo, n, shift,
-                                   (int64_t)nb, (const uint32_t*)cnt);
-                TFMM_LAUNCHED();
-            } else {
-                const ArraySrc<K> prev{to_out ? kalt : kout, to_out ? valt : vout};
-                hipLaunchKernelGGL((radix_up_kernel<K, HV, false, ArraySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, n, shift,
-                                   (int64_t)nb, cnt);
-                TFMM_LAUNCHED();
-                exclusive_scan_u32(cnt, cnt, nc, sscr, total, s);
-                hipLaunchKernelGGL((radix_down_kernel<K, HV, ArraySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, ko, vo, n,
-                                   shift, (int64_t)nb, (const uint32_t*)cnt);
-                TFMM_LAUNCHED();
-            }
-        }
-        return;
-    }
-    const SortScratch sc = carve(scratch, n, passes, RTILE);
+    const int64_t pt = cdiv(n, kPassTile);
+    const SortScratch sc = carve(scratch, n, passes);
     if (!counted) {
         const unsigned zb = (unsigned)std::min<int64_t>(2048, cdiv(sc.zero_words, RB));
         hipLaunchKernelGGL(zero_u64_kernel, dim3(zb), dim3(RB), 0, s, static_cast<unsigned long long*>(scratch),
@@ -508,17 +338,21 @@ void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int
         K* ko = to_out ? kout : kalt;
         int32_t* vo = to_out ? vout : valt;
         const uint32_t* db = sc.dcount + ps * RADIX;
-        unsigned long long* st = sc.status + (int64_t)ps * nb * RADIX;
         const int shift = shift0 + 8 * ps;
-        if (ps == 0) {
-            hipLaunchKernelGGL((radix_pass_kernel<K, HV, Src>), dim3(nb), dim3(RB), 0, s, src, ko, vo, n, shift,
-                               db, st, sc.ticket, err);
-        } else {
-            // the previous pass wrote the other pair of arrays
-            const ArraySrc<K> prev{to_out ? kalt : kout, to_out ? valt : vout};
-            hipLaunchKernelGGL((radix_pass_kernel<K, HV, ArraySrc<K>>), dim3(nb), dim3(RB), 0, s, prev, ko, vo, n,
-                               shift, db, st, sc.ticket + ps, err);
-        }
+        auto pass = [&](auto word, auto from) {
+            using S = decltype(word);
+            using From = decltype(from);
+            hipLaunchKernelGGL((radix_pass_kernel<K, S, From>), dim3((unsigned)pt), dim3(kPassThreads), 0, s, from,
+                               ko, vo, n, shift, db, static_cast<S*>(sc.status) + (int64_t)ps * pt * RADIX,
+                               sc.ticket + ps, err);
+        };
+        auto sized = [&](auto from) {
+            if (n < kShortStatus) pass(uint32_t{}, from);
+            else pass((unsigned long long)0, from);
+        };
+        // a later pass reads what the one before wrote, the other pair of arrays
+        if (ps == 0) sized(src);
+        else sized(ArraySrc<K>{to_out ? kalt : kout, to_out ? valt : vout});
         TFMM_LAUNCHED();
     }
 }
@@ -533,10 +367,10 @@ void radix_sort_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int
         // copy there back into the caller's arrays
         TFMM_HIP(hipMemcpyAsync(keys_alt, keys, (size_t)n * sizeof(K), hipMemcpyDeviceToDevice, s));
         TFMM_HIP(hipMemcpyAsync(vals_alt, vals, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        radix_sort_run<K, true>(ArraySrc<K>{keys_alt, vals_alt}, keys, vals, keys_alt, vals_alt, n, 0, bits, scratch,
+        radix_sort_run<K>(ArraySrc<K>{keys_alt, vals_alt}, keys, vals, keys_alt, vals_alt, n, 0, bits, scratch,
                                 err, s);
     } else {
-        radix_sort_run<K, true>(ArraySrc<K>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits, scratch, err,
+        radix_sort_run<K>(ArraySrc<K>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits, scratch, err,
                                 s);
     }
 }
@@ -544,9 +378,7 @@ void radix_sort_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int
 }  // namespace
 
 uint32_t* sort_counts(void* scratch, int64_t n, int bits, int64_t* clear_words) {
-    const int rtile = tile_keys<uint64_t, true>();
-    if (cdiv(n, rtile) >= kRtsMinTiles) return nullptr;
-    const SortScratch sc = carve(scratch, n, (bits + 7) / 8, rtile);
+    const SortScratch sc = carve(scratch, n, (bits + 7) / 8);
     *clear_words = sc.zero_words;
     return sc.dcount;
 }
@@ -555,17 +387,12 @@ void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, i
                             int bits, void* scratch, uint32_t* err, hipStream_t s) {
     if (n <= 1 || bits <= 0) return;
     if (((bits + 7) / 8) & 1) fail(TFMM_EINVAL, "a counted sort takes an even number of passes");
-    radix_sort_run<uint64_t, true>(ArraySrc<uint64_t>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits,
+    radix_sort_run<uint64_t>(ArraySrc<uint64_t>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits,
                                    scratch, err, s, true);
 }
 
 size_t sort_scratch_bytes(int64_t n, int bits) {
-    const int passes = bits <= 0 ? 1 : (bits + 7) / 8;
-    const int rtile = std::min({tile_keys<uint32_t, true>(), tile_keys<uint32_t, false>(), tile_keys<uint64_t, true>()});
-    const size_t onesweep = (size_t)carve(nullptr, n, passes, rtile).zero_words * 8 + 256;
-    const int64_t nc = cdiv(n > 0 ? n : 1, rtile) * RADIX;
-    const size_t rts = (size_t)(64 + round_up(nc, 64)) * 4 + scan_scratch_bytes(nc) + 256;
-    return std::max(onesweep, rts);
+    return (size_t)carve(nullptr, n, bits <= 0 ? 1 : (bits + 7) / 8).zero_words * 8 + 256;
 }
 
 void radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n, int bits,
@@ -583,7 +410,7 @@ void radix_sort_pairs(const int2* pairs, int64_t np, bool self_dummy, uint32_t s
                       hipStream_t s) {
     const int64_t n = 2 * np;
     if (n <= 0) return;
-    radix_sort_run<uint32_t, true>(PairSrc{pairs, self_key, self_dummy ? 1 : 0}, keys, vals, keys_alt, vals_alt, n,
+    radix_sort_run<uint32_t>(PairSrc{pairs, self_key, self_dummy ? 1 : 0}, keys, vals, keys_alt, vals_alt, n,
                                    0, bits > 0 ? bits : 1, scratch, err, s);
 }
 
