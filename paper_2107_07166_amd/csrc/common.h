@@ -201,7 +201,6 @@ struct Tree {
     int n_sets = 1;
     DevBuf set_off;            // int64, n_sets + 1 (device)
     DevBuf set_theta;          // FP64 theta of every set for the walk (device)
-    DevBuf set_sort;           // forest sort scratch: set keys and positions
     void* stage = nullptr;     // pinned host staging of the set tables
     hipEvent_t stage_ev = nullptr;  // the last upload from it
     // tree sizes (host copies)
@@ -293,31 +292,31 @@ struct Tree {
 
 // ---- scans (scan.hip) -----------------------------------------------------
 size_t scan_scratch_bytes(int64_t n);
-// Exclusive scan of n values (in == out allowed); writes the total to
-// *total_dev (device).
-void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, void* scratch, uint32_t* total_dev,
-                        hipStream_t s);
-// Two scans of n values each (one launch when n is small).
+// Two exclusive scans of n values each (one launch when n is small); the totals
+// land in *total0 and *total1 (device).
 void exclusive_scan2_u32(const uint32_t* in0, uint32_t* out0, uint32_t* total0, const uint32_t* in1,
                          uint32_t* out1, uint32_t* total1, int64_t n, void* scratch, hipStream_t s);
-// The same over gathered values: value i = val[idx[i]] (val non-negative).
+// One over gathered values: value i = val[idx[i]] (val non-negative).
 void exclusive_scan_gather_u32(const int32_t* idx, const int32_t* val, uint32_t* out, int64_t n, void* scratch,
                                uint32_t* total_dev, hipStream_t s);
 
 // ---- radix sort (sort.hip) ----------------------------------------------------
-size_t sort_scratch_bytes(int64_t n, int bits);
-// Stable LSD sort of (key, value) by the low `bits` bits of key; result ends in
-// keys/vals (alt buffers are scratch of the same size).
-void radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt,
-                    int64_t n, int bits, void* scratch, uint32_t* err, hipStream_t s);
-void radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt,
-                    int64_t n, int bits, void* scratch, uint32_t* err, hipStream_t s);
-// radix_sort_u64 with the digit totals counted by the caller: sort_counts gives
-// their place in the scratch (8 passes of 256 words, then the words the passes
-// need cleared up to *clear_words from the start).
-uint32_t* sort_counts(void* scratch, int64_t n, int bits, int64_t* clear_words);
-void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
-                            int bits, void* scratch, uint32_t* err, hipStream_t s);
+constexpr int sort_passes(int bits) { return bits <= 0 ? 1 : (bits + 7) / 8; }
+size_t sort_scratch_bytes(int64_t n, int passes);
+// Where the digit totals of a sort stand in its scratch (256 words per pass);
+// the sort needs the scratch cleared up to *clear_words before they are counted
+// (by sort_clear or the caller's own kernel).
+uint32_t* sort_counts(void* scratch, int64_t n, int passes, int64_t* clear_words);
+void sort_clear(void* scratch, int64_t words, hipStream_t s);
+// Stable sort of n >= 2 particles by set (off: n_sets + 1 starts on the device;
+// none for a single set) and key.  The digit totals of the kKeyPasses passes
+// over the key and the set_passes(n_sets) over the set number are in place.  The
+// input is in (keys, vals), or in the alternate arrays when the number of passes
+// is odd; the result ends in (keys, vals).
+constexpr int kKeyPasses = 8;
+constexpr int set_passes(int n_sets) { return n_sets <= 1 ? 0 : (n_sets <= 256 ? 1 : 2); }
+void radix_sort_particles(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
+                          const int64_t* off, int n_sets, void* scratch, uint32_t* err, hipStream_t s);
 // Stable sort by key of the 2 np directed entries of np node pairs: entry 2i
 // is (key x_i, value y_i), entry 2i + 1 is (y_i, x_i); with self_dummy, the
 // second entry of a pair (x, x) gets key self_key instead.  The sorted

@@ -727,7 +727,7 @@ void sorted_lists(Tree& t, const DevBuf& pairs, int64_t np, bool self_dummy, Dev
     uint32_t* kalt = scr2.as<uint32_t>();
     int32_t* valt = reinterpret_cast<int32_t*>(kalt + room);
     const int bits = bits_for(self_dummy ? nn + 1 : nn);
-    scr.ensure(ctx, sort_scratch_bytes(ne, bits) + 1024);
+    scr.ensure(ctx, sort_scratch_bytes(ne, sort_passes(bits)) + 1024);
     radix_sort_pairs(pairs.as<int2>(), np, self_dummy, (uint32_t)nn, tgtbuf.as<uint32_t>(), src.as<int32_t>(), kalt,
                      valt, bits, scr.p, ctx->dev_err, s);
     hipLaunchKernelGGL(csr_offsets_kernel, dim3(grid(cdiv(ne + 1, 4))), dim3(TB), 0, s,

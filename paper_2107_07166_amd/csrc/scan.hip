@@ -198,11 +198,6 @@ size_t scan_scratch_bytes(int64_t n) {
     return words * 4 + 256;
 }
 
-void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, void* scratch, uint32_t* total_dev,
-                        hipStream_t s) {
-    scan_run(ArrayIn{in}, out, n, scratch, total_dev, s);
-}
-
 void exclusive_scan2_u32(const uint32_t* in0, uint32_t* out0, uint32_t* total0, const uint32_t* in1,
                          uint32_t* out1, uint32_t* total1, int64_t n, void* scratch, hipStream_t s) {
     const Job<ArrayIn> j0{ArrayIn{in0}, out0, nullptr, total0}, j1{ArrayIn{in1}, out1, nullptr, total1};

@@ -1,7 +1,9 @@
-// Stable LSD radix sort of (key, int32 value) pairs, 8-bit digits.
+// Stable LSD radix sort of (key, int32 value) pairs, 8-bit digits.  After the
+// key's digits, the particle sort of a forest takes the digits of the set that
+// the value (a particle's input index) belongs to.
 //
-// One histogram kernel counts the digits of every pass at once (the global
-// digit totals do not depend on the order of the keys).  Each pass is then a
+// One histogram kernel, or the caller's own, counts the digits of every pass at
+// once (the global digit totals do not depend on the order of the keys).  Each pass is then a
 // single kernel over 4096-key tiles: a tile scans the pass's digit totals
 // itself (the output start of every digit), ranks its keys (wave ballots find
 // the lanes sharing a digit, a per-wave LDS counter carries ranks across
@@ -19,7 +21,7 @@
 // device error word, which the host checks at its next read-back; the kernel
 // always runs to its end.
 //
-// The histogram and the first pass read their input through a source: plain
+// The first pass (and the histogram) reads its input through a source: plain
 // key and value arrays, or an array of node pairs read as directed entries
 // (entry 2i = (x_i <- y_i), entry 2i + 1 = (y_i <- x_i)), which spares the
 // lists an expansion pass before the sort.
@@ -33,7 +35,7 @@ namespace {
 constexpr int RADIX = 256;
 constexpr int kLookBack = 4;      // earlier tiles read per look-back step
 constexpr int RB = 256;           // threads per block of the histogram (one digit per thread)
-constexpr int MAXP = 8;          // passes of a 64-bit key
+constexpr int MAXP = 10;         // passes of a 64-bit key and a set number
 constexpr int kHistBlocks = 1024;
 constexpr int kHistKeysPerThread = 16;  // fewer blocks, fewer global atomics
 constexpr uint32_t kSpinLimit = 1u << 20;
@@ -99,33 +101,48 @@ struct PairSrc {
     }
 };
 
+// Digit of an entry.
+struct KeyDigit {
+    int shift;
+    template <typename K>
+    __device__ __forceinline__ uint32_t operator()(K key, int32_t) const {
+        return (uint32_t)(key >> shift) & (RADIX - 1);
+    }
+};
+struct SetDigit {
+    const int64_t* off;
+    int n_sets, shift;
+    __device__ __forceinline__ uint32_t operator()(uint64_t, int32_t val) const {
+        return (uint32_t)(set_of(off, n_sets, val) >> shift) & (RADIX - 1);
+    }
+};
+
 __global__ __launch_bounds__(RB) void zero_u64_kernel(unsigned long long* __restrict__ p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * RB + threadIdx.x; i < n; i += (int64_t)gridDim.x * RB) p[i] = 0ull;
 }
 
 // Digit totals of every pass: LDS counters per block, then global atomics.
-template <typename K, typename Src>
-__global__ __launch_bounds__(RB) void radix_hist_all_kernel(Src src, int64_t n, int shift0, int passes,
-                                                            uint32_t* __restrict__ ghist) {
-    __shared__ uint32_t h[MAXP][RADIX];
-    for (int p = 0; p < MAXP; ++p) h[p][threadIdx.x] = 0u;
+__global__ __launch_bounds__(RB) void radix_hist_pairs_kernel(PairSrc src, int64_t n, int passes,
+                                                              uint32_t* __restrict__ ghist) {
+    __shared__ uint32_t h[4][RADIX];
+    for (int p = 0; p < 4; ++p) h[p][threadIdx.x] = 0u;
     __syncthreads();
     constexpr int U = kHistKeysPerThread;  // loads in flight per thread
     const int64_t stride = (int64_t)gridDim.x * RB * U;
     for (int64_t base = (int64_t)blockIdx.x * RB * U; base < n; base += stride) {
-        K k[U];
+        uint32_t k[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = base + (int64_t)u * RB + threadIdx.x;
             int32_t unused;
-            k[u] = (K)0;
+            k[u] = 0u;
             if (i < n) src.load(i, k[u], unused);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (base + (int64_t)u * RB + threadIdx.x < n) {
                 for (int p = 0; p < passes; ++p)
-                    atomicAdd(&h[p][(uint32_t)(k[u] >> (shift0 + 8 * p)) & (RADIX - 1)], 1u);
+                    atomicAdd(&h[p][(k[u] >> (8 * p)) & (RADIX - 1)], 1u);
             }
         }
     }
@@ -136,10 +153,10 @@ __global__ __launch_bounds__(RB) void radix_hist_all_kernel(Src src, int64_t n, 
     }
 }
 
-template <typename K, typename S, typename Src>
-__global__ __launch_bounds__(kPassThreads) void radix_pass_kernel(Src src, K* __restrict__ kout, int32_t* __restrict__ vout,
+template <typename K, typename S, typename Dig, typename Src>
+__global__ __launch_bounds__(kPassThreads) void radix_pass_kernel(Src src, Dig digit, K* __restrict__ kout, int32_t* __restrict__ vout,
                                                         int64_t n,
-                                                        int shift, const uint32_t* __restrict__ dcount,
+                                                        const uint32_t* __restrict__ dcount,
                                                         S* __restrict__ status,
                                                         uint32_t* __restrict__ ticket, uint32_t* __restrict__ err) {
     using ST = Status<S>;
@@ -181,7 +198,7 @@ __global__ __launch_bounds__(kPassThreads) void radix_pass_kernel(Src src, K* __
     for (int r = 0; r < RI; ++r) {
         const int64_t i = wbase + (int64_t)r * kWave + lane;
         const bool valid = i < n;
-        const uint32_t kd = valid ? (uint32_t)((k[r] >> shift) & (RADIX - 1)) : (uint32_t)RADIX - 1;
+        const uint32_t kd = valid ? digit(k[r], v[r]) : (uint32_t)RADIX - 1;
         dig[r] = kd;
         const uint64_t peers = digit_peers(kd);
         const uint32_t below = (uint32_t)__popcll(peers & lt);
@@ -286,10 +303,11 @@ __global__ __launch_bounds__(kPassThreads) void radix_pass_kernel(Src src, K* __
 
     for (int i = threadIdx.x; i < valid_count; i += T) {
         const K kk = skeys[i];
-        const uint32_t dd = (uint32_t)((kk >> shift) & (RADIX - 1));
+        const int32_t vv = svals[i];
+        const uint32_t dd = digit(kk, vv);
         const int64_t dst = (int64_t)gbase[dd] + (i - (int64_t)dstart[dd]);
         kout[dst] = kk;
-        vout[dst] = svals[i];
+        vout[dst] = vv;
     }
 }
 
@@ -306,112 +324,84 @@ SortScratch carve(void* scratch, int64_t n, int passes) {
     const int64_t nb = cdiv(n > 0 ? n : 1, kPassTile);
     auto* base = static_cast<unsigned long long*>(scratch);
     SortScratch s;
-    s.dcount = reinterpret_cast<uint32_t*>(base);                          // MAXP*RADIX u32 = 1024 u64
+    s.dcount = reinterpret_cast<uint32_t*>(base);                          // MAXP*RADIX u32
     s.ticket = reinterpret_cast<uint32_t*>(base + MAXP * RADIX / 2);      // 64 u64 of room
     s.status = base + MAXP * RADIX / 2 + 64;
     s.zero_words = MAXP * RADIX / 2 + 64 + (int64_t)passes * nb * RADIX / (n < kShortStatus ? 2 : 1);
     return s;
 }
 
-// Sorts n entries read from src by bits [shift0, shift0 + bits) of the key;
-// pass ps writes (kout, vout) when the number of passes after it is even,
-// else the alternate arrays, so the last pass always lands in (kout, vout).
-// counted: the scratch is cleared and the digit totals are in place.
+// The passes of a sort of n entries read from src (scratch cleared, digit totals
+// in place): the key's first bits, then the number of the value's set if off is
+// given.  Pass ps writes (kout, vout) when the number of passes after it is
+// even, else the alternate arrays, so the last pass always lands in (kout, vout).
 template <typename K, typename Src>
-void radix_sort_run(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int64_t n, int shift0, int bits,
-                    void* scratch, uint32_t* err, hipStream_t s, bool counted = false) {
-    const int passes = (bits + 7) / 8;
+void radix_passes(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int64_t n, int key_passes, int passes,
+                  const int64_t* off, int n_sets, void* scratch, uint32_t* err, hipStream_t s) {
     const int64_t pt = cdiv(n, kPassTile);
     const SortScratch sc = carve(scratch, n, passes);
-    if (!counted) {
-        const unsigned zb = (unsigned)std::min<int64_t>(2048, cdiv(sc.zero_words, RB));
-        hipLaunchKernelGGL(zero_u64_kernel, dim3(zb), dim3(RB), 0, s, static_cast<unsigned long long*>(scratch),
-                           sc.zero_words);
-        TFMM_LAUNCHED();
-        const unsigned hb = (unsigned)std::min<int64_t>(kHistBlocks, cdiv(n, RB * kHistKeysPerThread));
-        hipLaunchKernelGGL((radix_hist_all_kernel<K, Src>), dim3(hb), dim3(RB), 0, s, src, n, shift0, passes,
-                           sc.dcount);
-        TFMM_LAUNCHED();
-    }
     for (int ps = 0; ps < passes; ++ps) {
         const bool to_out = ((passes - 1 - ps) & 1) == 0;
         K* ko = to_out ? kout : kalt;
         int32_t* vo = to_out ? vout : valt;
         const uint32_t* db = sc.dcount + ps * RADIX;
-        const int shift = shift0 + 8 * ps;
-        auto pass = [&](auto word, auto from) {
+        auto pass = [&](auto word, auto from, auto digit) {
             using S = decltype(word);
-            using From = decltype(from);
-            hipLaunchKernelGGL((radix_pass_kernel<K, S, From>), dim3((unsigned)pt), dim3(kPassThreads), 0, s, from,
-                               ko, vo, n, shift, db, static_cast<S*>(sc.status) + (int64_t)ps * pt * RADIX,
-                               sc.ticket + ps, err);
+            hipLaunchKernelGGL((radix_pass_kernel<K, S, decltype(digit), decltype(from)>), dim3((unsigned)pt),
+                               dim3(kPassThreads), 0, s, from, digit, ko, vo, n, db,
+                               static_cast<S*>(sc.status) + (int64_t)ps * pt * RADIX, sc.ticket + ps, err);
+            TFMM_LAUNCHED();
         };
-        auto sized = [&](auto from) {
-            if (n < kShortStatus) pass(uint32_t{}, from);
-            else pass((unsigned long long)0, from);
+        auto sized = [&](auto from, auto digit) {
+            if (n < kShortStatus) pass(uint32_t{}, from, digit);
+            else pass((unsigned long long)0, from, digit);
         };
         // a later pass reads what the one before wrote, the other pair of arrays
-        if (ps == 0) sized(src);
-        else sized(ArraySrc<K>{to_out ? kalt : kout, to_out ? valt : vout});
-        TFMM_LAUNCHED();
-    }
-}
-
-template <typename K>
-void radix_sort_impl(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int64_t n, int bits, void* scratch,
-                     uint32_t* err, hipStream_t s) {
-    if (n <= 1 || bits <= 0) return;
-    const int passes = (bits + 7) / 8;
-    if (passes & 1) {
-        // an odd number of passes ends in the alternate arrays: sort from a
-        // copy there back into the caller's arrays
-        TFMM_HIP(hipMemcpyAsync(keys_alt, keys, (size_t)n * sizeof(K), hipMemcpyDeviceToDevice, s));
-        TFMM_HIP(hipMemcpyAsync(vals_alt, vals, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        radix_sort_run<K>(ArraySrc<K>{keys_alt, vals_alt}, keys, vals, keys_alt, vals_alt, n, 0, bits, scratch,
-                                err, s);
-    } else {
-        radix_sort_run<K>(ArraySrc<K>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits, scratch, err,
-                                s);
+        const ArraySrc<K> prev{to_out ? kalt : kout, to_out ? valt : vout};
+        if (ps == 0) sized(src, KeyDigit{0});
+        else if (ps < key_passes) sized(prev, KeyDigit{8 * ps});
+        else if constexpr (sizeof(K) == 8) sized(prev, SetDigit{off, n_sets, 8 * (ps - key_passes)});
     }
 }
 
 }  // namespace
 
-uint32_t* sort_counts(void* scratch, int64_t n, int bits, int64_t* clear_words) {
-    const SortScratch sc = carve(scratch, n, (bits + 7) / 8);
+uint32_t* sort_counts(void* scratch, int64_t n, int passes, int64_t* clear_words) {
+    const SortScratch sc = carve(scratch, n, passes);
     *clear_words = sc.zero_words;
     return sc.dcount;
 }
 
-void radix_sort_u64_counted(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
-                            int bits, void* scratch, uint32_t* err, hipStream_t s) {
-    if (n <= 1 || bits <= 0) return;
-    if (((bits + 7) / 8) & 1) fail(TFMM_EINVAL, "a counted sort takes an even number of passes");
-    radix_sort_run<uint64_t>(ArraySrc<uint64_t>{keys, vals}, keys, vals, keys_alt, vals_alt, n, 0, bits,
-                                   scratch, err, s, true);
+void sort_clear(void* scratch, int64_t words, hipStream_t s) {
+    hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)std::min<int64_t>(2048, cdiv(words, RB))), dim3(RB), 0, s,
+                       static_cast<unsigned long long*>(scratch), words);
+    TFMM_LAUNCHED();
 }
 
-size_t sort_scratch_bytes(int64_t n, int bits) {
-    return (size_t)carve(nullptr, n, bits <= 0 ? 1 : (bits + 7) / 8).zero_words * 8 + 256;
+void radix_sort_particles(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
+                          const int64_t* off, int n_sets, void* scratch, uint32_t* err, hipStream_t s) {
+    const int passes = kKeyPasses + set_passes(n_sets);
+    const bool odd = passes & 1;
+    radix_passes<uint64_t>(ArraySrc<uint64_t>{odd ? keys_alt : keys, odd ? vals_alt : vals}, keys, vals, keys_alt,
+                           vals_alt, n, kKeyPasses, passes, off, n_sets, scratch, err, s);
 }
 
-void radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n, int bits,
-                    void* scratch, uint32_t* err, hipStream_t s) {
-    radix_sort_impl<uint64_t>(keys, vals, keys_alt, vals_alt, n, bits, scratch, err, s);
-}
-
-void radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n, int bits,
-                    void* scratch, uint32_t* err, hipStream_t s) {
-    radix_sort_impl<uint32_t>(keys, vals, keys_alt, vals_alt, n, bits, scratch, err, s);
-}
+size_t sort_scratch_bytes(int64_t n, int passes) { return (size_t)carve(nullptr, n, passes).zero_words * 8 + 256; }
 
 void radix_sort_pairs(const int2* pairs, int64_t np, bool self_dummy, uint32_t self_key, uint32_t* keys,
                       int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int bits, void* scratch, uint32_t* err,
                       hipStream_t s) {
     const int64_t n = 2 * np;
     if (n <= 0) return;
-    radix_sort_run<uint32_t>(PairSrc{pairs, self_key, self_dummy ? 1 : 0}, keys, vals, keys_alt, vals_alt, n,
-                                   0, bits > 0 ? bits : 1, scratch, err, s);
+    const int passes = sort_passes(bits);
+    int64_t words = 0;
+    uint32_t* counts = sort_counts(scratch, n, passes, &words);
+    sort_clear(scratch, words, s);
+    const PairSrc src{pairs, self_key, self_dummy ? 1 : 0};
+    const unsigned hb = (unsigned)std::min<int64_t>(kHistBlocks, cdiv(n, RB * kHistKeysPerThread));
+    hipLaunchKernelGGL(radix_hist_pairs_kernel, dim3(hb), dim3(RB), 0, s, src, n, passes, counts);
+    TFMM_LAUNCHED();
+    radix_passes<uint32_t>(src, keys, vals, keys_alt, vals_alt, n, passes, passes, nullptr, 1, scratch, err, s);
 }
 
 }  // namespace tfmm

@@ -134,48 +134,67 @@ __device__ void cube_of_parts(const double* __restrict__ part, int nb, double* _
     __syncthreads();
 }
 
-// The cubes of the sets of a forest, one block per set (cube k at out + 16 k).
-__global__ __launch_bounds__(TB) void bbox_sets_kernel(const double* __restrict__ pos,
-                                                       const int64_t* __restrict__ off,
-                                                       double* __restrict__ out) {
-    const int64_t a0 = off[blockIdx.x], a1 = off[blockIdx.x + 1];
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    int bad = 0;
-    for (int64_t a = a0 + threadIdx.x; a < a1; a += TB) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double v = pos[3 * a + d];
-            bad |= !isfinite(v);
-            lo[d] = v < lo[d] ? v : lo[d];
-            hi[d] = v > hi[d] ? v : hi[d];
-        }
-    }
-    __shared__ double sh[6][TB];
-    __shared__ int s_bad;
-    if (threadIdx.x == 0) s_bad = 0;
-    __syncthreads();
-    if (bad) s_bad = 1;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        sh[d][threadIdx.x] = lo[d];
-        sh[3 + d][threadIdx.x] = hi[d];
-    }
-    __syncthreads();
-    for (int st = TB / 2; st > 0; st >>= 1) {
-        if (threadIdx.x < st) {
+// Doubles in the order of unsigned integers, above 0 (the cleared word).
+__device__ __forceinline__ unsigned long long ordered(double x) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    return (u >> 63) ? ~u : (u | 1ull << 63);
+}
+__device__ __forceinline__ double from_ordered(unsigned long long u) {
+    return __longlong_as_double((long long)((u >> 63) ? (u & ~(1ull << 63)) : ~u));
+}
+
+// The bounding boxes of the sets of a forest, box k in the cleared words
+// boxes + 8 k: the largest inverse ordered word of a coordinate (its minimum)
+// [0..2], the largest ordered word [3..5], not finite [6].  A wavefront takes
+// 1024 consecutive particles, whatever the sets, so that a large set is spread
+// as a single one is (a workgroup per set took 19 us for 16 sets of 8192).
+constexpr int kBoxRun = 1024;
+__global__ __launch_bounds__(TB) void bbox_sets_kernel(const double* __restrict__ pos, int64_t n,
+                                                       const int64_t* __restrict__ off, int n_sets,
+                                                       unsigned long long* __restrict__ boxes) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t w0 = ((int64_t)blockIdx.x * (TB / kWave) + threadIdx.x / kWave) * kBoxRun;
+    const int64_t w1 = w0 + kBoxRun < n ? w0 + kBoxRun : n;
+    if (w0 >= n) return;
+    for (int k = set_of(off, n_sets, w0); k < n_sets && off[k] < w1; ++k) {
+        const int64_t a0 = off[k] > w0 ? off[k] : w0, a1 = off[k + 1] < w1 ? off[k + 1] : w1;
+        double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+        bool bad = false;
+#pragma unroll 4
+        for (int64_t a = a0 + lane; a < a1; a += kWave) {
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
-                const double x = sh[d][threadIdx.x + st], y = sh[3 + d][threadIdx.x + st];
-                if (x < sh[d][threadIdx.x]) sh[d][threadIdx.x] = x;
-                if (y > sh[3 + d][threadIdx.x]) sh[3 + d][threadIdx.x] = y;
+                const double v = pos[3 * a + d];
+                bad |= !isfinite(v);
+                lo[d] = v < lo[d] ? v : lo[d];
+                hi[d] = v > hi[d] ? v : hi[d];
             }
         }
-        __syncthreads();
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const double x = __shfl_xor(lo[d], o, kWave), y = __shfl_xor(hi[d], o, kWave);
+                lo[d] = x < lo[d] ? x : lo[d];
+                hi[d] = y > hi[d] ? y : hi[d];
+            }
+        }
+        unsigned long long* box = boxes + 8 * (int64_t)k;
+        if (__ballot(bad) != 0ull && lane == 6) atomicMax(&box[6], 1ull);
+        if (lane < 3) atomicMax(&box[lane], ~ordered(lane == 0 ? lo[0] : (lane == 1 ? lo[1] : lo[2])));
+        else if (lane < 6) atomicMax(&box[lane], ordered(lane == 3 ? hi[0] : (lane == 4 ? hi[1] : hi[2])));
     }
-    if (threadIdx.x == 0) {
-        const double l[3] = {sh[0][0], sh[1][0], sh[2][0]}, h[3] = {sh[3][0], sh[4][0], sh[5][0]};
-        write_cube(l, h, s_bad != 0, out + 16 * (int64_t)blockIdx.x);
+}
+
+// The cube of a set from its box.
+__device__ __forceinline__ void cube_of_box(const unsigned long long* __restrict__ box, double* cube) {
+    double lo[3], hi[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = from_ordered(~box[d]);
+        hi[d] = from_ordered(box[3 + d]);
     }
+    write_cube(lo, hi, box[6] != 0ull, cube);
 }
 
 __device__ __forceinline__ uint64_t spread3(uint32_t v) {
@@ -200,44 +219,68 @@ __device__ __forceinline__ uint64_t morton_key(const double* __restrict__ x, con
 }
 
 // Keys and input indices; a block takes per * TB consecutive particles.  part:
-// the partial boxes of a single set (a forest's cubes are in cubes already).
-// counts: the sort's digit totals, 8 passes of 256, counted here while the keys
-// are in registers (nullptr: the sort counts by itself).
+// the partial boxes of a single set; boxes: those of a forest's sets.  counts:
+// the sort's digit totals, 256 per pass, of the keys (counted here while they are
+// in registers) and of the set numbers.  With the set number as one more digit
+// of the particle sort, 16 sets of 8192 are sorted in 12 launches; sorting by key
+// and then by set, each with its own clearing and counting, took 17 and 45 us
+// more of a 684 us evaluation.
 __global__ __launch_bounds__(TB) void morton_kernel(const double* __restrict__ pos, int64_t n,
                                                     const double* __restrict__ part, int nparts,
+                                                    const unsigned long long* __restrict__ boxes,
                                                     double* __restrict__ cubes,
                                                     const int64_t* __restrict__ set_off, int n_sets, int per,
                                                     uint64_t* __restrict__ keys, int32_t* __restrict__ idx,
                                                     uint32_t* __restrict__ counts) {
     __shared__ double cube0[9];
-    __shared__ uint32_t h[8][256];
+    __shared__ uint32_t h[kKeyPasses][256];
     static_assert(TB == 256, "a thread per digit");
-    if (n_sets <= 1) cube_of_parts(part, nparts, cubes, cube0);
-    if (counts) {
-#pragma unroll
-        for (int p = 0; p < 8; ++p) h[p][threadIdx.x] = 0u;
-        __syncthreads();
-    }
     const int64_t a0 = (int64_t)blockIdx.x * per * TB + threadIdx.x;
+    // the block's only set, or -1
+    int mine = 0;
+    if (n_sets <= 1) {
+        cube_of_parts(part, nparts, cubes, cube0);
+    } else {
+        const int64_t b0 = (int64_t)blockIdx.x * per * TB, b1 = b0 + (int64_t)per * TB;
+        mine = set_of(set_off, n_sets, b0);
+        if (mine != set_of(set_off, n_sets, b1 < n ? b1 - 1 : n - 1)) mine = -1;
+        if (mine >= 0 && threadIdx.x == 0) cube_of_box(boxes + 8 * (int64_t)mine, cube0);
+        if (blockIdx.x == 0) {
+            for (int k = threadIdx.x; k < n_sets; k += TB) {
+                const uint32_t size = (uint32_t)(set_off[k + 1] - set_off[k]);
+                atomicAdd(&counts[kKeyPasses * 256 + (k & 255)], size);
+                if (n_sets > 256) atomicAdd(&counts[(kKeyPasses + 1) * 256 + (k >> 8)], size);
+                double c[9];
+                cube_of_box(boxes + 8 * (int64_t)k, c);
+#pragma unroll
+                for (int d = 0; d < 9; ++d) cubes[16 * (int64_t)k + d] = c[d];
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < kKeyPasses; ++p) h[p][threadIdx.x] = 0u;
+    __syncthreads();
     for (int k = 0; k < per; ++k) {
         const int64_t a = a0 + (int64_t)k * TB;
         if (a >= n) break;
-        const double* cube = n_sets <= 1 ? cube0 : cubes + 16 * (int64_t)set_of(set_off, n_sets, a);
-        const uint64_t key = morton_key(pos + 3 * a, cube);
+        uint64_t key;
+        if (mine >= 0) {
+            key = morton_key(pos + 3 * a, cube0);
+        } else {
+            double c[9];
+            cube_of_box(boxes + 8 * (int64_t)set_of(set_off, n_sets, a), c);
+            key = morton_key(pos + 3 * a, c);
+        }
         keys[a] = key;
         idx[a] = (int32_t)a;
-        if (counts) {
 #pragma unroll
-            for (int p = 0; p < 8; ++p) atomicAdd(&h[p][(uint32_t)(key >> (8 * p)) & 255u], 1u);
-        }
+        for (int p = 0; p < kKeyPasses; ++p) atomicAdd(&h[p][(uint32_t)(key >> (8 * p)) & 255u], 1u);
     }
-    if (counts) {
-        __syncthreads();
+    __syncthreads();
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const uint32_t c = h[p][threadIdx.x];
-            if (c) atomicAdd(&counts[p * 256 + threadIdx.x], c);
-        }
+    for (int p = 0; p < kKeyPasses; ++p) {
+        const uint32_t c = h[p][threadIdx.x];
+        if (c) atomicAdd(&counts[p * 256 + threadIdx.x], c);
     }
 }
 
@@ -396,26 +439,6 @@ __global__ __launch_bounds__(ST) void small_sort_kernel(const double* __restrict
 // Forest: after the sort by key, a stable sort by set puts every set's
 // particles in its own range in key order.  skey = set of each sorted
 // particle, spos = its position; then the keys and the order follow spos.
-__global__ __launch_bounds__(TB) void set_keys_kernel(const int32_t* __restrict__ perm, int64_t n,
-                                                      const int64_t* __restrict__ set_off, int n_sets,
-                                                      uint32_t* __restrict__ skey, int32_t* __restrict__ spos) {
-    const int64_t j = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (j >= n) return;
-    skey[j] = (uint32_t)set_of(set_off, n_sets, perm[j]);
-    spos[j] = (int32_t)j;
-}
-
-__global__ __launch_bounds__(TB) void set_apply_kernel(const int32_t* __restrict__ spos, int64_t n,
-                                                       const uint64_t* __restrict__ keys,
-                                                       const int32_t* __restrict__ perm,
-                                                       uint64_t* __restrict__ keys_out, int32_t* __restrict__ perm_out) {
-    const int64_t j = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (j >= n) return;
-    const int32_t q = spos[j];
-    keys_out[j] = keys[q];
-    perm_out[j] = perm[q];
-}
-
 // Sorted FP64 particles and the level at which a key boundary appears in front
 // of each sorted position (22 = equal keys, never a boundary; 0 = the first
 // particle of a set, where its root starts).
@@ -937,7 +960,12 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     const int64_t* soff = ns > 1 ? t.set_off.as<int64_t>() : nullptr;
     const int64_t nblk = cdiv(n, TB);
     const int nbb = (int)std::min<int64_t>(256, nblk);
-    t.scratch.ensure(ctx, std::max<size_t>(sort_scratch_bytes(n, 3 * kLevels) + 256, scan_scratch_bytes(n) + 256));
+    const int passes = kKeyPasses + set_passes(ns);
+    int64_t sort_words = 0;
+    sort_counts(nullptr, n, passes, &sort_words);
+    // the sort's scratch, then the boxes of a forest's sets
+    const int64_t box_words = ns > 1 ? 8 * (int64_t)ns : 0;
+    t.scratch.ensure(ctx, (size_t)(sort_words + box_words) * 8 + 512);
     // the key cubes, then the partial boxes of a single set
     t.cube.ensure(ctx, (size_t)(ns * 16 + nbb * 7) * sizeof(double));
     double* cube = t.cube.as<double>();
@@ -972,50 +1000,28 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     } else {
         t.keys2.ensure(ctx, un * 8);
         t.perm2.ensure(ctx, un * 4);
-        int64_t words = 0;
-        uint32_t* counts = sort_counts(t.scratch.p, n, 3 * kLevels, &words);
+        uint32_t* counts = sort_counts(t.scratch.p, n, passes, &sort_words);
+        unsigned long long* boxes = t.scratch.as<unsigned long long>() + sort_words;
         if (ns > 1) {
-            counts = nullptr;
-            hipLaunchKernelGGL(bbox_sets_kernel, dim3((unsigned)ns), dim3(TB), 0, s, pos, soff, cube);
+            sort_clear(t.scratch.p, sort_words + box_words, s);
+            hipLaunchKernelGGL(bbox_sets_kernel, dim3((unsigned)cdiv(n, (int64_t)kBoxRun * (TB / kWave))), dim3(TB), 0,
+                               s, pos, n, soff, ns, boxes);
         } else {
             hipLaunchKernelGGL(bbox_partial_kernel, dim3(nbb), dim3(TB), 0, s, pos, n, part,
-                               t.scratch.as<unsigned long long>(), words);
+                               t.scratch.as<unsigned long long>(), sort_words);
         }
         TFMM_LAUNCHED();
         // blocks of 1024 particles, of 4096 when there are many (a block adds up
-        // to 2048 digit totals)
-        const int per = !counts ? 1 : (n < (1 << 19) ? 4 : 16);
+        // to 2048 digit totals); an odd number of sort passes starts from the
+        // other arrays
+        const int per = n < (1 << 19) ? 4 : 16;
+        const bool odd = passes & 1;
         hipLaunchKernelGGL(morton_kernel, dim3((unsigned)cdiv(n, (int64_t)per * TB)), dim3(TB), 0, s, pos, n,
-                           (const double*)part, nbb, cube, soff, ns, per, t.keys.as<uint64_t>(),
-                           t.perm.as<int32_t>(), counts);
+                           (const double*)part, nbb, (const unsigned long long*)boxes, cube, soff, ns, per,
+                           (odd ? t.keys2 : t.keys).as<uint64_t>(), (odd ? t.perm2 : t.perm).as<int32_t>(), counts);
         TFMM_LAUNCHED();
-        if (counts)
-            radix_sort_u64_counted(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(),
-                                   t.perm2.as<int32_t>(), n, 3 * kLevels, t.scratch.p, ctx->dev_err, s);
-        else
-            radix_sort_u64(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(),
-                           t.perm2.as<int32_t>(), n, 3 * kLevels, t.scratch.p, ctx->dev_err, s);
-        if (ns > 1) {
-            int bits = 1;
-            while ((1 << bits) < ns) ++bits;
-            t.set_sort.ensure(ctx, un * 16);
-            uint32_t* skey = t.set_sort.as<uint32_t>();
-            int32_t* spos = reinterpret_cast<int32_t*>(skey + n);
-            uint32_t* skey2 = skey + 2 * n;
-            int32_t* spos2 = reinterpret_cast<int32_t*>(skey + 3 * n);
-            hipLaunchKernelGGL(set_keys_kernel, dim3(grid(n)), dim3(TB), 0, s, (const int32_t*)t.perm.as<int32_t>(),
-                               n, soff, ns, skey, spos);
-            TFMM_LAUNCHED();
-            radix_sort_u32(skey, spos, skey2, spos2, n, bits, t.scratch.p, ctx->dev_err, s);
-            hipLaunchKernelGGL(set_apply_kernel, dim3(grid(n)), dim3(TB), 0, s, (const int32_t*)spos, n,
-                               (const uint64_t*)t.keys.as<uint64_t>(), (const int32_t*)t.perm.as<int32_t>(),
-                               t.keys2.as<uint64_t>(), t.perm2.as<int32_t>());
-            TFMM_LAUNCHED();
-            std::swap(t.keys.p, t.keys2.p);
-            std::swap(t.keys.cap, t.keys2.cap);
-            std::swap(t.perm.p, t.perm2.p);
-            std::swap(t.perm.cap, t.perm2.cap);
-        }
+        radix_sort_particles(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(),
+                             t.perm2.as<int32_t>(), n, soff, ns, t.scratch.p, ctx->dev_err, s);
         hipLaunchKernelGGL(gather_kernel, dim3(grid(n)), dim3(TB), 0, s, pos, mass, t.keys.as<uint64_t>(),
                            t.perm.as<int32_t>(), n, soff, ns, t.Xm.as<double4>(), t.lvlb.as<uint8_t>());
         TFMM_LAUNCHED();
