@@ -227,6 +227,7 @@ struct Tree {
     DevBuf nd_rmax;            // double
     DevBuf leaves;             // int32 node ids of the leaves
     DevBuf rmax_items;         // int2 (node, chunk) work items of the r_max pass
+    DevBuf balls;              // double4 per 64 sorted particles: centre, radius
 
     // walk and per-target interaction lists
     bool walk_valid = false;

@@ -284,6 +284,36 @@ __global__ __launch_bounds__(TB) void morton_kernel(const double* __restrict__ p
     }
 }
 
+__device__ __forceinline__ double dist2(const double4& x, double cx, double cy, double cz) {
+    const double dx = x.x - cx, dy = x.y - cy, dz = x.z - cz;
+    return (dx * dx + dy * dy) + dz * dz;
+}
+
+// Maximum over each row of 16 lanes or over the wavefront, in every lane.
+template <int LANES>
+__device__ __forceinline__ double group_max(double v) {
+    static_assert(LANES == 16 || LANES == kWave, "a row or a wavefront");
+    auto up = [&](double u) { v = u > v ? u : v; };
+    up(dpp<0xB1>(v));   // quad_perm [1,0,3,2]
+    up(dpp<0x4E>(v));   // quad_perm [2,3,0,1]
+    up(dpp<0x141>(v));  // row_half_mirror
+    up(dpp<0x140>(v));  // row_mirror
+    if (LANES == kWave) {
+        up(__shfl_xor(v, 16, kWave));
+        up(__shfl_xor(v, 32, kWave));
+    }
+    return v;
+}
+
+// A ball around one of the wavefront's particles (lane j of the first m lanes
+// holds one) that holds them all.
+__device__ __forceinline__ double4 ball_of(const double4& x, int m) {
+    const int mid = m > kWave / 2 ? kWave / 2 : 0;
+    const double cx = __shfl(x.x, mid, kWave), cy = __shfl(x.y, mid, kWave), cz = __shfl(x.z, mid, kWave);
+    const double r2 = (int)(threadIdx.x & (kWave - 1)) < m ? dist2(x, cx, cy, cz) : 0.0;
+    return make_double4(cx, cy, cz, sqrt(group_max<kWave>(r2)));
+}
+
 // Level at which a key boundary appears between two sorted neighbours (22 =
 // equal keys, never a boundary).
 __device__ __forceinline__ uint8_t boundary_level(uint64_t a, uint64_t b) {
@@ -306,7 +336,7 @@ __global__ __launch_bounds__(ST) void small_sort_kernel(const double* __restrict
                                                         const double* __restrict__ mass, int n,
                                                         double* __restrict__ cube_out, uint64_t* __restrict__ keys,
                                                         int32_t* __restrict__ perm, double4* __restrict__ Xm,
-                                                        uint8_t* __restrict__ lvlb) {
+                                                        double4* __restrict__ balls, uint8_t* __restrict__ lvlb) {
     constexpr int NW = ST / kWave;
     __shared__ uint64_t sk[KPL * ST];
     __shared__ uint16_t sv[KPL * ST];
@@ -426,32 +456,46 @@ __global__ __launch_bounds__(ST) void small_sort_kernel(const double* __restrict
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
         const int j = base + r * kWave;
+        double4 x = make_double4(0.0, 0.0, 0.0, 0.0);
         if (j < n) {
             const int a = id[r];
             keys[j] = k[r];
             perm[j] = a;
-            Xm[j] = make_double4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], mass[a]);
+            x = make_double4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], mass[a]);
+            Xm[j] = x;
             lvlb[j] = j > 0 ? boundary_level(sk[j - 1], k[r]) : (uint8_t)0;
+        }
+        const int w0 = j - lane;
+        if (w0 < n) {
+            const double4 ball = ball_of(x, n - w0 < kWave ? n - w0 : kWave);
+            if (lane == 0) balls[w0 / kWave] = ball;
         }
     }
 }
 
-// Forest: after the sort by key, a stable sort by set puts every set's
-// particles in its own range in key order.  skey = set of each sorted
-// particle, spos = its position; then the keys and the order follow spos.
 // Sorted FP64 particles and the level at which a key boundary appears in front
 // of each sorted position (22 = equal keys, never a boundary; 0 = the first
-// particle of a set, where its root starts).
+// particle of a set, where its root starts).  A wavefront's 64 particles also get
+// a ball around one of them that holds them all (for r_max).
 __global__ __launch_bounds__(TB) void gather_kernel(const double* __restrict__ pos,
                                                     const double* __restrict__ mass,
                                                     const uint64_t* __restrict__ keys,
                                                     const int32_t* __restrict__ perm, int64_t n,
                                                     const int64_t* __restrict__ set_off, int n_sets,
-                                                    double4* __restrict__ Xm, uint8_t* __restrict__ lvlb) {
+                                                    double4* __restrict__ Xm, double4* __restrict__ balls,
+                                                    uint8_t* __restrict__ lvlb) {
     const int64_t j = (int64_t)blockIdx.x * TB + threadIdx.x;
+    const int64_t w0 = j & ~(int64_t)(kWave - 1);
+    if (w0 >= n) return;
+    double4 x = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (j < n) {
+        const int64_t a = perm[j];
+        x = make_double4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], mass[a]);
+        Xm[j] = x;
+    }
+    const double4 ball = ball_of(x, n - w0 < kWave ? (int)(n - w0) : kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) balls[w0 / kWave] = ball;
     if (j >= n) return;
-    const int64_t a = perm[j];
-    Xm[j] = make_double4(pos[3 * a], pos[3 * a + 1], pos[3 * a + 2], mass[a]);
     uint8_t lb = 0;
     if (j > 0 && (n_sets <= 1 || set_off[set_of(set_off, n_sets, j)] != j)) lb = boundary_level(keys[j - 1], keys[j]);
     lvlb[j] = lb;
@@ -801,13 +845,21 @@ __global__ __launch_bounds__(TB) void geometry_top_kernel(const int32_t* __restr
 // Exact r_max, the maximum squared distance of a node's particles from its
 // centre of mass, and the walk's packed record of the node: geo = (centre of
 // mass, r_max), top = (child count + 16 x the siblings from this node to its
-// last, level, first child, set).  One wavefront per node; nodes of more than
-// RCH particles are cut into chunks of RCH, listed in items (in any order: the
-// chunks' maxima meet in an atomicMax on the bits of the non-negative double),
-// and finished by rmax_large_kernel and rmax_final_kernel.  Three launches (one
-// up to RCH particles) where a list of all (node, chunk) items took seven and
-// the walk's records one more.
-constexpr int RCH = 4096;
+// last, level, first child, set).  A row of 16 lanes per node; nodes of more
+// than kBallsFrom particles are listed (in any order) as items of up to RCH
+// particles, which a wavefront each takes through the balls of the sorted
+// particles.  The items of a node of more than RCH meet in an atomicMax on the
+// bits of the non-negative double, and rmax_final_kernel finishes it.  Sets of up
+// to RCH particles take a wavefront per node and that launch only.
+//
+// Bound by latency, a node being a chain of dependent loads, and on 2^22
+// particles by the reads.  With a wavefront for every node and all distances
+// looked at, the three launches took 44 us on 100000 particles, 67 on 2^20 and
+// 219 on 2^22; now 27, 47 and 120.  Items from 200 particles cost 27, 52 and 126
+// us, from 800 27, 48 and 125; rows of 16 lanes for nodes of any size 64, 116
+// and 157.
+constexpr int RCH = 4096;          // particles of an item: one ball per lane
+constexpr int kBallsFrom = 512;
 
 struct NodePack {
     const int64_t* set_off;
@@ -828,63 +880,117 @@ __device__ __forceinline__ void pack_node(const NodeArrays& nd, const NodePack& 
                           set_of(pk.set_off, pk.n_sets, nd.first[i]));
 }
 
+template <int LANES>
 __device__ __forceinline__ double max_r2(const double4* __restrict__ Xm, int32_t s0, int32_t s1, const double4& z) {
-    const int lane = threadIdx.x & (kWave - 1);
     double m = 0.0;
-    for (int32_t s = s0 + lane; s < s1; s += kWave) {
-        const double4 x = Xm[s];
-        const double dx = x.x - z.x, dy = x.y - z.y, dz = x.z - z.z;
-        const double d2 = (dx * dx + dy * dy) + dz * dz;
+#pragma unroll 4
+    for (int32_t s = s0 + (int32_t)(threadIdx.x & (LANES - 1)); s < s1; s += LANES) {
+        const double d2 = dist2(Xm[s], z.x, z.y, z.z);
         m = d2 > m ? d2 : m;
     }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const double u = __shfl_xor(m, o, kWave);
-        m = u > m ? u : m;
-    }
-    return m;
+    return group_max<LANES>(m);
 }
 
+// The same for up to RCH particles through the balls of the 64-particle groups:
+// a group's distances are looked at only if its ball reaches beyond the largest
+// of the farthest reaching group.  The factor and the last term cover the
+// rounding of the bound (the term where squares underflow), so the maximum is
+// exactly max_r2's.  best: a value known not to exceed it, or 0.
+__device__ __forceinline__ double max_r2_balls(const double4* __restrict__ Xm, const double4* __restrict__ balls,
+                                               int32_t s0, int32_t s1, const double4& z, double best) {
+    constexpr int U = 4;  // groups in flight
+    const int lane = threadIdx.x & (kWave - 1);
+    auto group = [&](int32_t b) {
+        const int32_t s = b * kWave + lane;
+        return s >= s0 && s < s1 ? dist2(Xm[s], z.x, z.y, z.z) : 0.0;
+    };
+    const int32_t last = (s1 - 1) / kWave;
+    for (int32_t b0 = s0 / kWave; b0 <= last; b0 += kWave) {  // one round, two if s0 is inside a group
+        double reach = -1.0;
+        if (b0 + lane <= last) {
+            const double4 c = balls[b0 + lane];
+            const double u = sqrt(dist2(c, z.x, z.y, z.z)) + c.w;
+            reach = u * u * (1.0 + 1e-12) + 1e-290;
+        }
+        const double top = group_max<kWave>(reach);
+        if (!(top > best)) continue;
+        const int k = __ffsll((unsigned long long)__ballot(reach == top)) - 1;
+        const double m = group_max<kWave>(group(b0 + k));
+        best = m > best ? m : best;
+        uint64_t todo = __ballot(reach > best) & ~(1ull << k);
+        double far = 0.0;
+        while (todo != 0ull) {
+            double d[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int g = todo != 0ull ? __ffsll((unsigned long long)todo) - 1 : k;
+                todo &= todo - 1ull;
+                d[q] = group(b0 + g);
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) far = d[q] > far ? d[q] : far;
+        }
+        far = group_max<kWave>(far);
+        best = far > best ? far : best;
+    }
+    return best;
+}
+
+template <int LANES>
 __global__ __launch_bounds__(TB) void rmax_kernel(NodeArrays nd, int64_t nn, const double4* __restrict__ Xm,
-                                                  const double4* __restrict__ Z, NodePack pk,
+                                                  const double4* __restrict__ Z, NodePack pk, int32_t item_from,
                                                   unsigned long long* __restrict__ r2bits, int2* __restrict__ items,
                                                   uint32_t* __restrict__ n_items) {
-    const int64_t i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (TB / kWave) + threadIdx.x / kWave));
+    // room for the block's items in one step
+    __shared__ uint32_t mine, at0;
+    if (threadIdx.x == 0) mine = 0u;
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * (TB / LANES) + threadIdx.x / LANES;
+    const int lane = threadIdx.x & (LANES - 1);
+    const int32_t s0 = i < nn ? nd.first[i] : 0, cnt = i < nn ? nd.count[i] : 0;
+    const bool listed = cnt > item_from;
+    const int nc = (cnt + RCH - 1) / RCH;
+    uint32_t at = 0u;
+    if (listed && lane == 0) {
+        r2bits[i] = 0ull;
+        at = atomicAdd(&mine, (uint32_t)nc);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && mine != 0u) at0 = atomicAdd(n_items, mine);
+    __syncthreads();
     if (i >= nn) return;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int32_t s0 = nd.first[i], cnt = nd.count[i];
-    if (cnt > RCH) {
-        const int nc = (cnt + RCH - 1) / RCH;
-        uint32_t at = 0;
-        if (lane == 0) {
-            r2bits[i] = 0ull;
-            at = atomicAdd(n_items, (uint32_t)nc);
-        }
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-        for (int k = lane; k < nc; k += kWave) items[at + k] = make_int2((int32_t)i, k);
+    if (listed) {
+        at = at0 + (uint32_t)__shfl((int)at, 0, LANES);
+        for (int k = lane; k < nc; k += LANES) items[at + k] = make_int2((int32_t)i, k);
         return;
     }
     const double4 z = Z[i];
-    const double m = max_r2(Xm, s0, s0 + cnt, z);
+    const double m = max_r2<LANES>(Xm, s0, s0 + cnt, z);
     if (lane == 0) pack_node(nd, pk, (int32_t)i, z, m);
 }
-
-__global__ __launch_bounds__(kWave) void rmax_large_kernel(const uint32_t* __restrict__ n_items,
-                                                           const int2* __restrict__ items,
-                                                           const int32_t* __restrict__ first,
-                                                           const int32_t* __restrict__ count,
-                                                           const double4* __restrict__ Xm,
-                                                           const double4* __restrict__ Z,
-                                                           unsigned long long* __restrict__ r2bits) {
-    if (blockIdx.x >= *n_items) return;
-    const int2 it = items[blockIdx.x];
-    const int32_t s0 = first[it.x] + it.y * RCH;
-    const int32_t e = first[it.x] + count[it.x];
-    const double4 z = Z[it.x];
-    const double m = max_r2(Xm, s0, (s0 + RCH < e) ? s0 + RCH : e, z);
-    if (threadIdx.x == 0) atomicMax(&r2bits[it.x], (unsigned long long)__double_as_longlong(m));
+__global__ __launch_bounds__(TB) void rmax_items_kernel(const uint32_t* __restrict__ n_items,
+                                                        const int2* __restrict__ items, NodeArrays nd,
+                                                        const double4* __restrict__ Xm,
+                                                        const double4* __restrict__ balls,
+                                                        const double4* __restrict__ Z, NodePack pk,
+                                                        unsigned long long* __restrict__ r2bits) {
+    const uint32_t ni = *n_items;
+    for (uint32_t q = blockIdx.x * (TB / kWave) + threadIdx.x / kWave; q < ni; q += gridDim.x * (TB / kWave)) {
+        const int2 it = items[q];
+        const int32_t i = it.x, cnt = nd.count[i];
+        const int32_t s0 = nd.first[i] + it.y * RCH, e = nd.first[i] + cnt;
+        const double4 z = Z[i];
+        const bool whole = cnt <= RCH;
+        const double best = whole ? 0.0
+                                  : __longlong_as_double((long long)__hip_atomic_load(&r2bits[i], __ATOMIC_RELAXED,
+                                                                                      __HIP_MEMORY_SCOPE_AGENT));
+        const double m = max_r2_balls(Xm, balls, s0, s0 + RCH < e ? s0 + RCH : e, z, best);
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+            if (whole) pack_node(nd, pk, i, z, m);
+            else if (m > best) atomicMax(&r2bits[i], (unsigned long long)__double_as_longlong(m));
+        }
+    }
 }
-
 __global__ __launch_bounds__(TB) void rmax_final_kernel(const uint32_t* __restrict__ n_items,
                                                         const int2* __restrict__ items, NodeArrays nd,
                                                         const double4* __restrict__ Z, NodePack pk,
@@ -892,7 +998,7 @@ __global__ __launch_bounds__(TB) void rmax_final_kernel(const uint32_t* __restri
     const uint32_t ni = *n_items;
     for (uint32_t k = blockIdx.x * TB + threadIdx.x; k < ni; k += gridDim.x * TB) {
         const int2 it = items[k];
-        if (it.y == 0) pack_node(nd, pk, it.x, Z[it.x], __longlong_as_double((long long)r2bits[it.x]));
+        if (it.y == 0 && nd.count[it.x] > RCH) pack_node(nd, pk, it.x, Z[it.x], __longlong_as_double((long long)r2bits[it.x]));
     }
 }
 
@@ -974,6 +1080,7 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     t.perm.ensure(ctx, un * 4);
     t.Xm.ensure(ctx, un * 32);
     t.lvlb.ensure(ctx, un);
+    t.balls.ensure(ctx, (size_t)cdiv(n, kWave) * 32);
     t.owner.ensure(ctx, un);
     t.leaf_of.ensure(ctx, un * 4);
     // header, a counter of finished blocks, the count of r_max items
@@ -991,7 +1098,8 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     if (ns == 1 && n <= kSmallSort) {
         auto run = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(1), dim3(ST), 0, s, pos, mass, (int)n, cube, t.keys.as<uint64_t>(),
-                               t.perm.as<int32_t>(), t.Xm.as<double4>(), t.lvlb.as<uint8_t>());
+                               t.perm.as<int32_t>(), t.Xm.as<double4>(), t.balls.as<double4>(),
+                               t.lvlb.as<uint8_t>());
             TFMM_LAUNCHED();
         };
         if (n <= 2 * ST) run(small_sort_kernel<2>);
@@ -1023,7 +1131,8 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
         radix_sort_particles(t.keys.as<uint64_t>(), t.perm.as<int32_t>(), t.keys2.as<uint64_t>(),
                              t.perm2.as<int32_t>(), n, soff, ns, t.scratch.p, ctx->dev_err, s);
         hipLaunchKernelGGL(gather_kernel, dim3(grid(n)), dim3(TB), 0, s, pos, mass, t.keys.as<uint64_t>(),
-                           t.perm.as<int32_t>(), n, soff, ns, t.Xm.as<double4>(), t.lvlb.as<uint8_t>());
+                           t.perm.as<int32_t>(), n, soff, ns, t.Xm.as<double4>(), t.balls.as<double4>(),
+                           t.lvlb.as<uint8_t>());
         TFMM_LAUNCHED();
     }
 
@@ -1086,18 +1195,23 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     t.w_geo.ensure(ctx, (size_t)nn * sizeof(double4));
     t.w_top.ensure(ctx, (size_t)nn * sizeof(int4));
     t.nd_r2bits.ensure(ctx, (size_t)nn * 8);
-    // chunks of large nodes: every level's hold each particle at most once
-    const int64_t ub = n > RCH ? 2 * (n * (t.max_level + 1) / RCH) + 1 : 0;
-    t.rmax_items.ensure(ctx, (size_t)std::max<int64_t>(ub, 1) * 8);
+    const double4* balls = t.balls.as<double4>();
+    const int32_t item_from = n > RCH ? kBallsFrom : RCH;
+    // every level holds each particle at most once
+    const int64_t ub = n > RCH ? (t.max_level + 1) * (n / kBallsFrom + n / RCH) + 1 : 0;
+    t.rmax_items.ensure(ctx, (size_t)std::max<int64_t>(std::min(ub, nn + (t.max_level + 1) * (n / RCH)), 1) * 8);
     const NodePack pk{soff, ns, t.nd_rmax.as<double>(), t.w_geo.as<double4>(), t.w_top.as<int4>()};
-    hipLaunchKernelGGL(rmax_kernel, dim3((unsigned)cdiv(nn, TB / kWave)), dim3(TB), 0, s, nd, nn,
-                       (const double4*)t.Xm.as<double4>(), (const double4*)t.nd_Z.as<double4>(), pk,
+    const bool rows = n > RCH;
+    hipLaunchKernelGGL((rows ? rmax_kernel<16> : rmax_kernel<kWave>),
+                       dim3((unsigned)cdiv(nn, TB / (rows ? 16 : kWave))), dim3(TB), 0, s, nd, nn,
+                       (const double4*)t.Xm.as<double4>(), (const double4*)t.nd_Z.as<double4>(), pk, item_from,
                        t.nd_r2bits.as<unsigned long long>(), t.rmax_items.as<int2>(), n_items);
     TFMM_LAUNCHED();
     if (ub > 0) {
-        hipLaunchKernelGGL(rmax_large_kernel, dim3((unsigned)ub), dim3(kWave), 0, s, (const uint32_t*)n_items,
-                           (const int2*)t.rmax_items.as<int2>(), nd.first, nd.count, t.Xm.as<double4>(),
-                           t.nd_Z.as<double4>(), t.nd_r2bits.as<unsigned long long>());
+        hipLaunchKernelGGL(rmax_items_kernel, dim3((unsigned)std::min<int64_t>(2048, cdiv(ub, TB / kWave))), dim3(TB), 0,
+                           s, (const uint32_t*)n_items, (const int2*)t.rmax_items.as<int2>(), nd,
+                           (const double4*)t.Xm.as<double4>(), balls, (const double4*)t.nd_Z.as<double4>(), pk,
+                           t.nd_r2bits.as<unsigned long long>());
         TFMM_LAUNCHED();
         hipLaunchKernelGGL(rmax_final_kernel, dim3((unsigned)std::min<int64_t>(64, cdiv(ub, TB))), dim3(TB), 0, s,
                            (const uint32_t*)n_items, (const int2*)t.rmax_items.as<int2>(), nd,
