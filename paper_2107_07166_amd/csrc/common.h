@@ -240,6 +240,7 @@ struct Tree {
     uint32_t list_mb = 0;         // read-back of the list totals under way (0: none)
     DevBuf w_fr, w_fr2, w_off, w_tg, w_fl, w_c;  // walk and list-building scratch
     DevBuf w_state, w_res, w_dec; // device-side walk counters, list totals, pair decisions
+    DevBuf w_sync;             // walk passes: tickets and counts of their workgroups
     DevBuf w_geo, w_top;          // per node, packed for the walk (COM + r_max; children, level)
     // sizes seen by the previous walk of this tree (capacity hints for the
     // passes that run without host synchronisation; 0 = none yet)

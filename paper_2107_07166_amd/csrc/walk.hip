@@ -203,6 +203,18 @@ struct WalkOut {
 };
 constexpr int kWalkGrid = 1024;
 
+constexpr int kPassGrid = 256;  // most workgroups of a pass in one launch
+
+// What the workgroups of a pass tell each other, per slot (a pass uses its own
+// and clears the other's): start tickets, and the output counts of every
+// workgroup in one word (20 bits each of next, far and near; bit 63 set, bit 62
+// if a count does not fit).
+constexpr int kCountBits = 20;
+struct PassSync {
+    unsigned long long counts[2][kPassGrid];
+    uint32_t ticket[2];
+};
+
 // Whether a pass's totals T fit.
 __device__ __forceinline__ bool pass_fits(const WalkOut& o, const U3L& T, const WalkSlot& s) {
     const unsigned long long lim = 0xffffffffull;
@@ -222,21 +234,27 @@ __device__ __forceinline__ void pass_done(WalkState* st, WalkSlot* out, const Wa
 // between.  The frontier stays in LDS (and is written to memory too, for the
 // launch that takes over).  With init, starts from the pairs (k, k) of the
 // roots.  Stops when the frontier is empty or larger than limit.  A pass here
-// takes 5 to 9 us (latency: one workgroup cannot hide it), two launches of
-// their own 12 us and the gaps between them.  A small tree's walk is this one
+// takes 5 to 9 us (latency: one workgroup cannot hide it), a launch of its own
+// 6 to 9 and the gap before it.  A small tree's walk is this one
 // launch: Plummer 10007, built and solved in one call, 1070 -> 711 us together
 // with the estimated room of a first walk.
 constexpr int SQ = 1024;          // threads
 constexpr int kSeqMax = 2048;     // most entries of a pass run here
-constexpr int kSeqHead = 1024;    // the walk's first passes go on here up to this
+constexpr int kSeqHead = 1024;    // a walk whose passes stay below this is run here whole
+// The first and last passes of a walk with larger ones (100000 particles 734 us
+// with 1024, 719 with 256; 20011 in FP64 557 and 552).
+constexpr int kSeqEnds = 256;
 __global__ __launch_bounds__(SQ) void walk_seq_kernel(WalkNodes w, WalkOut o, WalkState* __restrict__ st, int slot,
-                                                      int init, int n_roots, uint32_t limit, double theta, Mailbox mb) {
+                                                      int init, int n_roots, uint32_t limit, double theta,
+                                                      PassSync* __restrict__ sync, Mailbox mb) {
     constexpr int NW = SQ / kWave;
     constexpr int EPW = kWave / kRun;  // entries per wavefront and step
     __shared__ int2 fr[2][kSeqMax];
     __shared__ int8_t dec[kSeqMax * kRun];
     __shared__ U3 wtot[NW];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, x = lane % kRun;
+    for (int k = tid; k < kPassGrid; k += SQ) sync->counts[0][k] = sync->counts[1][k] = 0ull;
+    if (tid < 2) sync->ticket[tid] = 0u;
     WalkSlot s;
     if (init) {
         s = WalkSlot{(uint32_t)n_roots, 0u, 0ull, 0ull};
@@ -319,17 +337,171 @@ __global__ __launch_bounds__(SQ) void walk_seq_kernel(WalkNodes w, WalkOut o, Wa
     }
 }
 
-// Larger passes, two launches each.  The counting kernel decides every pair,
-// stores the decision and the block's output counts; the emitting kernel adds
-// the totals of the blocks before it and writes the outputs.  Block b of a
-// pass takes a contiguous range of tiles of TB / kRun entries, so the outputs
-// follow the frontier order whatever the grid.  Both are bound by the latency
-// of a tile's dependent reads: two tiles (the next tile, when writing) are in
-// flight per wavefront.  2^20 Plummer particles: the largest passes, 5e5
-// entries, take 18 and 24 us (with one pair per thread and frontier entry, all
-// pairs written and read back, 18 and 38), all passes 0.42 ms of kernels against
-// 0.54; steps 3.31 -> 3.13 ms.  Workgroups of 512 or 1024 threads, or 2048 of
-// them: 0-7 % slower steps.
+// Larger passes, one launch each.  Workgroup b (by its start ticket) takes a
+// contiguous range of entries, each of its wavefronts a contiguous part, so the
+// outputs follow the frontier order whatever the grid.  It decides its pairs
+// (the decisions and entries kept in LDS, or in memory when the frontier is much
+// larger than the grid was sized for), publishes its counts, adds up those of
+// the workgroups before it as they appear, and writes its outputs.  It waits only
+// for workgroups that have started; a wait past kSpinLimit polls sets the device
+// error word.
+//
+// Bound by latency: the entry, its five records, the counts before it, and then
+// the split nodes' records are read one after another.  On 2^20 Plummer particles
+// the 18 passes take 308 us; in two launches each, counting and emitting, with
+// the decisions through memory, 391 and the gaps between them (steps 3.20 -> 3.08
+// ms; 2^20, binary, 1498 -> 1450 us; 100000 particles 756 -> 719).
+constexpr int kPassLds = 4;          // entries per thread kept in LDS
+constexpr uint32_t kSpinLimit = 1u << 20;
+template <int PT>  // threads
+__global__ __launch_bounds__(PT) void walk_pass_kernel(WalkNodes w, WalkOut o, WalkState* __restrict__ st, int slot,
+                                                       double theta, int8_t* __restrict__ dec,
+                                                       PassSync* __restrict__ sync, uint32_t* __restrict__ err) {
+    constexpr int NW = PT / kWave, EPW = kWave / kRun, kPassEntries = kPassLds * PT;
+    __shared__ int2 ent[kPassEntries];
+    __shared__ int8_t code_of[kPassEntries * kRun];
+    __shared__ U3 wtot[NW], wbefore[NW];
+    __shared__ uint32_t s_b, s_bad;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave, x = lane % kRun;
+    if (tid == 0) {
+        s_b = atomicAdd(&sync->ticket[slot], 1u);
+        s_bad = 0u;
+    }
+    const WalkSlot s = st->slot[slot];
+    const uint32_t nf = st->overflow ? 0u : s.nf;
+    __syncthreads();
+    const uint32_t b = s_b, G = gridDim.x;
+    if (b >= G) return;  // a ticket too many: never, as every pass starts from cleared tickets
+    if (tid == 0) {
+        for (uint32_t j = b; j < (uint32_t)kPassGrid; j += G) sync->counts[slot ^ 1][j] = 0ull;
+        if (b == 0u) sync->ticket[slot ^ 1] = 0u;
+    }
+    if (nf == 0u) {
+        if (b == 0u && tid == 0) st->slot[slot ^ 1] = WalkSlot{0u, s.buf, s.n_far, s.n_near};
+        return;
+    }
+    const int64_t perb = ((int64_t)nf + (int64_t)G * EPW - 1) / ((int64_t)G * EPW) * EPW;
+    const int64_t b0 = (int64_t)b * perb < (int64_t)nf ? (int64_t)b * perb : (int64_t)nf;
+    const int64_t left = (int64_t)nf - b0;
+    const uint32_t n = (uint32_t)(left < perb ? left : perb);
+    const bool in_lds = perb <= kPassEntries;
+    const int2* fr = o.fr[s.buf] + b0;
+    int8_t* decided = dec + b0 * kRun;
+    const uint32_t pw = (n + NW * EPW - 1) / (NW * EPW) * EPW;
+    const uint32_t e0 = wv * pw < n ? wv * pw : n, e1 = e0 + pw < n ? e0 + pw : n;
+    U3 c{0u, 0u, 0u};
+    for (uint32_t k = e0; k < e1; k += 2 * EPW) {  // two steps' reads in flight
+        const uint32_t ea = k + lane / kRun, eb = ea + EPW;
+        const bool va = ea < e1, vb = eb < e1;
+        const int2 pa = fr[va ? ea : e0], pb = fr[vb ? eb : e0];
+        const PairRecords ra = load_pair(w, va, pa, x), rb = load_pair(w, vb, pb, x);
+        const int ca = decide(w, ra, x, theta), cb = decide(w, rb, x, theta);
+        if (in_lds) {
+            if (va) code_of[ea * kRun + x] = (int8_t)ca;
+            if (vb) code_of[eb * kRun + x] = (int8_t)cb;
+            if (va && x == 0) ent[ea] = pa;
+            if (vb && x == 0) ent[eb] = pb;
+        } else {
+            if (va) decided[(int64_t)ea * kRun + x] = (int8_t)ca;
+            if (vb) decided[(int64_t)eb * kRun + x] = (int8_t)cb;
+        }
+        U3 unused;
+        c = u3add(c, u3add(wave_counts(ca, ra.ta.x & 15, unused), wave_counts(cb, rb.ta.x & 15, unused)));
+    }
+    if (lane == 0) wtot[wv] = c;
+    __syncthreads();
+    U3 own{0u, 0u, 0u}, pre{0u, 0u, 0u};  // of the workgroup, of its wavefronts before this one
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        if (k < wv) pre = u3add(pre, wtot[k]);
+        own = u3add(own, wtot[k]);
+    }
+    constexpr unsigned long long kSet = 1ull << 63, kBad = 1ull << 62, kMask = (1ull << kCountBits) - 1ull;
+    unsigned long long* counts = sync->counts[slot];
+    bool bad = ((own.a | own.b | own.c) >> kCountBits) != 0u;
+    if (tid == 0)
+        __hip_atomic_store(&counts[b], kSet | (bad ? kBad : (unsigned long long)own.a |
+                                                               (unsigned long long)own.b << kCountBits |
+                                                               (unsigned long long)own.c << (2 * kCountBits)),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    U3 before{0u, 0u, 0u};
+    for (uint32_t j = tid; j < b; j += PT) {
+        unsigned long long v;
+        uint32_t spins = 0u;
+        while (((v = __hip_atomic_load(&counts[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kSet) == 0ull) {
+            if (++spins > kSpinLimit) {
+                atomicOr(err, 1u);
+                v = kBad;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        bad |= (v & kBad) != 0ull;
+        before = u3add(before, U3{(uint32_t)(v & kMask), (uint32_t)(v >> kCountBits & kMask),
+                                  (uint32_t)(v >> (2 * kCountBits) & kMask)});
+    }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1)
+        before = u3add(before, U3{(uint32_t)__shfl_xor((int)before.a, d, kWave),
+                                  (uint32_t)__shfl_xor((int)before.b, d, kWave),
+                                  (uint32_t)__shfl_xor((int)before.c, d, kWave)});
+    if (lane == 0) wbefore[wv] = before;
+    if (bad) s_bad = 1u;
+    __syncthreads();
+    before = wbefore[0];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) before = u3add(before, wbefore[k]);
+    // outputs up to this workgroup's: the last one's are the pass's totals
+    const U3L T{(unsigned long long)before.a + own.a, (unsigned long long)before.b + own.b,
+                (unsigned long long)before.c + own.c};
+    const bool fits = s_bad == 0u && pass_fits(o, T, s);
+    if (b == G - 1u && tid == 0) {
+        if (fits) {
+            pass_done(st, &st->slot[slot ^ 1], s, T);
+        } else {
+            st->overflow = 1u;
+            st->slot[slot ^ 1] = WalkSlot{0u, s.buf, s.n_far, s.n_near};
+        }
+    }
+    if (!fits) return;
+    int2* nxt = o.fr[s.buf ^ 1u];
+    auto sink = [&](unsigned long long i, int2 e) { nxt[i] = e; };
+    unsigned long long on = before.a + pre.a, of = s.n_far + before.b + pre.b, onr = s.n_near + before.c + pre.c;
+    // a step's split nodes are read while the step before is written
+    auto fetch = [&](uint32_t k, int2& pr, int& code) {
+        const uint32_t e = k + lane / kRun;
+        code = -1;
+        pr = make_int2(0, 0);
+        if (e < e1) {
+            code = in_lds ? code_of[e * kRun + x] : decided[(int64_t)e * kRun + x];
+            pr = in_lds ? ent[e] : fr[e];
+        }
+        return code >= 2 ? w.top[code == 7 ? pr.y : pr.x + x] : make_int4(0, 0, 0, 0);
+    };
+    int2 pr;
+    int code;
+    int4 ts = fetch(e0, pr, code);
+    for (uint32_t k = e0; k < e1; k += EPW) {
+        int2 pr_next;
+        int code_next;
+        const int4 ts_next = fetch(k + EPW, pr_next, code_next);
+        U3 lo;
+        const U3 q = wave_counts(code, ts.x & 15, lo);
+        lane_emit(code, pr.x + x, pr.y, ts, on + lo.a, of + lo.b, onr + lo.c, o.far, o.near, sink);
+        on += q.a;
+        of += q.b;
+        onr += q.c;
+        pr = pr_next;
+        code = code_next;
+        ts = ts_next;
+    }
+}
+
+// The same in two launches, between which the host sizes the outputs
+// (walk_bfs_sized): the counting kernel decides every pair, stores the decision
+// and the block's output counts; the emitting kernel adds the totals of the
+// blocks before it and writes the outputs.  Block b of a pass takes a contiguous
+// range of tiles of TB / kRun entries.
 __device__ __forceinline__ void block_tiles(uint32_t nf, int64_t& t0, int64_t& t1) {
     const int64_t tiles = ((int64_t)nf + TB / kRun - 1) / (TB / kRun);
     const int64_t per = (tiles + gridDim.x - 1) / gridDim.x;
@@ -454,7 +626,7 @@ WalkOut walk_out(Tree& t) {
 void launch_seq(Tree& t, const WalkNodes& w, int slot, bool init, int limit, double theta, const Mailbox& mb,
                 hipStream_t s) {
     hipLaunchKernelGGL(walk_seq_kernel, dim3(1), dim3(SQ), 0, s, w, walk_out(t), t.w_state.as<WalkState>(), slot,
-                       init ? 1 : 0, t.n_sets, (uint32_t)limit, theta, mb);
+                       init ? 1 : 0, t.n_sets, (uint32_t)limit, theta, t.w_sync.as<PassSync>(), mb);
     TFMM_LAUNCHED();
 }
 
@@ -464,17 +636,23 @@ WalkState wait_state(Tree& t, const Mailbox& mb, hipStream_t s) {
     return h;
 }
 
-// One pass in two launches, for a frontier of about expect entries (any grid
-// covers any frontier).
+// One pass, for a frontier of about expect entries (any grid covers any
+// frontier): smaller workgroups while there are few, so that more compute units
+// share the reads, and no more than 256, one per compute unit.  Passes of 500 to
+// 2000 entries take 6.4 to 7 us with 256 threads, 7 to 7.5 with 512 and 9 to 10
+// with 1024; of 15000 entries 11 to 15, 10 to 11 and 10.5 to 11; of 5e5 43, 37
+// and 33 (the workgroups' tickets and counts are in one another's way: 1024
+// workgroups take 24 us for any pass).
 void launch_pass(Tree& t, const WalkNodes& w, int slot, int64_t expect, double theta, hipStream_t s) {
-    const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kWalkGrid, cdiv(expect, TB / kRun)));
-    const WalkOut o = walk_out(t);
-    hipLaunchKernelGGL(walk_count_kernel, dim3(g), dim3(TB), 0, s, w, o, (const WalkState*)t.w_state.as<WalkState>(),
-                       slot, theta, t.w_dec.as<int8_t>(), t.w_off.as<U3L>());
-    TFMM_LAUNCHED();
-    hipLaunchKernelGGL(walk_emit_kernel, dim3(g), dim3(TB), 0, s, w, o, t.w_state.as<WalkState>(), slot,
-                       (const int8_t*)t.w_dec.as<int8_t>(), (const U3L*)t.w_off.as<U3L>());
-    TFMM_LAUNCHED();
+    auto run = [&](auto kern, int threads) {
+        const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kPassGrid, cdiv(expect, threads / kRun)));
+        hipLaunchKernelGGL(kern, dim3(g), dim3(threads), 0, s, w, walk_out(t), t.w_state.as<WalkState>(), slot, theta,
+                           t.w_dec.as<int8_t>(), t.w_sync.as<PassSync>(), t.ctx->dev_err);
+        TFMM_LAUNCHED();
+    };
+    if (expect <= 2048) run(walk_pass_kernel<256>, 256);
+    else if (expect <= 16384) run(walk_pass_kernel<512>, 512);
+    else run(walk_pass_kernel<1024>, 1024);
 }
 
 // Frontier passes sized on the host: the totals of every pass are read back
@@ -497,6 +675,7 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
     t.w_off.ensure(ctx, (size_t)kWalkGrid * sizeof(U3L));
     t.w_dec.ensure(ctx, (size_t)std::max(4096, t.n_sets) * kRun);
     t.w_state.ensure(ctx, sizeof(WalkState));
+    t.w_sync.ensure(ctx, sizeof(PassSync));
     t.scratch2.ensure(ctx, 256);
     WalkState* st = t.w_state.as<WalkState>();
     U3L* tot = t.scratch2.as<U3L>();
@@ -562,7 +741,7 @@ void first_room(const Tree& t, const std::vector<double>& theta, int64_t& fr, in
 
 // Frontier passes with no host synchronisation, sized from the previous walk
 // of this tree plus a quarter: the first passes, while they are small, in one
-// launch, then two launches per pass as many as that walk had larger ones, then
+// launch, then a launch per pass as many as that walk had larger ones, then
 // the last small passes in one launch.  The host reads the state back once; a
 // frontier that is left (the passes came out differently) gets more launches.
 // A tree's first walk reads the state back after the first launch too, and its
@@ -586,18 +765,19 @@ bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thet
     t.w_fr.ensure(ctx, (size_t)want_fr * 8);
     t.w_fr2.ensure(ctx, (size_t)want_fr * 8);
     t.w_dec.ensure(ctx, (size_t)want_fr * kRun);
-    t.w_off.ensure(ctx, (size_t)kWalkGrid * sizeof(U3L));
     t.m2l_pairs.ensure(ctx, (size_t)want_far * 8);
     t.p2p_pairs.ensure(ctx, (size_t)want_near * 8);
     t.w_state.ensure(ctx, sizeof(WalkState));
+    t.w_sync.ensure(ctx, sizeof(PassSync));
     int slot = 0;
-    // larger passes of the previous walk: from the first above kSeqHead to the last
+    // larger passes of the previous walk: from the first above the limit to the last
     int a = 0, b = (int)t.walk_hint_nf.size();
-    if (!known) b = 0;
-    while (a < b && t.walk_hint_nf[a] <= kSeqHead) ++a;
-    while (b > a && t.walk_hint_nf[b - 1] <= kSeqHead) --b;
+    if (!known || t.walk_hint_fr <= kSeqHead) b = 0;
+    const int limit = b > 0 ? kSeqEnds : kSeqHead;
+    while (a < b && t.walk_hint_nf[a] <= limit) ++a;
+    while (b > a && t.walk_hint_nf[b - 1] <= limit) --b;
     const Mailbox mb = mailbox_next(ctx);
-    launch_seq(t, w, slot ^ 1, true, kSeqHead, theta, b > a ? Mailbox{} : mb, s);
+    launch_seq(t, w, slot ^ 1, true, limit, theta, b > a ? Mailbox{} : mb, s);
     if (b > a) {
         for (int k = a; k < b; ++k, slot ^= 1)
             launch_pass(t, w, slot, t.walk_hint_nf[k] + t.walk_hint_nf[k] / 4 + 64, theta, s);
