@@ -553,12 +553,11 @@ int tfmm_leapfrog(tfmm_tree* tree, const tfmm_params* params, double* pos, doubl
             evaluate(t, params, nullptr, force, nullptr, s);
         }
         for (int k = 0; k < nsteps; ++k) {
-            run_kick(t.n, vel, force, mass, 0.5 * dt, s);
-            run_drift(t.n, pos, vel, dt, s);
+            run_kick_drift(t.n, pos, vel, force, mass, dt, k > 0, s);  // with the kick that ends step k - 1
             build_tree(t, pos, mass, s);
             evaluate(t, params, nullptr, force, nullptr, s);
-            run_kick(t.n, vel, force, mass, 0.5 * dt, s);
         }
+        if (nsteps > 0) run_kick(t.n, vel, force, mass, 0.5 * dt, s);
     });
 }
 

@@ -428,7 +428,8 @@ void run_diagnostics_noalloc(int64_t n, const double* pos, const double* vel, co
 // largest n of the allocation-free diagnostics (the library's particle limit)
 constexpr int64_t kNoAllocMaxN = (int64_t)1 << 30;
 void run_kick(int64_t n, double* vel, const double* force, const double* mass, double h, hipStream_t s);
-void run_drift(int64_t n, double* pos, const double* vel, double dt, hipStream_t s);
+void run_kick_drift(int64_t n, double* pos, double* vel, const double* force, const double* mass, double dt,
+                    bool both, hipStream_t s);
 
 // number of FP64 local values per node for a variant
 inline int n_local(int p, int variant) {

@@ -12,22 +12,42 @@ namespace {
 
 constexpr int KB = 256;
 
+__device__ __forceinline__ void kick(double* v, const double* __restrict__ force, int64_t i, double s) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) v[d] = fma(force[3 * i + d], s, v[d]);
+}
+
 __global__ __launch_bounds__(KB) void kick_kernel(int64_t n, double* __restrict__ vel,
                                                   const double* __restrict__ force,
                                                   const double* __restrict__ mass, double h) {
     const int64_t i = (int64_t)blockIdx.x * KB + threadIdx.x;
     if (i >= n) return;
-    const double s = h / mass[i];
-    vel[3 * i] += force[3 * i] * s;
-    vel[3 * i + 1] += force[3 * i + 1] * s;
-    vel[3 * i + 2] += force[3 * i + 2] * s;
+    double v[3] = {vel[3 * i], vel[3 * i + 1], vel[3 * i + 2]};
+    kick(v, force, i, h / mass[i]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) vel[3 * i + d] = v[d];
 }
 
-__global__ __launch_bounds__(KB) void drift_kernel(int64_t n, double* __restrict__ pos,
-                                                   const double* __restrict__ vel, double dt) {
+// The kick that ends a step (if both), the one that starts the next, and its
+// drift: one launch between two force evaluations instead of three (eight steps
+// of 5000 particles, with the smaller sort and the single r_max launch of such sets,
+// 1690 -> 1657 us).
+__global__ __launch_bounds__(KB) void kick_drift_kernel(int64_t n, double* __restrict__ pos,
+                                                        double* __restrict__ vel,
+                                                        const double* __restrict__ force,
+                                                        const double* __restrict__ mass, double h, double dt,
+                                                        int both) {
     const int64_t i = (int64_t)blockIdx.x * KB + threadIdx.x;
-    if (i >= 3 * n) return;
-    pos[i] += vel[i] * dt;
+    if (i >= n) return;
+    const double s = h / mass[i];
+    double v[3] = {vel[3 * i], vel[3 * i + 1], vel[3 * i + 2]};
+    if (both) kick(v, force, i, s);
+    kick(v, force, i, s);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        vel[3 * i + d] = v[d];
+        pos[3 * i + d] = fma(v[d], dt, pos[3 * i + d]);
+    }
 }
 
 }  // namespace
@@ -37,8 +57,10 @@ void run_kick(int64_t n, double* vel, const double* force, const double* mass, d
     TFMM_LAUNCHED();
 }
 
-void run_drift(int64_t n, double* pos, const double* vel, double dt, hipStream_t s) {
-    hipLaunchKernelGGL(drift_kernel, dim3((unsigned)cdiv(3 * n, KB)), dim3(KB), 0, s, n, pos, vel, dt);
+void run_kick_drift(int64_t n, double* pos, double* vel, const double* force, const double* mass, double dt,
+                    bool both, hipStream_t s) {
+    hipLaunchKernelGGL(kick_drift_kernel, dim3((unsigned)cdiv(n, KB)), dim3(KB), 0, s, n, pos, vel, force, mass,
+                       0.5 * dt, dt, both ? 1 : 0);
     TFMM_LAUNCHED();
 }
 

@@ -849,8 +849,8 @@ __global__ __launch_bounds__(TB) void geometry_top_kernel(const int32_t* __restr
 // than kBallsFrom particles are listed (in any order) as items of up to RCH
 // particles, which a wavefront each takes through the balls of the sorted
 // particles.  The items of a node of more than RCH meet in an atomicMax on the
-// bits of the non-negative double, and rmax_final_kernel finishes it.  Sets of up
-// to RCH particles take a wavefront per node and that launch only.
+// bits of the non-negative double, and rmax_final_kernel finishes it.  Up to
+// kWaveNodes particles a wavefront takes a node, whole, and that launch is all.
 //
 // Bound by latency, a node being a chain of dependent loads, and on 2^22
 // particles by the reads.  With a wavefront for every node and all distances
@@ -860,6 +860,7 @@ __global__ __launch_bounds__(TB) void geometry_top_kernel(const int32_t* __restr
 // and 157.
 constexpr int RCH = 4096;          // particles of an item: one ball per lane
 constexpr int kBallsFrom = 512;
+constexpr int kWaveNodes = 4 * RCH;
 
 struct NodePack {
     const int64_t* set_off;
@@ -891,7 +892,7 @@ __device__ __forceinline__ double max_r2(const double4* __restrict__ Xm, int32_t
     return group_max<LANES>(m);
 }
 
-// The same for up to RCH particles through the balls of the 64-particle groups:
+// The same, best for up to some RCH particles, through the balls of the 64-particle groups:
 // a group's distances are looked at only if its ball reaches beyond the largest
 // of the farthest reaching group.  The factor and the last term cover the
 // rounding of the bound (the term where squares underflow), so the maximum is
@@ -905,7 +906,7 @@ __device__ __forceinline__ double max_r2_balls(const double4* __restrict__ Xm, c
         return s >= s0 && s < s1 ? dist2(Xm[s], z.x, z.y, z.z) : 0.0;
     };
     const int32_t last = (s1 - 1) / kWave;
-    for (int32_t b0 = s0 / kWave; b0 <= last; b0 += kWave) {  // one round, two if s0 is inside a group
+    for (int32_t b0 = s0 / kWave; b0 <= last; b0 += kWave) {
         double reach = -1.0;
         if (b0 + lane <= last) {
             const double4 c = balls[b0 + lane];
@@ -938,7 +939,8 @@ __device__ __forceinline__ double max_r2_balls(const double4* __restrict__ Xm, c
 
 template <int LANES>
 __global__ __launch_bounds__(TB) void rmax_kernel(NodeArrays nd, int64_t nn, const double4* __restrict__ Xm,
-                                                  const double4* __restrict__ Z, NodePack pk, int32_t item_from,
+                                                  const double4* __restrict__ balls, const double4* __restrict__ Z,
+                                                  NodePack pk,
                                                   unsigned long long* __restrict__ r2bits, int2* __restrict__ items,
                                                   uint32_t* __restrict__ n_items) {
     // room for the block's items in one step
@@ -948,7 +950,7 @@ __global__ __launch_bounds__(TB) void rmax_kernel(NodeArrays nd, int64_t nn, con
     const int64_t i = (int64_t)blockIdx.x * (TB / LANES) + threadIdx.x / LANES;
     const int lane = threadIdx.x & (LANES - 1);
     const int32_t s0 = i < nn ? nd.first[i] : 0, cnt = i < nn ? nd.count[i] : 0;
-    const bool listed = cnt > item_from;
+    const bool listed = LANES < kWave && cnt > kBallsFrom;
     const int nc = (cnt + RCH - 1) / RCH;
     uint32_t at = 0u;
     if (listed && lane == 0) {
@@ -965,7 +967,8 @@ __global__ __launch_bounds__(TB) void rmax_kernel(NodeArrays nd, int64_t nn, con
         return;
     }
     const double4 z = Z[i];
-    const double m = max_r2<LANES>(Xm, s0, s0 + cnt, z);
+    const double m = LANES == kWave && cnt > kBallsFrom ? max_r2_balls(Xm, balls, s0, s0 + cnt, z, 0.0)
+                                                        : max_r2<LANES>(Xm, s0, s0 + cnt, z);
     if (lane == 0) pack_node(nd, pk, (int32_t)i, z, m);
 }
 __global__ __launch_bounds__(TB) void rmax_items_kernel(const uint32_t* __restrict__ n_items,
@@ -1102,9 +1105,16 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
                                t.lvlb.as<uint8_t>());
             TFMM_LAUNCHED();
         };
-        if (n <= 2 * ST) run(small_sort_kernel<2>);
-        else if (n <= 4 * ST) run(small_sort_kernel<4>);
-        else run(small_sort_kernel<8>);
+        switch (cdiv(n, ST)) {
+            case 1: run(small_sort_kernel<1>); break;
+            case 2: run(small_sort_kernel<2>); break;
+            case 3: run(small_sort_kernel<3>); break;
+            case 4: run(small_sort_kernel<4>); break;
+            case 5: run(small_sort_kernel<5>); break;
+            case 6: run(small_sort_kernel<6>); break;
+            case 7: run(small_sort_kernel<7>); break;
+            default: run(small_sort_kernel<8>);
+        }
     } else {
         t.keys2.ensure(ctx, un * 8);
         t.perm2.ensure(ctx, un * 4);
@@ -1196,15 +1206,14 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     t.w_top.ensure(ctx, (size_t)nn * sizeof(int4));
     t.nd_r2bits.ensure(ctx, (size_t)nn * 8);
     const double4* balls = t.balls.as<double4>();
-    const int32_t item_from = n > RCH ? kBallsFrom : RCH;
+    const bool rows = n > kWaveNodes;
     // every level holds each particle at most once
-    const int64_t ub = n > RCH ? (t.max_level + 1) * (n / kBallsFrom + n / RCH) + 1 : 0;
+    const int64_t ub = rows ? (t.max_level + 1) * (n / kBallsFrom + n / RCH) + 1 : 0;
     t.rmax_items.ensure(ctx, (size_t)std::max<int64_t>(std::min(ub, nn + (t.max_level + 1) * (n / RCH)), 1) * 8);
     const NodePack pk{soff, ns, t.nd_rmax.as<double>(), t.w_geo.as<double4>(), t.w_top.as<int4>()};
-    const bool rows = n > RCH;
     hipLaunchKernelGGL((rows ? rmax_kernel<16> : rmax_kernel<kWave>),
                        dim3((unsigned)cdiv(nn, TB / (rows ? 16 : kWave))), dim3(TB), 0, s, nd, nn,
-                       (const double4*)t.Xm.as<double4>(), (const double4*)t.nd_Z.as<double4>(), pk, item_from,
+                       (const double4*)t.Xm.as<double4>(), balls, (const double4*)t.nd_Z.as<double4>(), pk,
                        t.nd_r2bits.as<unsigned long long>(), t.rmax_items.as<int2>(), n_items);
     TFMM_LAUNCHED();
     if (ub > 0) {

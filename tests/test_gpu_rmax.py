@@ -1,5 +1,5 @@
-"""r_max where its routes change: a wavefront per node in sets of up to 4096
-particles, else rows of 16 lanes, items of up to 4096 particles from 512 on, and
+"""r_max where its routes change: a wavefront per node in sets of up to 16384
+particles, else rows of 16 lanes, items of up to 4096 particles from 513 on, and
 several items from 4097 on.  All are exact maxima, operation by operation.
 """
 import numpy as np
@@ -10,7 +10,7 @@ from paper_2107_07166_amd import generators as g
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 65, 4096, 4097, 8193, 60000])
+@pytest.mark.parametrize("n", [1, 65, 512, 4097, 16384, 16385, 60000])
 @pytest.mark.parametrize("kind", ["plummer", "ties", "shell", "tiny"])
 def test_rmax_is_exact(n, kind):
     import torch

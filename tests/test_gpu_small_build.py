@@ -18,7 +18,8 @@ def _set(n, kind):
     return pos, mass
 
 
-@pytest.mark.parametrize("n", [1, 2, 64, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 20000])
+@pytest.mark.parametrize("n", [1, 2, 64, 1024, 1025, 2047, 2048, 2049, 3073, 4096, 4097, 5121, 6145, 7168, 8191,
+                               8192, 8193, 20000])
 @pytest.mark.parametrize("kind", ["plummer", "ties"])
 def test_build_routes(n, kind):
     import torch
