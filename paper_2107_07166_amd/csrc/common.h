@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <string>
 #include <vector>
@@ -381,8 +382,10 @@ void upload(Tree& t, DevBuf& dst, const void* src, size_t bytes, int slot, hipSt
 // theta: one value for every set, or one per set (n_sets values)
 void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s);
 // passes_done: an event recorded on s once the frontier passes are queued
-// (before the list chains), or nullptr
-void walk_lists_begin(Tree& t, const std::vector<double>& theta, hipStream_t s, hipEvent_t passes_done = nullptr);
+// (before the list chains), or nullptr.  meanwhile: called once when the passes
+// are queued, before the host waits for them (launches for other streams).
+void walk_lists_begin(Tree& t, const std::vector<double>& theta, hipStream_t s, hipEvent_t passes_done,
+                      const std::function<void()>& meanwhile);
 void walk_lists_end(Tree& t, hipStream_t s);
 void aux_fork(Tree& t, hipStream_t s);
 void aux_join(Tree& t, hipStream_t s);
@@ -402,6 +405,7 @@ struct PendingLists {
     }
 };
 int64_t near_interactions(Tree& t);
+void moments_room(Tree& t, int p);
 void compute_moments(Tree& t, int p, hipStream_t s);
 void prepare_sources(Tree& t, int precision, hipStream_t s);
 // kdeg: degree of the conserving projection scalar (p - 1 by default; above

@@ -146,12 +146,17 @@ void run(Tree& t, hipStream_t s) {
 
 }  // namespace
 
-void compute_moments(Tree& t, int p, hipStream_t s) {
+void moments_room(Tree& t, int p) {
     if (t.mom_p == p) return;
     const int NCP = (int)round_up(c_le(p), 4);
     const int64_t nn = t.n_nodes;
     t.W64.ensure(t.ctx, (size_t)nn * NCP * 8);
     t.W32.ensure(t.ctx, (size_t)nn * NCP * 4);
+}
+
+// After moments_room.
+void compute_moments(Tree& t, int p, hipStream_t s) {
+    if (t.mom_p == p) return;
     switch (p) {
         case 1: run<1>(t, s); break;
         case 2: run<2>(t, s); break;

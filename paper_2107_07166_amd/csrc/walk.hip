@@ -747,7 +747,8 @@ void first_room(const Tree& t, const std::vector<double>& theta, int64_t& fr, in
 // A tree's first walk reads the state back after the first launch too, and its
 // room is estimated.  Returns false (lists invalid) when the host-sized passes
 // must be used instead.
-bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thetas, hipStream_t s) {
+bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thetas, hipStream_t s,
+                    const std::function<void()>& queued) {
     Ctx* ctx = t.ctx;
     const double theta = thetas[0];
     const bool known = t.walk_hint_fr > 0;
@@ -784,6 +785,7 @@ bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thet
         launch_seq(t, w, slot, false, kSeqMax, theta, mb, s);
         slot ^= 1;
     }
+    queued();
     WalkState h = wait_state(t, mb, s);
     while (!h.overflow && h.slot[slot].nf != 0u) {
         if (h.passes > (uint32_t)kMaxPasses) return false;
@@ -823,7 +825,8 @@ void aux_join(Tree& t, hipStream_t s) {
 // The frontier passes on s, then the far-list chain on the tree's second
 // stream (after the passes) and the near-list chain on s.  walk_lists_end
 // reads the totals back once the near chain is done.
-void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t s, hipEvent_t passes_done) {
+void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t s, hipEvent_t passes_done,
+                      const std::function<void()>& meanwhile) {
     const int64_t nn = t.n_nodes;
     if (theta_in.size() != 1 && theta_in.size() != (size_t)t.n_sets) fail(TFMM_EINVAL, "theta: one value or one per set");
     const std::vector<double> theta_keep = theta_in;  // the caller's vector may be the tree's own
@@ -835,7 +838,15 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t 
     }
     WalkNodes w{t.w_geo.as<double4>(), t.w_top.as<int4>(), theta_dev, (int32_t)nn};
     t.walk_valid = false;
-    if (!walk_bfs_async(t, w, theta_keep, s)) walk_bfs_sized(t, w, theta, s);
+    bool called = false;
+    const std::function<void()> once = [&] {
+        if (!called) meanwhile();
+        called = true;
+    };
+    if (!walk_bfs_async(t, w, theta_keep, s, once)) {
+        once();
+        walk_bfs_sized(t, w, theta, s);
+    }
     t.walk_hint_far = t.n_m2l;
     t.walk_hint_near = t.n_p2p;
     if (passes_done) TFMM_HIP(hipEventRecord(passes_done, s));
@@ -855,7 +866,7 @@ void walk_lists_end(Tree& t, hipStream_t s) {
 
 void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s) {
     PendingLists pending(t, s);
-    walk_lists_begin(t, theta, s);
+    walk_lists_begin(t, theta, s, nullptr, [] {});
     aux_join(t, s);
     walk_lists_end(t, s);
 }
