@@ -261,6 +261,14 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     };
     prepare_sources(t, prm->precision, s);
     PendingLists pending(t, s);
+    // Of the two list chains the one queued second starts late by its sibling's
+    // launches.  Up to order 5 and 2^15 nodes the near field is what the end waits
+    // for, and its chain goes first: Plummer 2^18 with the potential 1351 -> 1325
+    // us, in FP64 1771 -> 1729, 5000 particles 1602 -> 1574.  Beyond, M2L gains
+    // more from its head start: 100000 particles at order 6 714 us against 730
+    // with the near chain first, a binary of 2^20 at order 4 1434 against 1473, a
+    // disk of 2^22 at order 6 6358 against 6489.
+    const bool near_first = pe <= 5 && t.n_nodes <= 32768;
     if (need_walk) {
         t.walk_valid = false;
         if (t.timing) TFMM_HIP(hipEventRecord(t.ev[11], s));
@@ -268,7 +276,7 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
         // host takes as long to queue the moments' ten launches as the device to
         // run them (four steps of 5000 particles 1657 -> 1606 us, a ball of 2048 226
         // -> 214)
-        walk_lists_begin(t, theta, s, t.timing ? t.ev[12] : nullptr, moments);
+        walk_lists_begin(t, theta, s, t.timing ? t.ev[12] : nullptr, moments, near_first);
     } else {
         moments();
     }

@@ -385,7 +385,7 @@ void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s);
 // (before the list chains), or nullptr.  meanwhile: called once when the passes
 // are queued, before the host waits for them (launches for other streams).
 void walk_lists_begin(Tree& t, const std::vector<double>& theta, hipStream_t s, hipEvent_t passes_done,
-                      const std::function<void()>& meanwhile);
+                      const std::function<void()>& meanwhile, bool near_first);
 void walk_lists_end(Tree& t, hipStream_t s);
 void aux_fork(Tree& t, hipStream_t s);
 void aux_join(Tree& t, hipStream_t s);

@@ -826,7 +826,7 @@ void aux_join(Tree& t, hipStream_t s) {
 // stream (after the passes) and the near-list chain on s.  walk_lists_end
 // reads the totals back once the near chain is done.
 void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t s, hipEvent_t passes_done,
-                      const std::function<void()>& meanwhile) {
+                      const std::function<void()>& meanwhile, bool near_first) {
     const int64_t nn = t.n_nodes;
     if (theta_in.size() != 1 && theta_in.size() != (size_t)t.n_sets) fail(TFMM_EINVAL, "theta: one value or one per set");
     const std::vector<double> theta_keep = theta_in;  // the caller's vector may be the tree's own
@@ -854,8 +854,9 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t 
     // The far-list chain runs on the tree's second stream, the near-list chain
     // on s; they share no buffer.
     aux_fork(t, s);
+    if (near_first) build_near_lists(t, s);
     build_far_lists(t, t.aux);
-    build_near_lists(t, s);
+    if (!near_first) build_near_lists(t, s);
     t.walk_theta = theta_keep;
 }
 
@@ -866,7 +867,7 @@ void walk_lists_end(Tree& t, hipStream_t s) {
 
 void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s) {
     PendingLists pending(t, s);
-    walk_lists_begin(t, theta, s, nullptr, [] {});
+    walk_lists_begin(t, theta, s, nullptr, [] {}, false);
     aux_join(t, s);
     walk_lists_end(t, s);
 }
