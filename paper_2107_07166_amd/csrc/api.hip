@@ -166,16 +166,14 @@ int scalar_degree(const tfmm_params* p) {
 
 // Two streams: s (the caller's) and the tree's second stream a.
 //   a: moments (during the frontier passes) -> far-list chain -> M2L -> L2L
-//      -> L2P's far part
 //   s: sources -> frontier passes -> near-list chain -> P2P -> split-leaf
-//      reduction -> [join a] -> forces (near + far)
+//      reduction -> [join a] -> L2P and the forces (near + far)
 // The latency-bound list chains hide behind each other, and P2P starts as
 // soon as the near lists exist, beside M2L and L2L on the second stream.
 // Adds the phase times of the last timed evaluation to the tree's sums.
-// Events: moments [0,1], M2L [7,2], L2L [2,3] on the tree's second stream;
+// Events: moments [13,1], M2L [7,2], L2L [2,3] on the tree's second stream;
 // P2P [6,4] (the near-field kernel; the partial-sum reduction follows it),
-// the forces from near and far parts [8,5] on the caller's stream (8: after
-// the streams join; L2P's far part runs before the join, after L2L);
+// L2P and the forces [8,5] on the caller's stream (8: after the streams join);
 // whole evaluation [0,5]; walk [11, later of 7 and 6], its frontier passes
 // [11,12] (only in evaluations that walked).
 double elapsed_ms(Tree& t, int i, int j) {
@@ -191,7 +189,7 @@ void fold_times(Tree& t) {
     t.t_sum[1] += elapsed_ms(t, 6, 4);  // P2P
     t.t_sum[2] += elapsed_ms(t, 2, 3);  // L2L
     t.t_sum[3] += elapsed_ms(t, 8, 5);  // forces after the join
-    t.t_sum[4] += elapsed_ms(t, 0, 1);  // moments
+    t.t_sum[4] += elapsed_ms(t, 13, 1);  // moments
     t.t_sum[5] += elapsed_ms(t, 0, 5);  // whole evaluation after the tree build
     {
         // the interaction pass: from the first of P2P and M2L to start (6, 7)
@@ -254,8 +252,9 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     aux_fork(t, s);
     const hipStream_t a = t.aux;
     moments_room(t, pe);
+    if (t.timing) TFMM_HIP(hipEventRecord(t.ev[0], a));
     auto moments = [&] {
-        if (t.timing) TFMM_HIP(hipEventRecord(t.ev[0], a));
+        if (t.timing) TFMM_HIP(hipEventRecord(t.ev[13], a));
         compute_moments(t, pe, a);
         if (t.timing) TFMM_HIP(hipEventRecord(t.ev[1], a));
     };
@@ -285,9 +284,6 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     if (t.timing) TFMM_HIP(hipEventRecord(t.ev[2], a));
     run_l2l(t, pe, ve, a);
     if (t.timing) TFMM_HIP(hipEventRecord(t.ev[3], a));
-    // the far-field part of L2P beside the near field; only the sum of the
-    // two waits for both
-    run_l2p_far(t, pe, ve, a);
     if (potential && !shared_pot) {
         run_m2l_pot(t, prm->p, pe, prm->precision, eps2, a);
         run_l2l_pot(t, prm->p, a);
@@ -299,7 +295,7 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     run_p2p_reduce(t, potential != nullptr, s);
     aux_join(t, s);
     if (t.timing) TFMM_HIP(hipEventRecord(t.ev[8], s));
-    run_force_combine(t, prm->G, force, s);
+    run_l2p(t, pe, ve, prm->G, force, s);
     if (potential)
         run_l2p_pot(t, prm->p, prm->precision, eps2, prm->G, (shared_pot ? t.loc_leaf : t.loc_pot_leaf).as<double>(),
                     potential, s);

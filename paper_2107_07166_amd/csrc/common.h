@@ -263,7 +263,6 @@ struct Tree {
     DevBuf loc_leaf;              // FP64 gathered locals per leaf (per node when built level by level)
     DevBuf loc_has;               // uint8 per node: its gathered locals exist (level-by-level pass)
     DevBuf near3;                 // FP64 near-field acceleration (3 per sorted particle)
-    DevBuf far3;                  // FP64 far-field acceleration (3 per sorted particle)
     DevBuf near_pot, partial_pot; // FP64 near-field potential (per sorted particle / per partial row)
     DevBuf loc_pot, loc_pot_leaf; // FP64 standard locals with L_0 (potential beside conserving forces)
 
@@ -284,7 +283,7 @@ struct Tree {
     // rebuild, folded at the next rebuild or when read; ev[11], ev[12]: the
     // walk of the latest evaluation (start, end of the frontier passes).
     bool timing = false;
-    hipEvent_t ev[13] = {};
+    hipEvent_t ev[14] = {};
     bool ev_ready = false;
     bool ev_pending = false;
     bool ev_walked = false;        // the pending evaluation ran a walk
@@ -420,10 +419,8 @@ void run_l2l_pot(Tree& t, int p, hipStream_t s);
 void run_l2p_pot(Tree& t, int p, int precision, double eps2, double G, const double* loc_leaf, double* pot,
                  hipStream_t s);
 void run_l2l(Tree& t, int p, int variant, hipStream_t s);
-// Far-field acceleration of every particle into t.far3 (after L2L, on the
-// stream L2L ran on), then the forces G m (near + far) in caller order.
-void run_l2p_far(Tree& t, int p, int variant, hipStream_t s);
-void run_force_combine(Tree& t, double G, double* force, hipStream_t s);
+// The forces of every particle from its leaf's locals and the near sums.
+void run_l2p(Tree& t, int p, int variant, double G, double* force, hipStream_t s);
 void run_diagnostics(int64_t n, const double* pos, const double* vel, const double* mass,
                      const double* force, double* out_host, Ctx* ctx, hipStream_t s);
 void diag_scratch_init(int device);  // with the device current

@@ -318,15 +318,31 @@ void l2l_levels(Tree& t, hipStream_t s) {
     }
 }
 
+// The force G m (near + far) of sorted particle j, into its caller-order slot.
+__device__ __forceinline__ void write_force(int64_t j, const double4& x, const double* a,
+                                            const double* __restrict__ near, const int32_t* __restrict__ perm,
+                                            double G, double* __restrict__ force) {
+    const double s = G * x.w;
+    const int64_t o = perm[j];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) force[3 * o + d] = s * (near[3 * j + d] + a[d]);
+}
+
 // Far-field acceleration at every particle (sorted order) from its leaf's
-// locals, into far3 (three values per particle).  It runs on the tree's
-// second stream right after L2L, beside the near field.
+// locals, and its force with the near sums.  One launch once both are there:
+// with the far part in a launch of its own beside the near field, 24 bytes per
+// particle were written and read back, and on large trees that launch ran
+// after the near field all the same, for lack of free wavefronts before (binary
+// of 2^20 1429 -> 1416 us, Plummer 2^20 3.10 -> 3.07 ms, disk of 2^22 6.47 ->
+// 6.45).
 template <int P, int VAR>
-__global__ __launch_bounds__(LB) void l2p_far_kernel(int64_t n, const double4* __restrict__ Xm,
-                                                     const int32_t* __restrict__ leaf_of,
-                                                     const double4* __restrict__ Z,
-                                                     const double* __restrict__ loc_leaf,
-                                                     double* __restrict__ far3) {
+__global__ __launch_bounds__(LB) void l2p_kernel(int64_t n, const double4* __restrict__ Xm,
+                                                 const int32_t* __restrict__ leaf_of,
+                                                 const double4* __restrict__ Z,
+                                                 const double* __restrict__ loc_leaf,
+                                                 const double* __restrict__ near,
+                                                 const int32_t* __restrict__ perm, double G,
+                                                 double* __restrict__ force) {
     using E = Expansion<P>;
     const int64_t j = (int64_t)blockIdx.x * LB + threadIdx.x;
     if (j >= n) return;
@@ -342,9 +358,7 @@ __global__ __launch_bounds__(LB) void l2p_far_kernel(int64_t n, const double4* _
     } else {
         E::l2p_std(loc_leaf + (int64_t)leaf * E::NC, dx, dy, dz, a);
     }
-    far3[3 * j] = a[0];
-    far3[3 * j + 1] = a[1];
-    far3[3 * j + 2] = a[2];
+    write_force(j, x, a, near, perm, G, force);
 }
 
 // The same for the conserving locals from order 6 (224 or more coefficients
@@ -370,9 +384,10 @@ __device__ __forceinline__ void l2p_eval(const double* __restrict__ l, double dx
 
 template <int P, int VAR>
 __global__ __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(P == 6 ? 4 : 1)))
-void l2p_far_staged_kernel(int64_t n, const double4* __restrict__ Xm, const int32_t* __restrict__ leaf_of,
+void l2p_staged_kernel(int64_t n, const double4* __restrict__ Xm, const int32_t* __restrict__ leaf_of,
                            const double4* __restrict__ Z, const double* __restrict__ loc_leaf,
-                           double* __restrict__ far3) {
+                           const double* __restrict__ near, const int32_t* __restrict__ perm, double G,
+                           double* __restrict__ force) {
     using E = Expansion<P>;
     constexpr int NL = VAR == TFMM_CONSERVING ? 4 * E::NC1 : E::NC;  // coefficients per leaf
     constexpr int STRIDE = NL | 1;  // odd: the slots' words fall in different banks
@@ -415,27 +430,10 @@ void l2p_far_staged_kernel(int64_t n, const double4* __restrict__ Xm, const int3
         if (mine) {
             double a[3];
             l2p_eval<P, VAR>(cs + (slot - base) * STRIDE, dx, dy, dz, a);
-            far3[3 * j] = a[0];
-            far3[3 * j + 1] = a[1];
-            far3[3 * j + 2] = a[2];
+            write_force(j, x, a, near, perm, G, force);
         }
         __syncthreads();
     }
-}
-
-// The force G m (near + far) of every particle, into its caller-order slot.
-__global__ __launch_bounds__(LB) void force_combine_kernel(int64_t n, const double4* __restrict__ Xm,
-                                                           const int32_t* __restrict__ perm,
-                                                           const double* __restrict__ near,
-                                                           const double* __restrict__ far3, double G,
-                                                           double* __restrict__ force) {
-    const int64_t j = (int64_t)blockIdx.x * LB + threadIdx.x;
-    if (j >= n) return;
-    const double s = G * Xm[j].w;
-    const int64_t o = perm[j];
-    force[3 * o] = s * (near[3 * j] + far3[3 * j]);
-    force[3 * o + 1] = s * (near[3 * j + 1] + far3[3 * j + 1]);
-    force[3 * o + 2] = s * (near[3 * j + 2] + far3[3 * j + 2]);
 }
 
 // Potential output: phi_a = sum_{|j| <= p} L_j x^j / j! (standard locals with
@@ -503,26 +501,16 @@ void l2l_dispatch(Tree& t, int variant, hipStream_t s) {
 }
 
 template <int P>
-void l2p_far_dispatch(Tree& t, int variant, hipStream_t s) {
-    const int64_t n = t.n;
-    if constexpr (P >= 6) {
-        if (variant == TFMM_CONSERVING) {
-            hipLaunchKernelGGL((l2p_far_staged_kernel<P, TFMM_CONSERVING>), dim3((unsigned)cdiv(n, LB)), dim3(LB), 0,
-                               s, n, t.Xm.as<double4>(), t.leaf_of.as<int32_t>(), t.nd_Z.as<double4>(),
-                               t.loc_leaf.as<double>(), t.far3.as<double>());
-            TFMM_LAUNCHED();
-            return;
-        }
-    }
-    if (variant == TFMM_CONSERVING)
-        hipLaunchKernelGGL((l2p_far_kernel<P, TFMM_CONSERVING>), dim3((unsigned)cdiv(n, LB)), dim3(LB), 0, s, n,
-                           t.Xm.as<double4>(), t.leaf_of.as<int32_t>(), t.nd_Z.as<double4>(),
-                           t.loc_leaf.as<double>(), t.far3.as<double>());
-    else
-        hipLaunchKernelGGL((l2p_far_kernel<P, TFMM_STANDARD>), dim3((unsigned)cdiv(n, LB)), dim3(LB), 0, s, n,
-                           t.Xm.as<double4>(), t.leaf_of.as<int32_t>(), t.nd_Z.as<double4>(),
-                           t.loc_leaf.as<double>(), t.far3.as<double>());
-    TFMM_LAUNCHED();
+void l2p_dispatch(Tree& t, int variant, double G, double* force, hipStream_t s) {
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(t.n, LB)), dim3(LB), 0, s, t.n, t.Xm.as<double4>(),
+                           t.leaf_of.as<int32_t>(), t.nd_Z.as<double4>(), t.loc_leaf.as<double>(),
+                           t.near3.as<double>(), t.perm.as<int32_t>(), G, force);
+        TFMM_LAUNCHED();
+    };
+    if (variant != TFMM_CONSERVING) run(l2p_kernel<P, TFMM_STANDARD>);
+    else if constexpr (P >= 6) run(l2p_staged_kernel<P, TFMM_CONSERVING>);
+    else run(l2p_kernel<P, TFMM_CONSERVING>);
 }
 
 }  // namespace
@@ -574,26 +562,18 @@ void run_l2p_pot(Tree& t, int p, int precision, double eps2, double G, const dou
     }
 }
 
-void run_l2p_far(Tree& t, int p, int variant, hipStream_t s) {
-    t.far3.ensure(t.ctx, (size_t)t.n * 24);
+void run_l2p(Tree& t, int p, int variant, double G, double* force, hipStream_t s) {
     switch (p) {
-        case 1: l2p_far_dispatch<1>(t, variant, s); break;
-        case 2: l2p_far_dispatch<2>(t, variant, s); break;
-        case 3: l2p_far_dispatch<3>(t, variant, s); break;
-        case 4: l2p_far_dispatch<4>(t, variant, s); break;
-        case 5: l2p_far_dispatch<5>(t, variant, s); break;
-        case 6: l2p_far_dispatch<6>(t, variant, s); break;
-        case 7: l2p_far_dispatch<7>(t, variant, s); break;
-        case 8: l2p_far_dispatch<8>(t, variant, s); break;
+        case 1: l2p_dispatch<1>(t, variant, G, force, s); break;
+        case 2: l2p_dispatch<2>(t, variant, G, force, s); break;
+        case 3: l2p_dispatch<3>(t, variant, G, force, s); break;
+        case 4: l2p_dispatch<4>(t, variant, G, force, s); break;
+        case 5: l2p_dispatch<5>(t, variant, G, force, s); break;
+        case 6: l2p_dispatch<6>(t, variant, G, force, s); break;
+        case 7: l2p_dispatch<7>(t, variant, G, force, s); break;
+        case 8: l2p_dispatch<8>(t, variant, G, force, s); break;
         default: fail(TFMM_EINVAL, "p must be in 1..8");
     }
-}
-
-void run_force_combine(Tree& t, double G, double* force, hipStream_t s) {
-    const int64_t n = t.n;
-    hipLaunchKernelGGL(force_combine_kernel, dim3((unsigned)cdiv(n, LB)), dim3(LB), 0, s, n, t.Xm.as<double4>(),
-                       t.perm.as<int32_t>(), t.near3.as<double>(), t.far3.as<double>(), G, force);
-    TFMM_LAUNCHED();
 }
 
 }  // namespace tfmm
