@@ -298,7 +298,7 @@ size_t scan_scratch_bytes(int64_t n);
 // land in *total0 and *total1 (device).
 void exclusive_scan2_u32(const uint32_t* in0, uint32_t* out0, uint32_t* total0, const uint32_t* in1,
                          uint32_t* out1, uint32_t* total1, int64_t n, void* scratch, hipStream_t s);
-// One over gathered values: value i = val[idx[i]] (val non-negative).
+// One over gathered source counts: value i = source_step(val[idx[i]]).
 void exclusive_scan_gather_u32(const int32_t* idx, const int32_t* val, uint32_t* out, int64_t n, void* scratch,
                                uint32_t* total_dev, hipStream_t s);
 

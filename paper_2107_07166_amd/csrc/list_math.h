@@ -1,0 +1,44 @@
+// Arithmetic of the near-field work items, free of HIP so that a test can run it
+// on the CPU too.
+#pragma once
+
+#include <cstdint>
+
+namespace tfmm {
+
+// A target leaf's near list is cut before entry q when the number of source
+// particles preceding q in that list crosses a multiple of kItemSources, so no
+// wavefront receives more than about kItemSources sources per target.
+constexpr uint32_t kItemSources = 4096;
+
+// What a source leaf adds to the prefixes P that the lists are cut by: its
+// particles, and kItemSources if it holds more, as a leaf of the deepest level
+// may whose particles (nearly) coincide.  With no more than that per entry the
+// item index grows by at most one from an entry to the next: every item has a
+// first entry of its own, and a list has no more items than entries.
+constexpr uint32_t source_step(int32_t count) {
+    return (uint32_t)count < kItemSources ? (uint32_t)count : kItemSources;
+}
+
+// Items of the list of entries [q0, q1): entry q belongs to item
+// floor((P[q] - P[q0]) / kItemSources).  P is taken modulo 2^32; only differences
+// inside one list are used.
+constexpr uint32_t list_items(const uint32_t* P, uint32_t q0, uint32_t q1) {
+    return q1 > q0 ? (P[q1 - 1u] - P[q0]) / kItemSources + 1u : 0u;
+}
+
+// First entry of item k of the list: the first q with P[q] - P[q0] >= k
+// kItemSources, by binary search.
+constexpr uint32_t item_start(const uint32_t* P, uint32_t q0, uint32_t q1, uint32_t k) {
+    if (k == 0u) return q0;
+    const uint32_t p0 = P[q0], want = k * kItemSources;
+    uint32_t lo = q0 + 1u, hi = q1 - 1u;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2u;
+        if (P[mid] - p0 >= want) hi = mid;
+        else lo = mid + 1u;
+    }
+    return lo;
+}
+
+}  // namespace tfmm

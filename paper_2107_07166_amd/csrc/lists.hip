@@ -24,6 +24,7 @@
 #include <cstddef>
 
 #include "common.h"
+#include "list_math.h"
 
 namespace tfmm {
 namespace {
@@ -288,27 +289,18 @@ __global__ __launch_bounds__(PB) void bucket_scatter_kernel(const int2* __restri
 }
 
 // What the near lists need besides their bounds: the sources before every
-// entry along its bucket (mod 2^32; only differences inside a list are used),
-// and per target its items and partial rows.
+// entry along its bucket (as source_step counts them, mod 2^32), and per target
+// its items and partial rows.
 struct NearOut {
     const int32_t* count;
     uint32_t *P, *nitems, *prows;
 };
-// ---- near-field work items:
-// A target leaf's near list is cut before entry q when the number of source
-// particles preceding q in that list crosses a multiple of kItemSources, so no
-// wavefront receives more than about kItemSources sources per target.  (The
-// prefix is taken modulo 2^32; only differences inside one list are used.)
-constexpr uint32_t kItemSources = 4096;
 
-// Items of a list with source prefixes P over entries [q0, q1): entry q belongs
-// to item k = floor((P[q] - P[q0]) / kItemSources).  A source leaf holds at
-// most 4096 particles, so k grows by at most one per entry and the list has
-// k_last + 1 items.  Only a leaf split into several items needs partial-sum
-// rows (one per item and target particle).
-__device__ __forceinline__ void list_items(const uint32_t* P, uint32_t q0, uint32_t q1, int32_t count, uint32_t* nit,
+// Items of a target leaf's list, and its partial-sum rows (one per item and target
+// particle), which only a leaf split into several items needs.
+__device__ __forceinline__ void leaf_items(const uint32_t* P, uint32_t q0, uint32_t q1, int32_t count, uint32_t* nit,
                                            uint32_t* prw) {
-    const uint32_t n = (q1 > q0) ? (P[q1 - 1] - P[q0]) / kItemSources + 1u : 0u;
+    const uint32_t n = list_items(P, q0, q1);
     *nit = n;
     *prw = n > 1u ? n * (uint32_t)count : 0u;
 }
@@ -433,7 +425,7 @@ __global__ __launch_bounds__(LT) void bucket_lists_kernel(const Word* __restrict
 #pragma unroll
             for (int r = 0; r < LP; ++r) {
                 const uint32_t i = r * LT + tid;
-                st[i + i / LP] = q0 + i < E1 ? (uint32_t)no.count[src[q0 + i]] : 0u;
+                st[i + i / LP] = q0 + i < E1 ? source_step(no.count[src[q0 + i]]) : 0u;
             }
             __syncthreads();
             uint32_t c[LP], sumc = 0u;
@@ -461,7 +453,7 @@ __global__ __launch_bounds__(LT) void bucket_lists_kernel(const Word* __restrict
         __syncthreads();
         if (tid < nl) {
             const int64_t t = sp.target(b, (uint32_t)tid);
-            if (t < nn) list_items(no.P, l0[t], l1[t], no.count[t], &no.nitems[t], &no.prows[t]);
+            if (t < nn) leaf_items(no.P, l0[t], l1[t], no.count[t], &no.nitems[t], &no.prows[t]);
         }
     }
 }
@@ -508,29 +500,13 @@ __global__ __launch_bounds__(TB) void node_items_kernel(const uint32_t* __restri
                                                         const int32_t* __restrict__ count,
                                                         uint32_t* __restrict__ nitems, uint32_t* __restrict__ prows) {
     const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-    if (i < nn) list_items(P, off[i], off[i + 1], count[i], &nitems[i], &prows[i]);
+    if (i < nn) leaf_items(P, off[i], off[i + 1], count[i], &nitems[i], &prows[i]);
 }
 
 // ---- work items ------------------------------------------------------------------
 // One thread per item: its leaf is the last node whose first item is at or
 // before it (nodes without items share their first-item index with the next
-// node); item k of a list starts at its first entry q with
-// P[q] - P[q0] >= k kItemSources (P grows along a list, by at most kItemSources
-// per entry, so every item has a first entry), found by binary search, and ends
-// where item k + 1 starts.
-__device__ __forceinline__ uint32_t item_start(const uint32_t* __restrict__ P, uint32_t q0, uint32_t q1,
-                                               uint32_t k) {
-    if (k == 0u) return q0;
-    const uint32_t p0 = P[q0], want = k * kItemSources;
-    uint32_t lo = q0 + 1u, hi = q1 - 1u;
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2u;
-        if (P[mid] - p0 >= want) hi = mid;
-        else lo = mid + 1u;
-    }
-    return lo;
-}
-
+// node); it ends where the next item of the list starts.
 __global__ __launch_bounds__(TB) void item_write_kernel(const uint32_t* __restrict__ P,
                                                         const uint32_t* __restrict__ l0,
                                                         const uint32_t* __restrict__ l1, int64_t nn,
@@ -791,7 +767,7 @@ void build_near_lists(Tree& t, hipStream_t s) {
                            nn, t.nd_count.as<int32_t>(), nit, prw);
         TFMM_LAUNCHED();
     }
-    // there are at most ne items, so every item array is sized by ne
+    // a list has no more items than entries, so every item array is sized by ne
     const size_t ni = (size_t)std::max<int64_t>(ne, 1);
     t.it_leaf.ensure(ctx, ni * 4);
     t.it_q0.ensure(ctx, ni * 4);

@@ -12,10 +12,12 @@
 // launch per scan and spent most of its time in the chain of look-backs; one
 // large workgroup for the tile totals waited for whole compute units to
 // drain.)  In-place use (in == out) is allowed: a tile is read whole before it
-// is written.  The input may also be gathered: value i = val[idx[i]].
+// is written.  The input may also be gathered: value i =
+// source_step(val[idx[i]]), the near lists' source counts.
 #include <algorithm>
 
 #include "common.h"
+#include "list_math.h"
 
 namespace tfmm {
 namespace {
@@ -34,7 +36,7 @@ struct ArrayIn {
 struct GatherIn {
     const int32_t* idx;
     const int32_t* val;
-    __device__ __forceinline__ uint32_t operator()(int64_t i) const { return (uint32_t)val[idx[i]]; }
+    __device__ __forceinline__ uint32_t operator()(int64_t i) const { return source_step(val[idx[i]]); }
 };
 
 // Exclusive scan of the per-thread sums over a workgroup of B threads; the
