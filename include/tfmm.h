@@ -139,13 +139,16 @@ int tfmm_build_tree(tfmm_ctx *ctx, int64_t n, const double *pos, const double *m
 /* Rebuild an existing tree in place for a particle set of n particles (n may
  * differ from the previous build; pos and mass as in tfmm_build_tree).  Device
  * buffers are grow-only, so a tree reused for sets of similar size allocates
- * nothing.  Synchronising.  Errors: EINVAL, ENOMEM, EDEVICE. */
+ * nothing.  A rebuild that is refused for its arguments (n, NULL pointers)
+ * changes nothing; one that fails later (positions that are not finite, ENOMEM)
+ * leaves the tree without particles: walks, evaluations and exports give ESTATE
+ * until a rebuild succeeds.  Synchronising.  Errors: EINVAL, ENOMEM, EDEVICE. */
 int tfmm_tree_rebuild(tfmm_tree *tree, int64_t n, const double *pos, const double *mass, void *stream);
 
 /* Run the mutual dual-tree walk for `theta` (Eq. mac_criterion) and build the
  * per-target interaction lists.  tfmm_evaluate_forces calls it when theta
- * changed; exposed for list export.  Synchronising.  Errors: EINVAL, ENOMEM,
- * EDEVICE. */
+ * changed; exposed for list export.  Synchronising.  Errors: EINVAL, ESTATE
+ * (the last rebuild failed), ENOMEM, EDEVICE. */
 int tfmm_tree_walk(tfmm_tree *tree, double theta, void *stream);
 
 /* Forces on every particle: force (device, n x 3 FP64 row-major, original
@@ -162,7 +165,8 @@ int tfmm_tree_walk(tfmm_tree *tree, double theta, void *stream);
  * ordered on `stream` like a single kernel.
  * Errors: EINVAL (p outside 1..8, theta outside [0,1), eps < 0, bad variant
  * or precision, TFMM_CONSERVING_R2 with p != 1, scalar_degree set for another
- * variant or outside its range, NULL force), ENOMEM, EDEVICE. */
+ * variant or outside its range, NULL force), ESTATE (the last rebuild failed),
+ * ENOMEM, EDEVICE. */
 int tfmm_evaluate_forces(tfmm_tree *tree, const tfmm_params *params, double *force,
                          double *potential, void *stream);
 
@@ -259,7 +263,7 @@ int tfmm_tree_info(const tfmm_tree *tree, int64_t *out);
  * prefix (uint64, key >> 3(21 - level)), first / count (int32, sorted range),
  * child_first (int32, -1 for leaves), nchild (int32), parent (int32, -1 for
  * the root), com (3 FP64 per node), mass (FP64), rmax (FP64).  Synchronising.
- * Errors: EINVAL, EDEVICE. */
+ * Errors: EINVAL, ESTATE (the last rebuild failed), EDEVICE. */
 int tfmm_tree_export(tfmm_tree *tree, uint64_t *keys, int32_t *order, int32_t *level,
                      uint64_t *prefix, int32_t *first, int32_t *count, int32_t *child_first,
                      int32_t *nchild, int32_t *parent, double *com, double *mass, double *rmax);

@@ -223,6 +223,39 @@ void timing_events(Tree& t) {
     }
 }
 
+// Rebuilds t for n particles, the sets of a forest if offsets is given.  If that
+// fails the tree has its former sizes again, which are those that the caller's
+// arrays still have, and is not built.
+void rebuild(Tree& t, int64_t n, int n_sets, const int64_t* offsets, const double* pos, const double* mass,
+             hipStream_t s) {
+    const int64_t n_before = t.n;
+    const int sets_before = t.n_sets;
+    timing_events(t);
+    if (t.timing) {
+        fold_build(t);
+        TFMM_HIP(hipEventRecord(t.ev[9], s));
+    }
+    t.built = t.walk_valid = false;
+    try {
+        t.n = n;
+        t.n_sets = 1;
+        if (offsets) set_sets(t, n_sets, offsets, s);
+        build_tree(t, pos, mass, s);
+    } catch (...) {
+        t.n = n_before;
+        t.n_sets = sets_before;
+        throw;
+    }
+    if (t.timing) {
+        TFMM_HIP(hipEventRecord(t.ev[10], s));
+        t.build_pending = true;
+    }
+}
+
+void check_built(const Tree& t) {
+    if (!t.built) fail(TFMM_ESTATE, "the tree's last build failed: rebuild it first");
+}
+
 // theta_sets: one theta per set of a forest (host), or nullptr for
 // params->theta everywhere.
 void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double* force, double* potential,
@@ -426,20 +459,7 @@ int tfmm_tree_rebuild(tfmm_tree* tree, int64_t n, const double* pos, const doubl
         if (n < 1 || n > (int64_t)INT32_MAX / 2) fail(TFMM_EINVAL, "n must be in 1..2^30");
         if (!pos || !mass) fail(TFMM_EINVAL, "pos and mass must be device pointers");
         set_device(tree->ctx);
-        Tree& t = *tree;
-        const hipStream_t s = (hipStream_t)stream;
-        timing_events(t);
-        if (t.timing) {
-            fold_build(t);
-            TFMM_HIP(hipEventRecord(t.ev[9], s));
-        }
-        t.n = n;
-        t.n_sets = 1;
-        build_tree(t, pos, mass, s);
-        if (t.timing) {
-            TFMM_HIP(hipEventRecord(t.ev[10], s));
-            t.build_pending = true;
-        }
+        rebuild(*tree, n, 1, nullptr, pos, mass, (hipStream_t)stream);
     });
 }
 
@@ -482,20 +502,7 @@ int tfmm_forest_rebuild(tfmm_tree* tree, int n_sets, const int64_t* offsets, con
         const int64_t n = check_sets(n_sets, offsets);
         if (!pos || !mass) fail(TFMM_EINVAL, "pos and mass must be device pointers");
         set_device(tree->ctx);
-        Tree& t = *tree;
-        const hipStream_t s = (hipStream_t)stream;
-        timing_events(t);
-        if (t.timing) {
-            fold_build(t);
-            TFMM_HIP(hipEventRecord(t.ev[9], s));
-        }
-        t.n = n;
-        set_sets(t, n_sets, offsets, s);
-        build_tree(t, pos, mass, s);
-        if (t.timing) {
-            TFMM_HIP(hipEventRecord(t.ev[10], s));
-            t.build_pending = true;
-        }
+        rebuild(*tree, n, n_sets, offsets, pos, mass, (hipStream_t)stream);
     });
 }
 
@@ -509,6 +516,7 @@ int tfmm_evaluate_forest(tfmm_tree* tree, const tfmm_params* params, const doubl
             for (int k = 0; k < tree->n_sets; ++k)
                 if (!(theta[k] >= 0.0) || !(theta[k] < 1.0))
                     fail(TFMM_EINVAL, "theta must satisfy 0 <= theta < 1 for every set");
+        check_built(*tree);
         set_device(tree->ctx);
         evaluate(*tree, params, theta, force, potential, (hipStream_t)stream);
     });
@@ -518,6 +526,7 @@ int tfmm_tree_walk(tfmm_tree* tree, double theta, void* stream) {
     if (!tree) return TFMM_EINVAL;
     return guarded(tree->ctx, [&] {
         if (!(theta >= 0.0) || !(theta < 1.0)) fail(TFMM_EINVAL, "theta must satisfy 0 <= theta < 1");
+        check_built(*tree);
         set_device(tree->ctx);
         walk_tree(*tree, std::vector<double>{theta}, (hipStream_t)stream);
     });
@@ -529,6 +538,7 @@ int tfmm_evaluate_forces(tfmm_tree* tree, const tfmm_params* params, double* for
     return guarded(tree->ctx, [&] {
         check_params(params);
         if (!force) fail(TFMM_EINVAL, "force must be a device pointer");
+        check_built(*tree);
         set_device(tree->ctx);
         evaluate(*tree, params, nullptr, force, potential, (hipStream_t)stream);
     });
@@ -619,6 +629,7 @@ int tfmm_tree_export(tfmm_tree* tree, uint64_t* keys, int32_t* order, int32_t* l
     if (!tree) return TFMM_EINVAL;
     return guarded(tree->ctx, [&] {
         Tree& t = *tree;
+        check_built(t);
         set_device(t.ctx);
         TFMM_HIP(hipDeviceSynchronize());
         const size_t n = (size_t)t.n, nn = (size_t)t.n_nodes;

@@ -229,6 +229,7 @@ struct Tree {
     DevBuf leaves;             // int32 node ids of the leaves
     DevBuf rmax_items;         // int2 (node, chunk) work items of the r_max pass
     DevBuf balls;              // double4 per 64 sorted particles: centre, radius
+    bool built = false;        // the buffers above hold one complete build
 
     // walk and per-target interaction lists
     bool walk_valid = false;
@@ -373,6 +374,8 @@ V read_back_checked(Ctx* ctx, const V* dev, hipStream_t s) {
 }
 
 // ---- phases ---------------------------------------------------------------
+// For the sets that t.n, t.n_sets and t.set_off describe.  If it fails the tree is
+// left not built.
 void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s);
 // Copies bytes from host memory to dst (device) on s through the tree's
 // pinned staging area (slot 0 or 1, kStageSlot bytes each).

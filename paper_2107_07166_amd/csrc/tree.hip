@@ -1064,6 +1064,11 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
     Ctx* ctx = t.ctx;
     const int64_t n = t.n;
     const size_t un = (size_t)n;
+    // what was derived from the particles before goes with them
+    t.built = false;
+    t.walk_valid = false;
+    t.mom_p = -1;
+    t.src_prec = -1;
 
     const int ns = t.n_sets;
     const int64_t* soff = ns > 1 ? t.set_off.as<int64_t>() : nullptr;
@@ -1229,9 +1234,7 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
         TFMM_LAUNCHED();
     }
 
-    t.walk_valid = false;
-    t.mom_p = -1;
-    t.src_prec = -1;
+    t.built = true;
 }
 
 void prepare_sources(Tree& t, int precision, hipStream_t s) {
