@@ -148,6 +148,7 @@ void run(Tree& t, hipStream_t s) {
 
 void moments_room(Tree& t, int p) {
     if (t.mom_p == p) return;
+    t.mom_p = -1;  // what is there goes when the buffers grow
     const int NCP = (int)round_up(c_le(p), 4);
     const int64_t nn = t.n_nodes;
     t.W64.ensure(t.ctx, (size_t)nn * NCP * 8);

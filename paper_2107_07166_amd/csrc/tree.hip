@@ -1239,6 +1239,7 @@ void build_tree(Tree& t, const double* pos, const double* mass, hipStream_t s) {
 
 void prepare_sources(Tree& t, int precision, hipStream_t s) {
     if (t.src_prec == precision) return;
+    t.src_prec = -1;  // what is there goes when the buffer grows
     const int64_t n = t.n;
     if (precision == TFMM_MIXED32) {
         t.src4.ensure(t.ctx, (size_t)n * 16);

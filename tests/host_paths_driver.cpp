@@ -1,0 +1,103 @@
+// The library's host paths when memory is refused: run on the CPU against
+// tests/fake_hip.cpp, one scenario per argument.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "fake_hip.h"
+#include "tfmm.h"
+
+#define CHECK(x)                                                                          \
+    do {                                                                                  \
+        if (!(x)) {                                                                       \
+            std::printf("failed: %s (line %d, %s)\n", #x, __LINE__, fake.what.c_str());   \
+            std::exit(1);                                                                 \
+        }                                                                                 \
+    } while (0)
+
+static double arrays[64];  // stand for the caller's device arrays
+
+struct Size {
+    long n, leaves, levels;
+};
+static const Size kSizes[] = {{900, 30, 2}, {40000, 1500, 5}, {200000, 8000, 8}};
+
+static void shape(const Size& s) {
+    fake.leaves = s.leaves;
+    fake.levels = s.levels;
+    fake.near = 9 * s.leaves;
+    fake.far = 40 * s.leaves;
+}
+static tfmm_ctx* make_ctx() {
+    tfmm_ctx* c = nullptr;
+    CHECK(tfmm_ctx_create(0, 0, &c) == TFMM_OK);
+    return c;
+}
+static tfmm_tree* make_tree(tfmm_ctx* c, const Size& s) {
+    shape(s);
+    tfmm_tree* t = nullptr;
+    int rc;
+    while ((rc = tfmm_build_tree(c, s.n, arrays, arrays + 1, 64, nullptr, &t)) != TFMM_OK) CHECK(rc == TFMM_ENOMEM);
+    return t;
+}
+static void drop(tfmm_tree* t, tfmm_ctx* c) {
+    CHECK(tfmm_tree_destroy(t) == TFMM_OK);
+    CHECK(tfmm_ctx_destroy(c) == TFMM_OK);
+    CHECK(fake_all_gone());
+}
+// Evaluations of every kind; refused: how many may be for lack of memory.  What
+// went well before a refused one goes well after it.
+static void evaluations(tfmm_tree* t, int refused) {
+    tfmm_params last{};
+    for (int variant : {TFMM_STANDARD, TFMM_CONSERVING, TFMM_CONSERVING_R2})
+        for (int p : {1, 2, 6, 4, 8, 5})
+            for (int pot : {0, 1})
+                for (int prec : {TFMM_MIXED32, TFMM_FP64, TFMM_MIXED32}) {
+                    if (variant == TFMM_CONSERVING_R2 && p != 1) continue;
+                    tfmm_params q{p, 0.5, 1e-3, 1.0, variant, prec, 0};
+                    if (variant == TFMM_CONSERVING && p <= 5 && prec == TFMM_FP64) q.scalar_degree = p;
+                    if (pot) q.theta = 0.6;
+                    const int rc = tfmm_evaluate_forces(t, &q, arrays, pot ? arrays + 1 : nullptr, nullptr);
+                    CHECK(rc == TFMM_OK || (rc == TFMM_ENOMEM && refused-- > 0));
+                    if (rc == TFMM_OK) last = q;
+                    else if (last.p) {
+                        const int again = tfmm_evaluate_forces(t, &last, arrays, nullptr, nullptr);
+                        CHECK(again == TFMM_OK || (again == TFMM_ENOMEM && refused-- > 0));
+                    }
+                }
+}
+
+// Every allocation refused in turn; the tree serves on as if nothing had been.
+static void refused_memory() {
+    for (const Size& s : kSizes)
+        for (int overflow : {0, 1}) {
+            long total = 0;
+            for (long k = 0; k <= total; ++k) {
+                tfmm_ctx* c = make_ctx();
+                fake.what = "n " + std::to_string(s.n) + ", allocation " + std::to_string(k) + " refused";
+                fake.overflow = overflow;
+                fake.mallocs = 0;
+                fake.fail_at = k;
+                tfmm_tree* t = make_tree(c, s);
+                evaluations(t, k ? 2 : 0);
+                int rc;
+                while ((rc = tfmm_tree_rebuild(t, s.n + 50, arrays, arrays + 1, nullptr)) != TFMM_OK)
+                    CHECK(rc == TFMM_ENOMEM);
+                evaluations(t, k ? 2 : 0);
+                if (k == 0) total = fake.mallocs;
+                fake.fail_at = 0;
+                drop(t, c);
+            }
+            CHECK(total > 50);
+        }
+}
+
+int main(int, char** argv) {
+    for (const double& x : arrays) fake.user.insert(&x);
+    const std::string what = argv[1];
+    if (what == "refused_memory") refused_memory();
+    else return 2;
+    std::puts("host paths ok");
+    return 0;
+}
