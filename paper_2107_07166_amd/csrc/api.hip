@@ -282,6 +282,7 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     const bool shared_pot = potential && prm->variant == TFMM_STANDARD;
     timing_events(t);
     if (t.timing) fold_times(t);
+    Unfinished work(t, s);
     aux_fork(t, s);
     const hipStream_t a = t.aux;
     moments_room(t, pe);
@@ -292,7 +293,6 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
         if (t.timing) TFMM_HIP(hipEventRecord(t.ev[1], a));
     };
     prepare_sources(t, prm->precision, s);
-    PendingLists pending(t, s);
     // Of the two list chains the one queued second starts late by its sibling's
     // launches.  Up to order 5 and 2^15 nodes the near field is what the end waits
     // for, and its chain goes first: Plummer 2^18 with the potential 1351 -> 1325
@@ -327,6 +327,7 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
     if (t.timing) TFMM_HIP(hipEventRecord(t.ev[4], s));
     run_p2p_reduce(t, potential != nullptr, s);
     aux_join(t, s);
+    work.done = true;
     if (t.timing) TFMM_HIP(hipEventRecord(t.ev[8], s));
     run_l2p(t, pe, ve, prm->G, force, s);
     if (potential)

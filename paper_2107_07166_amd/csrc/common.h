@@ -394,15 +394,21 @@ void aux_join(Tree& t, hipStream_t s);
 void build_far_lists(Tree& t, hipStream_t s);
 void build_near_lists(Tree& t, hipStream_t s);
 void near_lists_end(Tree& t, hipStream_t s);
-// From walk_lists_begin to walk_lists_end the list totals may be on their way
-// to the mailbox; if that stretch is left by an error, they have to arrive
-// before the mailbox serves another read-back.
-struct PendingLists {
+// Stands from the fork of the second stream to its join.  If that stretch is left
+// by an error, both streams are waited for: nothing has joined the second one,
+// and a later rebuild on the caller's stream would overwrite what its kernels
+// read; and the list totals, if they are on their way to the mailbox, have to
+// arrive before it serves another read-back.
+struct Unfinished {
     Tree& t;
     hipStream_t s;
-    PendingLists(Tree& tree, hipStream_t stream) : t(tree), s(stream) { t.list_mb = 0u; }
-    ~PendingLists() {
-        if (t.list_mb) (void)hipStreamSynchronize(s);
+    bool done = false;
+    Unfinished(Tree& tree, hipStream_t stream) : t(tree), s(stream) { t.list_mb = 0u; }
+    ~Unfinished() {
+        if (!done) {
+            if (t.aux) (void)hipStreamSynchronize(t.aux);
+            (void)hipStreamSynchronize(s);
+        }
         t.list_mb = 0u;
     }
 };

@@ -866,10 +866,11 @@ void walk_lists_end(Tree& t, hipStream_t s) {
 }
 
 void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s) {
-    PendingLists pending(t, s);
+    Unfinished work(t, s);
     walk_lists_begin(t, theta, s, nullptr, [] {}, false);
     aux_join(t, s);
     walk_lists_end(t, s);
+    work.done = true;
 }
 
 }  // namespace tfmm

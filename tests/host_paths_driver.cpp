@@ -46,6 +46,14 @@ static void drop(tfmm_tree* t, tfmm_ctx* c) {
     CHECK(tfmm_ctx_destroy(c) == TFMM_OK);
     CHECK(fake_all_gone());
 }
+// After a refused call nothing runs on the tree's own stream any more, which the
+// caller's stream does not wait for.
+static int evaluate(tfmm_tree* t, const tfmm_params& q, double* pot) {
+    const int rc = tfmm_evaluate_forces(t, &q, arrays, pot, nullptr);
+    if (rc != TFMM_OK)
+        for (void* s : fake.busy) CHECK(s == nullptr);
+    return rc;
+}
 // Evaluations of every kind; refused: how many may be for lack of memory.  What
 // went well before a refused one goes well after it.
 static void evaluations(tfmm_tree* t, int refused) {
@@ -58,11 +66,11 @@ static void evaluations(tfmm_tree* t, int refused) {
                     tfmm_params q{p, 0.5, 1e-3, 1.0, variant, prec, 0};
                     if (variant == TFMM_CONSERVING && p <= 5 && prec == TFMM_FP64) q.scalar_degree = p;
                     if (pot) q.theta = 0.6;
-                    const int rc = tfmm_evaluate_forces(t, &q, arrays, pot ? arrays + 1 : nullptr, nullptr);
+                    const int rc = evaluate(t, q, pot ? arrays + 1 : nullptr);
                     CHECK(rc == TFMM_OK || (rc == TFMM_ENOMEM && refused-- > 0));
                     if (rc == TFMM_OK) last = q;
                     else if (last.p) {
-                        const int again = tfmm_evaluate_forces(t, &last, arrays, nullptr, nullptr);
+                        const int again = evaluate(t, last, nullptr);
                         CHECK(again == TFMM_OK || (again == TFMM_ENOMEM && refused-- > 0));
                     }
                 }
