@@ -632,7 +632,9 @@ void launch_seq(Tree& t, const WalkNodes& w, int slot, bool init, int limit, dou
 
 WalkState wait_state(Tree& t, const Mailbox& mb, hipStream_t s) {
     WalkState h;
-    mailbox_wait(t.ctx, mb.seq, sizeof(h), &h, false, s);
+    // with the device error word: after a wait that ran out the pairs are not
+    // all there, and must not be read as lists
+    mailbox_wait(t.ctx, mb.seq, sizeof(h), &h, true, s);
     return h;
 }
 

@@ -101,10 +101,30 @@ static void refused_memory() {
         }
 }
 
+// A walk pass that gave up waiting for another workgroup leaves pairs unwritten:
+// no list is made from them.
+static void wait_ran_out() {
+    for (const Size& s : kSizes)
+        for (int walks : {1, 2}) {  // the first walk, and one sized by the walk before
+            fake.what = "n " + std::to_string(s.n) + ", walk " + std::to_string(walks);
+            tfmm_ctx* c = make_ctx();
+            tfmm_tree* t = make_tree(c, s);
+            if (walks == 2) CHECK(tfmm_tree_walk(t, 0.7, nullptr) == TFMM_OK);
+            fake.list_launches = 0;
+            fake.wait_ran_out = true;
+            const tfmm_params q{4, 0.5, 1e-3, 1.0, TFMM_CONSERVING, TFMM_MIXED32, 0};
+            CHECK(tfmm_evaluate_forces(t, &q, arrays, nullptr, nullptr) == TFMM_EDEVICE);
+            CHECK(fake.list_launches == 0);
+            fake.wait_ran_out = false;
+            drop(t, c);
+        }
+}
+
 int main(int, char** argv) {
     for (const double& x : arrays) fake.user.insert(&x);
     const std::string what = argv[1];
     if (what == "refused_memory") refused_memory();
+    else if (what == "wait_ran_out") wait_ran_out();
     else return 2;
     std::puts("host paths ok");
     return 0;

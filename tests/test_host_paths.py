@@ -1,4 +1,4 @@
-"""The library's host code when things are refused, on the CPU: its host side
+"""The library's host code when something is refused or fails, on the CPU: its host side
 compiled with the address sanitizer and linked with a stand-in for the HIP
 runtime that checks every launch (tests/fake_hip.cpp), driven by
 tests/host_paths_driver.cpp."""
@@ -12,7 +12,7 @@ import pytest
 ROOT = Path(__file__).resolve().parent.parent
 CSRC = ROOT / "paper_2107_07166_amd" / "csrc"
 CLANG = Path("/opt/rocm/llvm/bin/clang++")
-SCENARIOS = ["refused_memory"]
+SCENARIOS = ["refused_memory", "wait_ran_out"]
 
 
 def _run(cmd):
