@@ -6,6 +6,15 @@
 
 namespace tfmm {
 
+// List offsets and entry counts have 32 bits, and loops over the entries step past
+// the last one by less than kListStep: the most pairs whose directed entries (two
+// each) leave room for that.
+constexpr uint32_t kListStep = 1u << 20;
+constexpr int64_t kMaxPairs = (((int64_t)1 << 32) - kListStep) / 2;
+constexpr bool lists_fit(int64_t far_pairs, int64_t near_pairs) {
+    return far_pairs <= kMaxPairs && near_pairs <= kMaxPairs;
+}
+
 // A target leaf's near list is cut before entry q when the number of source
 // particles preceding q in that list crosses a multiple of kItemSources, so no
 // wavefront receives more than about kItemSources sources per target.
@@ -26,6 +35,12 @@ constexpr uint32_t source_step(int32_t count) {
 constexpr uint32_t list_items(const uint32_t* P, uint32_t q0, uint32_t q1) {
     return q1 > q0 ? (P[q1 - 1u] - P[q0]) / kItemSources + 1u : 0u;
 }
+
+// Partial-sum rows of a list of n items (one per item and target particle): only a
+// leaf split into several items needs any.  Offsets into them have 32 bits; the
+// total is kept in 64 to see whether they do.
+constexpr uint64_t item_rows(uint32_t n, int32_t targets) { return n > 1u ? (uint64_t)n * (uint32_t)targets : 0u; }
+constexpr bool rows_fit(uint64_t rows) { return rows <= 0xffffffffull; }
 
 // First entry of item k of the list: the first q with P[q] - P[q0] >= k
 // kItemSources, by binary search.

@@ -49,7 +49,8 @@ struct WalkTotals {
     uint32_t multi;        // leaves split into several near-field items
     uint32_t near_entries; // directed near entries (check of 2 n_near - n_leaves)
     uint32_t items;        // near-field work items
-    uint32_t partial;      // partial-sum rows of multi-item leaves
+    uint32_t partial;      // partial-sum rows of multi-item leaves, mod 2^32
+    unsigned long long rows;  // all of them
     uint32_t scratch[12];  // totals nobody reads
     unsigned long long near_int;
 };
@@ -187,6 +188,7 @@ __global__ __launch_bounds__(NBK) void bucket_starts_kernel(uint32_t* __restrict
         if (res) {
             res->near_entries = all;
             res->multi = 0u;
+            res->rows = 0ull;
         }
     }
 }
@@ -271,6 +273,7 @@ __global__ __launch_bounds__(PB) void bucket_scatter_kernel(const int2* __restri
         if (res) {
             res->near_entries = nvalid;
             res->multi = 0u;
+            res->rows = 0ull;
         }
     }
     __syncthreads();
@@ -296,13 +299,12 @@ struct NearOut {
     uint32_t *P, *nitems, *prows;
 };
 
-// Items of a target leaf's list, and its partial-sum rows (one per item and target
-// particle), which only a leaf split into several items needs.
+// Items and partial-sum rows (mod 2^32) of a target leaf's list.
 __device__ __forceinline__ void leaf_items(const uint32_t* P, uint32_t q0, uint32_t q1, int32_t count, uint32_t* nit,
                                            uint32_t* prw) {
     const uint32_t n = list_items(P, q0, q1);
     *nit = n;
-    *prw = n > 1u ? n * (uint32_t)count : 0u;
+    *prw = (uint32_t)item_rows(n, count);
 }
 
 // One bucket: its targets' lists.  l0[t], l1[t]: the list of target t is src
@@ -319,6 +321,7 @@ constexpr int LTILE = LT * PI;           // entries placed together
 constexpr int kLocalBits = 9;
 constexpr int NLB = 1 << kLocalBits;     // most targets of a bucket
 constexpr int LP = 8;                    // entries per thread of the prefix
+static_assert(LTILE <= (int)kListStep && 8 * LT <= (int)kListStep, "loops over the entries end");
 template <typename Word, bool NEAR>
 __global__ __launch_bounds__(LT) void bucket_lists_kernel(const Word* __restrict__ in,
                                                           const uint32_t* __restrict__ start, Split sp, int nb,
@@ -520,8 +523,9 @@ __global__ __launch_bounds__(TB) void item_write_kernel(const uint32_t* __restri
                                                         int32_t* __restrict__ leaf_item0,
                                                         int32_t* __restrict__ leaf_nitems,
                                                         int32_t* __restrict__ multi_leaf,
-                                                        uint32_t* __restrict__ multi_count) {
+                                                        WalkTotals* __restrict__ res) {
     const uint32_t total = *n_items;
+    // (gridDim.x * TB at most kListStep)
     for (uint32_t i = (uint32_t)(blockIdx.x * TB + threadIdx.x); i < total; i += gridDim.x * TB) {
         int64_t lo = 0, hi = nn - 1;
         while (lo < hi) {
@@ -539,7 +543,10 @@ __global__ __launch_bounds__(TB) void item_write_kernel(const uint32_t* __restri
         if (k == 0u) {
             leaf_item0[L] = (int32_t)item0[L];
             leaf_nitems[L] = (int32_t)n;
-            if (n > 1u) multi_leaf[atomicAdd(multi_count, 1u)] = (int32_t)L;
+            if (n > 1u) {
+                multi_leaf[atomicAdd(&res->multi, 1u)] = (int32_t)L;
+                atomicAdd(&res->rows, (unsigned long long)item_rows(n, count[L]));
+            }
         }
     }
 }
@@ -566,8 +573,12 @@ __global__ __launch_bounds__(SI) void items_small_kernel(const uint32_t* __restr
     __shared__ uint32_t item0[kSmallNodes], pbase[kSmallNodes];
     __shared__ uint32_t wsum[SI / kWave];
     __shared__ uint32_t multi;
+    __shared__ unsigned long long rows;
     const int tid = threadIdx.x;
-    if (tid == 0) multi = 0u;
+    if (tid == 0) {
+        multi = 0u;
+        rows = 0ull;
+    }
     uint32_t a[PER], p[PER], sa = 0u, sb = 0u;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -605,7 +616,10 @@ __global__ __launch_bounds__(SI) void items_small_kernel(const uint32_t* __restr
         if (k == 0u) {
             leaf_item0[lo] = (int32_t)item0[lo];
             leaf_nitems[lo] = (int32_t)n;
-            if (n > 1u) multi_leaf[atomicAdd(&multi, 1u)] = lo;
+            if (n > 1u) {
+                multi_leaf[atomicAdd(&multi, 1u)] = lo;
+                atomicAdd(&rows, (unsigned long long)item_rows(n, count[lo]));
+            }
         }
     }
     __syncthreads();
@@ -613,6 +627,7 @@ __global__ __launch_bounds__(SI) void items_small_kernel(const uint32_t* __restr
         tot->multi = multi;
         tot->items = n_items;
         tot->partial = n_rows;
+        tot->rows = rows;
     }
     __syncthreads();
     mailbox_write(mb, tot, (int)(offsetof(WalkTotals, scratch) / 4));
@@ -763,6 +778,9 @@ void build_near_lists(Tree& t, hipStream_t s) {
         hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(TB), 0, s, reinterpret_cast<int32_t*>(&res->multi),
                            (int64_t)1, 0);
         TFMM_LAUNCHED();
+        hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(TB), 0, s, reinterpret_cast<int32_t*>(&res->rows),
+                           (int64_t)2, 0);
+        TFMM_LAUNCHED();
         hipLaunchKernelGGL(node_items_kernel, dim3(grid(nn)), dim3(TB), 0, s, (const uint32_t*)l0, (const uint32_t*)P,
                            nn, t.nd_count.as<int32_t>(), nit, prw);
         TFMM_LAUNCHED();
@@ -796,7 +814,7 @@ void build_near_lists(Tree& t, hipStream_t s) {
                        (const uint32_t*)it0, (const uint32_t*)&res->items, (const uint32_t*)pbs,
                        t.nd_count.as<int32_t>(), t.it_leaf.as<int32_t>(), t.it_q0.as<uint32_t>(),
                        t.it_q1.as<uint32_t>(), t.it_pbase.as<uint32_t>(), t.leaf_item0.as<int32_t>(),
-                       t.leaf_nitems.as<int32_t>(), t.multi_leaf.as<int32_t>(), &res->multi);
+                       t.leaf_nitems.as<int32_t>(), t.multi_leaf.as<int32_t>(), res);
     TFMM_LAUNCHED();
 }
 
@@ -811,6 +829,8 @@ void near_lists_end(Tree& t, hipStream_t s) {
     if ((int64_t)h.near_entries != ne)
         fail(TFMM_EDEVICE, "walk: near entry count " + std::to_string(h.near_entries) + " differs from " +
                                std::to_string(ne));
+    if (!rows_fit(h.rows))
+        fail(TFMM_ENOMEM, "near field: " + std::to_string(h.rows) + " partial sums exceed 2^32 - 1");
     t.n_near_int = -1;  // counted on request (near_interactions)
     t.n_items = h.items;
     t.n_partial = h.partial;

@@ -27,6 +27,7 @@
 #include <cmath>
 
 #include "common.h"
+#include "list_math.h"
 
 namespace tfmm {
 namespace {
@@ -852,6 +853,9 @@ void walk_lists_begin(Tree& t, const std::vector<double>& theta_in, hipStream_t 
     t.walk_hint_far = t.n_m2l;
     t.walk_hint_near = t.n_p2p;
     if (passes_done) TFMM_HIP(hipEventRecord(passes_done, s));
+    if (!lists_fit(t.n_m2l, t.n_p2p))
+        fail(TFMM_ENOMEM, "walk: " + std::to_string(t.n_m2l) + " far and " + std::to_string(t.n_p2p) +
+                              " near pairs exceed the lists' 32-bit offsets");
 
     // The far-list chain runs on the tree's second stream, the near-list chain
     // on s; they share no buffer.

@@ -66,6 +66,11 @@ struct State {
     Slot slot[2];
     uint32_t overflow, passes, max_nf, pad, nf_pass[64];
 };
+struct Totals {
+    uint32_t multi, near_entries, items, partial;
+    unsigned long long rows;
+};
+bool sized_pass = false;  // a host-sized walk pass waits for its totals
 void post(const Mailbox& m, const void* src, size_t bytes) {
     std::memcpy(m.box + kBoxHeaderWords, src, bytes);
     m.box[1] = *m.err;
@@ -103,18 +108,21 @@ void answer(const std::string& n, void** a) {
             post(m, &s, sizeof s);
         }
     } else if (has(n, "items_small_kernel")) {
-        const uint32_t t[4] = {0u, (uint32_t)(2 * fake.near - fake.leaves), (uint32_t)fake.leaves, 0u};
-        post(*(Mailbox*)a[15], t, sizeof t);
+        const Totals t{0u, (uint32_t)(2 * fake.near - fake.leaves), (uint32_t)fake.leaves, 0u, fake.rows};
+        post(*(Mailbox*)a[15], &t, sizeof t);
     } else if (has(n, "walk_count_kernel")) {
         ++fake.sized_passes;
+        sized_pass = true;
     } else if (has(n, "mailbox_kernel")) {
         const int nw = *(int*)a[2];
         std::vector<uint32_t> v((size_t)nw, 0u);
-        if (nw == 4) {  // the list totals
-            v = {1u, (uint32_t)(2 * fake.near - fake.leaves), (uint32_t)fake.leaves + 3u, 100u};
-        } else if (nw == 6) {  // a host-sized pass: the first one gives every pair
+        if (sized_pass) {  // the first one gives every pair
             const unsigned long long t[3] = {0ull, (unsigned long long)fake.far, (unsigned long long)fake.near};
             std::memcpy(v.data(), t, sizeof t);
+            sized_pass = false;
+        } else if (nw == (int)sizeof(Totals) / 4) {
+            const Totals t{1u, (uint32_t)(2 * fake.near - fake.leaves), (uint32_t)fake.leaves + 3u, 100u, fake.rows};
+            std::memcpy(v.data(), &t, sizeof t);
         }
         post(*(Mailbox*)a[0], v.data(), (size_t)nw * 4);
     } else if (has(n, "p2m_kernel")) {
@@ -125,6 +133,7 @@ void answer(const std::string& n, void** a) {
         if (has(n, "m2l_kernel") && *(int64_t*)a[5] != round_up(c_le(moments[W]), 4)) die("M2L with moments of order " + std::to_string(moments[W]));
         if (has(n, "cons_pass") && moments[W] != order_of(n)) die("M2L with moments of order " + std::to_string(moments[W]));
     }
+    if (has(n, "p2p_")) ++fake.near_launches;
     if (has(n, "bucket_") || has(n, "radix_hist") || has(n, "p2p_")) ++fake.list_launches;
 }
 

@@ -120,11 +120,52 @@ static void wait_ran_out() {
         }
 }
 
+// Pairs whose directed entries do not fit 32-bit offsets: refused before any list
+// is made from them.
+static void too_many_pairs() {
+    for (int near : {0, 1})
+        for (long pairs : {2147483648L, 4294967297L}) {
+            fake.what = (near ? "near " : "far ") + std::to_string(pairs);
+            tfmm_ctx* c = make_ctx();
+            tfmm_tree* t = make_tree(c, kSizes[1]);
+            (near ? fake.near : fake.far) = pairs;
+            fake.list_launches = 0;
+            const tfmm_params q{4, 0.5, 1e-3, 1.0, TFMM_CONSERVING, TFMM_MIXED32, 0};
+            CHECK(tfmm_evaluate_forces(t, &q, arrays, nullptr, nullptr) == TFMM_ENOMEM);
+            CHECK(fake.list_launches == 0);
+            CHECK(tfmm_tree_walk(t, 0.5, nullptr) == TFMM_ENOMEM);
+            shape(kSizes[1]);
+            CHECK(tfmm_evaluate_forces(t, &q, arrays, nullptr, nullptr) == TFMM_OK);
+            drop(t, c);
+        }
+}
+
+// More partial sums than 32-bit offsets reach: refused before the near field.
+static void too_many_rows() {
+    for (const Size& s : kSizes)
+        for (unsigned long long rows : {4294967295ull, 4294967296ull, 1ull << 40}) {
+            fake.what = "n " + std::to_string(s.n) + ", rows " + std::to_string(rows);
+            tfmm_ctx* c = make_ctx();
+            tfmm_tree* t = make_tree(c, s);
+            fake.rows = rows;
+            fake.near_launches = 0;
+            const tfmm_params q{4, 0.5, 1e-3, 1.0, TFMM_CONSERVING, TFMM_MIXED32, 0};
+            const bool fits = rows <= 4294967295ull;
+            CHECK(tfmm_evaluate_forces(t, &q, arrays, nullptr, nullptr) == (fits ? TFMM_OK : TFMM_ENOMEM));
+            CHECK((fake.near_launches > 0) == fits);
+            fake.rows = 0;
+            CHECK(tfmm_evaluate_forces(t, &q, arrays, nullptr, nullptr) == TFMM_OK);
+            drop(t, c);
+        }
+}
+
 int main(int, char** argv) {
     for (const double& x : arrays) fake.user.insert(&x);
     const std::string what = argv[1];
     if (what == "refused_memory") refused_memory();
     else if (what == "wait_ran_out") wait_ran_out();
+    else if (what == "too_many_pairs") too_many_pairs();
+    else if (what == "too_many_rows") too_many_rows();
     else return 2;
     std::puts("host paths ok");
     return 0;

@@ -48,6 +48,13 @@ int main() {
     // as many particles as an ordinary leaf may hold: the count itself
     CHECK(source_step(1) == 1u && source_step(4095) == 4095u && source_step(4096) == 4096u);
     CHECK(source_step(4097) == 4096u && source_step(1 << 30) == 4096u);
+    // the directed entries of the most pairs, and a loop's last step past them
+    CHECK(lists_fit(0, 0) && lists_fit(kMaxPairs, kMaxPairs));
+    CHECK(!lists_fit(kMaxPairs + 1, 0) && !lists_fit(0, kMaxPairs + 1) && !lists_fit((int64_t)1 << 31, 0));
+    CHECK(2ull * kMaxPairs + (kListStep - 1u) <= 0xffffffffull);
+    CHECK(item_rows(0, 64) == 0 && item_rows(1, 64) == 0 && item_rows(3, 64) == 192);
+    CHECK(item_rows(1u << 20, 1 << 30) == 1ull << 50);
+    CHECK(rows_fit(0) && rows_fit(4294967295ull) && !rows_fit(4294967296ull) && !rows_fit(1ull << 50));
     std::mt19937 rng(1);
     std::vector<std::vector<int32_t>> lists = {{}, {1}, {4096}, {1000000}, {1, 1000000, 1}, {1000000, 1000000},
                                                {4, 4, 4, 1000000, 4, 4, 4}, std::vector<int32_t>(5000, 5000)};
