@@ -438,8 +438,9 @@ void l2p_staged_kernel(int64_t n, const double4* __restrict__ Xm, const int32_t*
 
 // Potential output: phi_a = sum_{|j| <= p} L_j x^j / j! (standard locals with
 // L_0, of the same node pairs) + the near-field sum, less the particle's own
-// term -m_a / eps that the near-field kernel includes when eps > 0 (removed
-// in the precision it was added in); pot[a] = G phi_a in caller order.
+// term -m_a / eps that the near-field kernel includes when eps > 0 (removed by
+// the operations that it was added by, so that nothing of it is left);
+// pot[a] = G phi_a in caller order.
 template <int P, typename TS>
 __global__ __launch_bounds__(LB) void l2p_pot_kernel(int64_t n, const double4* __restrict__ Xm,
                                                      const int32_t* __restrict__ leaf_of,
@@ -456,8 +457,9 @@ __global__ __launch_bounds__(LB) void l2p_pot_kernel(int64_t n, const double4* _
     const double4 z = Z[leaf];
     double phi = E::l2p_pot(loc_leaf + (int64_t)leaf * E::NC, x.x - z.x, x.y - z.y, x.z - z.z) + near_pot[j];
     if (eps2 > 0.0) {
-        if constexpr (sizeof(TS) == 4) phi += (double)((float)x.w * __builtin_amdgcn_rsqf((float)eps2));
-        else phi += x.w * rsqrt_refined(eps2);
+        TS own = TS(0);
+        (void)weight<true>((TS)eps2, (TS)x.w, own);
+        phi += (double)own;
     }
     pot[perm[j]] = G * phi;
 }
