@@ -43,6 +43,18 @@ void DevBuf::ensure_keep(Ctx* c, size_t bytes, hipStream_t s) {
     cap = got;
 }
 
+void DevBuf::fit(size_t bytes, hipStream_t s) {
+    const size_t want = (size_t)round_up((int64_t)std::max<size_t>(bytes, 16), 256);
+    if (cap <= 2 * want) return;
+    size_t got = 0;
+    void* q = ctx->alloc(want, &got);
+    TFMM_HIP(hipMemcpyAsync(q, p, want, hipMemcpyDeviceToDevice, s));
+    TFMM_HIP(hipStreamSynchronize(s));
+    release();
+    p = q;
+    cap = got;
+}
+
 // A cached block of size in [bytes, 2 bytes] is reused as is; otherwise new
 // memory, after giving the cache back if the budget or the device is short.
 void* Ctx::alloc(size_t bytes, size_t* got) {
@@ -223,6 +235,10 @@ void timing_events(Tree& t) {
     }
 }
 
+void build(Tree& t, const double* pos, const double* mass, hipStream_t s) {
+    within_memory(t, [&] { build_tree(t, pos, mass, s); });
+}
+
 // Rebuilds t for n particles, the sets of a forest if offsets is given.  If that
 // fails the tree has its former sizes again, which are those that the caller's
 // arrays still have, and is not built.
@@ -240,7 +256,7 @@ void rebuild(Tree& t, int64_t n, int n_sets, const int64_t* offsets, const doubl
         t.n = n;
         t.n_sets = 1;
         if (offsets) set_sets(t, n_sets, offsets, s);
-        build_tree(t, pos, mass, s);
+        build(t, pos, mass, s);
     } catch (...) {
         t.n = n_before;
         t.n_sets = sets_before;
@@ -258,8 +274,8 @@ void check_built(const Tree& t) {
 
 // theta_sets: one theta per set of a forest (host), or nullptr for
 // params->theta everywhere.
-void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double* force, double* potential,
-              hipStream_t s) {
+void evaluate_once(Tree& t, const tfmm_params* prm, const double* theta_sets, double* force, double* potential,
+                   hipStream_t s) {
     const std::vector<double> theta =
         theta_sets ? std::vector<double>(theta_sets, theta_sets + t.n_sets) : std::vector<double>{prm->theta};
     const bool need_walk = !t.walk_valid || t.walk_theta != theta;
@@ -338,6 +354,11 @@ void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double*
         t.ev_pending = true;
         t.ev_walked = need_walk;
     }
+}
+
+void evaluate(Tree& t, const tfmm_params* prm, const double* theta_sets, double* force, double* potential,
+              hipStream_t s) {
+    within_memory(t, [&] { evaluate_once(t, prm, theta_sets, force, potential, s); });
 }
 
 }  // namespace
@@ -529,7 +550,7 @@ int tfmm_tree_walk(tfmm_tree* tree, double theta, void* stream) {
         if (!(theta >= 0.0) || !(theta < 1.0)) fail(TFMM_EINVAL, "theta must satisfy 0 <= theta < 1");
         check_built(*tree);
         set_device(tree->ctx);
-        walk_tree(*tree, std::vector<double>{theta}, (hipStream_t)stream);
+        within_memory(*tree, [&] { walk_tree(*tree, std::vector<double>{theta}, (hipStream_t)stream); });
     });
 }
 
@@ -573,12 +594,12 @@ int tfmm_leapfrog(tfmm_tree* tree, const tfmm_params* params, double* pos, doubl
         Tree& t = *tree;
         const hipStream_t s = (hipStream_t)stream;
         if (!force_valid) {
-            build_tree(t, pos, mass, s);
+            build(t, pos, mass, s);
             evaluate(t, params, nullptr, force, nullptr, s);
         }
         for (int k = 0; k < nsteps; ++k) {
             run_kick_drift(t.n, pos, vel, force, mass, dt, k > 0, s);  // with the kick that ends step k - 1
-            build_tree(t, pos, mass, s);
+            build(t, pos, mass, s);
             evaluate(t, params, nullptr, force, nullptr, s);
         }
         if (nsteps > 0) run_kick(t.n, vel, force, mass, 0.5 * dt, s);

@@ -52,6 +52,7 @@ struct DevBuf {
     ~DevBuf();
     void ensure(Ctx* c, size_t bytes);                 // contents not preserved
     void ensure_keep(Ctx* c, size_t bytes, hipStream_t s);  // contents preserved (async copy)
+    void fit(size_t bytes, hipStream_t s);  // give back what exceeds twice bytes; the first bytes preserved
     void release();
     template <typename T> T* as() const { return static_cast<T*>(p); }
 };
@@ -261,6 +262,8 @@ struct Tree {
     // passes that run without host synchronisation; 0 = none yet)
     int64_t walk_hint_fr = 0, walk_hint_far = 0, walk_hint_near = 0;
     std::vector<int64_t> walk_hint_nf;  // frontier entries of every pass
+    bool walk_estimated = false;  // the walk's buffers have the size estimated for a first walk
+    bool walk_sized = false;      // the estimate did not fit: a first walk is sized on the host
     // near-field work items: a target leaf's list cut into pieces of bounded
     // source count, each run by one wavefront into its own partial sums
     int64_t n_items = 0, n_partial = 0;
@@ -402,6 +405,22 @@ void walk_tree(Tree& t, const std::vector<double>& theta, hipStream_t s);
 void walk_lists_begin(Tree& t, const std::vector<double>& theta, hipStream_t s, hipEvent_t passes_done,
                       const std::function<void()>& meanwhile, bool near_first);
 void walk_lists_end(Tree& t, hipStream_t s);
+// Gives the walk's buffers back, and with them the walk.
+void drop_walk_room(Tree& t);
+// Runs f, and if it is refused memory while the tree holds the estimated room of a
+// first walk, once more without that room: the estimate may be several times the
+// need, and must not refuse what a walk sized as it goes leaves room for.
+template <typename F>
+void within_memory(Tree& t, F&& f) {
+    try {
+        f();
+        return;
+    } catch (const Error& e) {
+        if (e.code != TFMM_ENOMEM || !t.walk_estimated) throw;
+    }
+    drop_walk_room(t);
+    f();
+}
 void aux_fork(Tree& t, hipStream_t s);
 void aux_join(Tree& t, hipStream_t s);
 void build_far_lists(Tree& t, hipStream_t s);

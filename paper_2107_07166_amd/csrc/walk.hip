@@ -732,7 +732,8 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
 // entries per node grow like (1 + 2 / theta)^3, the volume within 1 / theta
 // cell sizes (ball, Plummer and disk sets of 10^3 to 10^6 particles, theta 0.2 to
 // 0.95: far up to 1.6, near up to 0.75, frontier up to about 0.05 of it per
-// node).  A walk that needs more runs the host-sized passes.
+// node).  A walk that needs more runs the host-sized passes, and so does one for
+// which the estimate does not fit the memory there is.
 void first_room(const Tree& t, const std::vector<double>& theta, int64_t& fr, int64_t& far, int64_t& near) {
     const double th = std::max(*std::min_element(theta.begin(), theta.end()), 0.05);
     const double around = (1.0 + 2.0 / th) * (1.0 + 2.0 / th) * (1.0 + 2.0 / th);
@@ -740,6 +741,20 @@ void first_room(const Tree& t, const std::vector<double>& theta, int64_t& fr, in
     far = (int64_t)std::min(all, nn * std::min(1.65 * around, 400.0)) + 4096;
     near = (int64_t)std::min(all, nn * std::min(0.75 * around + 8.0, 160.0)) + 4096;
     fr = (int64_t)std::min(all, nn * std::min(0.06 * around + 2.0, 32.0)) + 4096 + t.n_sets;
+}
+
+// Under a budget the surplus of a first walk's estimate goes back to the context,
+// where other trees may need it.  If there is no memory for that, it stays.
+void fit_room(Tree& t, hipStream_t s) {
+    try {
+        const size_t fr = (size_t)(t.walk_hint_fr + t.walk_hint_fr / 4 + 4096);
+        for (DevBuf* b : {&t.w_fr, &t.w_fr2, &t.w_dec}) b->fit(fr * 8, s);
+        t.m2l_pairs.fit((size_t)t.n_m2l * 8, s);
+        t.p2p_pairs.fit((size_t)t.n_p2p * 8, s);
+        t.walk_estimated = false;
+    } catch (const Error& e) {
+        if (e.code != TFMM_ENOMEM) throw;
+    }
 }
 
 // Frontier passes with no host synchronisation, sized from the previous walk
@@ -761,18 +776,26 @@ bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thet
         want_far = t.walk_hint_far + t.walk_hint_far / 4 + 4096;
         want_near = t.walk_hint_near + t.walk_hint_near / 4 + 4096;
     } else {
+        if (t.walk_sized) return false;
         first_room(t, thetas, want_fr, want_far, want_near);
         const int64_t bytes = 8 * (4 * want_fr + want_far + want_near);
         if (ctx->budget && ctx->used - ctx->cached + (size_t)bytes > ctx->budget / 2) return false;
     }
     if (want_fr > (int64_t)UINT32_MAX) return false;
-    t.w_fr.ensure(ctx, (size_t)want_fr * 8);
-    t.w_fr2.ensure(ctx, (size_t)want_fr * 8);
-    t.w_dec.ensure(ctx, (size_t)want_fr * kRun);
-    t.m2l_pairs.ensure(ctx, (size_t)want_far * 8);
-    t.p2p_pairs.ensure(ctx, (size_t)want_near * 8);
     t.w_state.ensure(ctx, sizeof(WalkState));
     t.w_sync.ensure(ctx, sizeof(PassSync));
+    try {
+        t.w_fr.ensure(ctx, (size_t)want_fr * 8);
+        t.w_fr2.ensure(ctx, (size_t)want_fr * 8);
+        t.w_dec.ensure(ctx, (size_t)want_fr * kRun);
+        t.m2l_pairs.ensure(ctx, (size_t)want_far * 8);
+        t.p2p_pairs.ensure(ctx, (size_t)want_near * 8);
+    } catch (const Error& e) {
+        if (known || e.code != TFMM_ENOMEM) throw;
+        drop_walk_room(t);
+        return false;
+    }
+    if (!known) t.walk_estimated = true;
     int slot = 0;
     // larger passes of the previous walk: from the first above the limit to the last
     int a = 0, b = (int)t.walk_hint_nf.size();
@@ -804,10 +827,18 @@ bool walk_bfs_async(Tree& t, const WalkNodes& w, const std::vector<double>& thet
     t.n_p2p = (int64_t)h.slot[slot].n_near;
     t.walk_hint_fr = h.max_nf;
     t.walk_hint_nf.assign(h.nf_pass, h.nf_pass + std::min<uint32_t>(h.passes, (uint32_t)kMaxPasses));
+    if (t.walk_estimated && ctx->budget) fit_room(t, s);
     return true;
 }
 
 }  // namespace
+
+void drop_walk_room(Tree& t) {
+    for (DevBuf* b : {&t.w_fr, &t.w_fr2, &t.w_dec, &t.m2l_pairs, &t.p2p_pairs}) b->release();
+    t.walk_valid = false;
+    t.walk_estimated = false;
+    t.walk_sized = true;
+}
 
 // Fork the tree's second stream from s / join it back into s.
 void aux_fork(Tree& t, hipStream_t s) {

@@ -159,6 +159,73 @@ static void too_many_rows() {
         }
 }
 
+// What fits with a walk that takes its room as it goes is not refused for the
+// larger room that is estimated for a first walk.
+static void first_walk_memory() {
+    for (const Size& s : {kSizes[1], kSizes[2]}) {
+        tfmm_params q{8, 0.5, 1e-3, 1.0, TFMM_CONSERVING, TFMM_FP64, 0};
+        // the bytes of a solve with the estimate, and of one without
+        auto solve = [&](size_t budget, size_t limit, bool must) {
+            fake.what = "n " + std::to_string(s.n) + ", p " + std::to_string(q.p) + ", budget " +
+                        std::to_string(budget) + ", device " + std::to_string(limit);
+            tfmm_ctx* c = make_ctx();
+            CHECK(tfmm_ctx_set_budget(c, budget) == TFMM_OK);
+            fake.limit = limit;
+            fake.sized_passes = 0;
+            shape(s);
+            tfmm_tree* t = nullptr;
+            int rc = tfmm_build_tree(c, s.n, arrays, arrays + 1, 64, nullptr, &t);
+            if (rc == TFMM_OK) rc = evaluate(t, q, nullptr);
+            CHECK(rc == TFMM_OK || (rc == TFMM_ENOMEM && !must));
+            const size_t held = rc == TFMM_OK ? tfmm_ctx_bytes_in_use(c) : 0;
+            fake.limit = 0;
+            drop(t, c);
+            return held;
+        };
+        for (int p : {2, 6, 8}) {
+            q.p = p;
+            const size_t estimated = solve(0, 0, true);
+            CHECK(fake.sized_passes == 0);
+            size_t sized = 0;  // the least that a budget admits
+            for (size_t b = estimated / 8; !sized; b += b / 50) sized = solve(b, 0, false) ? b : 0;
+            CHECK(sized < estimated && (p > 2 || fake.sized_passes > 0));
+            for (size_t b = sized; b < 3 * estimated; b += b / 25) solve(b, 0, true);
+            for (size_t d = sized + sized / 50; d < 2 * estimated; d += d / 25) solve(0, d, true);
+        }
+        // a second tree finds what the first one's estimate left over
+        fake.what = "two trees";
+        const size_t sized = [&] {
+            for (size_t b = 1 << 20;; b += b / 50)
+                if (solve(b, 0, false)) return b;
+        }();
+        tfmm_ctx* c = make_ctx();
+        CHECK(tfmm_ctx_set_budget(c, 4 * sized) == TFMM_OK);
+        std::vector<tfmm_tree*> trees;
+        for (int k = 0; k < 3; ++k) {
+            trees.push_back(nullptr);
+            CHECK(tfmm_build_tree(c, s.n, arrays, arrays + 1, 64, nullptr, &trees.back()) == TFMM_OK);
+            CHECK(evaluate(trees.back(), q, nullptr) == TFMM_OK);
+        }
+        for (tfmm_tree* t : trees) CHECK(tfmm_tree_destroy(t) == TFMM_OK);
+        CHECK(tfmm_ctx_destroy(c) == TFMM_OK);
+        // a walked tree that needs more later, on a device that is full by then
+        fake.what = "later";
+        c = make_ctx();
+        tfmm_tree* t = make_tree(c, s);
+        q.p = 1;
+        CHECK(evaluate(t, q, nullptr) == TFMM_OK);
+        CHECK(tfmm_ctx_trim(c) == TFMM_OK);
+        fake.limit = fake.bytes;
+        q.p = 3;
+        CHECK(evaluate(t, q, nullptr) == TFMM_OK);
+        int64_t info[8];
+        CHECK(tfmm_tree_info(t, info) == TFMM_OK && info[4] == fake.far && info[5] == fake.near);
+        CHECK(tfmm_tree_rebuild(t, s.n + s.n / 10, arrays, arrays + 1, nullptr) == TFMM_OK);
+        fake.limit = 0;
+        drop(t, c);
+    }
+}
+
 int main(int, char** argv) {
     for (const double& x : arrays) fake.user.insert(&x);
     const std::string what = argv[1];
@@ -166,6 +233,7 @@ int main(int, char** argv) {
     else if (what == "wait_ran_out") wait_ran_out();
     else if (what == "too_many_pairs") too_many_pairs();
     else if (what == "too_many_rows") too_many_rows();
+    else if (what == "first_walk_memory") first_walk_memory();
     else return 2;
     std::puts("host paths ok");
     return 0;
