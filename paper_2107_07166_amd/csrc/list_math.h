@@ -6,6 +6,16 @@
 
 namespace tfmm {
 
+// The workgroups of a walk pass in one launch, at most kPassGrid, hand their output
+// counts on in words of kCountBits bits per kind.  A workgroup takes up to nf /
+// kPassGrid + 8 of the pass's nf entries, and an entry gives at most 15 outputs of a
+// kind (seven pairs of its run split, and one self pair with eight children), so
+// the counts of up to kPassMax entries fit whatever becomes of them.  Larger passes
+// run in two launches.
+constexpr int kPassGrid = 256;
+constexpr int kCountBits = 20;
+constexpr int64_t kPassMax = (int64_t)kPassGrid << (kCountBits - 4);
+
 // List offsets and entry counts have 32 bits, and loops over the entries step past
 // the last one by less than kListStep: the most pairs whose directed entries (two
 // each) leave room for that.

@@ -204,13 +204,10 @@ struct WalkOut {
 };
 constexpr int kWalkGrid = 1024;
 
-constexpr int kPassGrid = 256;  // most workgroups of a pass in one launch
-
 // What the workgroups of a pass tell each other, per slot (a pass uses its own
 // and clears the other's): start tickets, and the output counts of every
-// workgroup in one word (20 bits each of next, far and near; bit 63 set, bit 62
+// workgroup in one word (kCountBits each of next, far and near; bit 63 set, bit 62
 // if a count does not fit).
-constexpr int kCountBits = 20;
 struct PassSync {
     unsigned long long counts[2][kPassGrid];
     uint32_t ticket[2];
@@ -498,8 +495,8 @@ __global__ __launch_bounds__(PT) void walk_pass_kernel(WalkNodes w, WalkOut o, W
     }
 }
 
-// The same in two launches, between which the host sizes the outputs
-// (walk_bfs_sized): the counting kernel decides every pair, stores the decision
+// The same in two launches, for passes of more than kPassMax entries and where the
+// host sizes the outputs in between (walk_bfs_sized): the counting kernel decides every pair, stores the decision
 // and the block's output counts; the emitting kernel adds the totals of the
 // blocks before it and writes the outputs.  Block b of a pass takes a contiguous
 // range of tiles of TB / kRun entries.
@@ -552,10 +549,15 @@ __global__ __launch_bounds__(TB) void walk_total_kernel(const U3L* __restrict__ 
 // offset), so no scan launch sits between counting and emitting.
 __global__ __launch_bounds__(TB) void walk_emit_kernel(WalkNodes w, WalkOut o, WalkState* __restrict__ st, int slot,
                                                        const int8_t* __restrict__ dec,
-                                                       const U3L* __restrict__ bsum) {
+                                                       const U3L* __restrict__ bsum,
+                                                       PassSync* __restrict__ sync) {
     constexpr int NW = TB / kWave;
     __shared__ U3L wsum[NW];
     __shared__ U3 wtot[2][NW];
+    if (blockIdx.x == 0) {  // for the next pass, as in one launch
+        for (int j = threadIdx.x; j < kPassGrid; j += TB) sync->counts[slot ^ 1][j] = 0ull;
+        if (threadIdx.x == 0) sync->ticket[slot ^ 1] = 0u;
+    }
     const WalkSlot s = st->slot[slot];
     const uint32_t nf = st->overflow ? 0u : s.nf;
     if (nf == 0u) {
@@ -645,8 +647,21 @@ WalkState wait_state(Tree& t, const Mailbox& mb, hipStream_t s) {
 // 2000 entries take 6.4 to 7 us with 256 threads, 7 to 7.5 with 512 and 9 to 10
 // with 1024; of 15000 entries 11 to 15, 10 to 11 and 10.5 to 11; of 5e5 43, 37
 // and 33 (the workgroups' tickets and counts are in one another's way: 1024
-// workgroups take 24 us for any pass).
+// workgroups take 24 us for any pass).  Past kPassMax entries, whose counts one
+// launch could not hand on, two launches.
 void launch_pass(Tree& t, const WalkNodes& w, int slot, int64_t expect, double theta, hipStream_t s) {
+    if (expect > kPassMax) {
+        t.w_off.ensure(t.ctx, (size_t)kWalkGrid * sizeof(U3L));
+        hipLaunchKernelGGL(walk_count_kernel, dim3(kWalkGrid), dim3(TB), 0, s, w, walk_out(t),
+                           (const WalkState*)t.w_state.as<WalkState>(), slot, theta, t.w_dec.as<int8_t>(),
+                           t.w_off.as<U3L>());
+        TFMM_LAUNCHED();
+        hipLaunchKernelGGL(walk_emit_kernel, dim3(kWalkGrid), dim3(TB), 0, s, w, walk_out(t),
+                           t.w_state.as<WalkState>(), slot, (const int8_t*)t.w_dec.as<int8_t>(),
+                           (const U3L*)t.w_off.as<U3L>(), t.w_sync.as<PassSync>());
+        TFMM_LAUNCHED();
+        return;
+    }
     auto run = [&](auto kern, int threads) {
         const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(kPassGrid, cdiv(expect, threads / kRun)));
         hipLaunchKernelGGL(kern, dim3(g), dim3(threads), 0, s, w, walk_out(t), t.w_state.as<WalkState>(), slot, theta,
@@ -712,7 +727,8 @@ void walk_bfs_sized(Tree& t, const WalkNodes& w, double theta, hipStream_t s) {
         WalkOut o = walk_out(t);
         o.cap_next = std::min<size_t>(nxt.cap / 8, UINT32_MAX);  // the decisions grow before the next count
         hipLaunchKernelGGL(walk_emit_kernel, dim3(g), dim3(TB), 0, s, w, o, st, slot,
-                           (const int8_t*)t.w_dec.as<int8_t>(), (const U3L*)t.w_off.as<U3L>());
+                           (const int8_t*)t.w_dec.as<int8_t>(), (const U3L*)t.w_off.as<U3L>(),
+                           t.w_sync.as<PassSync>());
         TFMM_LAUNCHED();
         n_far += (int64_t)T.b;
         n_near += (int64_t)T.c;

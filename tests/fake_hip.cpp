@@ -98,8 +98,8 @@ void answer(const std::string& n, void** a) {
         State s{};
         s.slot[slot ^ 1] = {0, 0, (unsigned long long)fake.far, (unsigned long long)fake.near};
         s.passes = 5;
-        s.max_nf = 3000;
-        for (int k = 0; k < 5; ++k) s.nf_pass[k] = k == 2 ? 3000 : 100;
+        s.max_nf = (uint32_t)fake.pass_entries;
+        for (int k = 0; k < 5; ++k) s.nf_pass[k] = k == 2 ? s.max_nf : 100;
         s.overflow = fake.overflow > 0;
         std::memcpy(*(void**)a[2], &s, sizeof s);
         if (m.box) {
@@ -110,7 +110,11 @@ void answer(const std::string& n, void** a) {
     } else if (has(n, "items_small_kernel")) {
         const Totals t{0u, (uint32_t)(2 * fake.near - fake.leaves), (uint32_t)fake.leaves, 0u, fake.rows};
         post(*(Mailbox*)a[15], &t, sizeof t);
-    } else if (has(n, "walk_count_kernel")) {
+    } else if (has(n, "walk_pass_kernel")) {
+        ++fake.pass_launches;
+    } else if (has(n, "walk_emit_kernel")) {
+        ++fake.emit_launches;
+    } else if (has(n, "walk_total_kernel")) {
         ++fake.sized_passes;
         sized_pass = true;
     } else if (has(n, "mailbox_kernel")) {

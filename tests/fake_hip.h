@@ -17,6 +17,7 @@ struct FakeHip {
     long leaves = 0, levels = 1, far = 0, near = 0;
     unsigned long long rows = 0;   // partial sums of the near field
     bool nonfinite = false;        // the positions hold a value that is not finite
+    long pass_entries = 3000;      // the walk's largest frontier
     int overflow = 0;              // unsynchronised walks still to run out of room
     bool wait_ran_out = false;     // a walk pass sets the device error word
     // memory: allocations so far; the fail_at-th and the next one fail (0: none)
@@ -24,7 +25,8 @@ struct FakeHip {
     size_t bytes = 0;              // device bytes allocated
     size_t limit = 0;              // the device's size (0: no limit)
     // what was launched
-    long launches = 0, list_launches = 0, near_launches = 0, sized_passes = 0;
+    long launches = 0, list_launches = 0, near_launches = 0;
+    long sized_passes = 0, emit_launches = 0, pass_launches = 0;  // walk passes by kind
     std::set<void*> busy;          // streams with work nobody has waited for
 };
 extern FakeHip fake;

@@ -226,6 +226,24 @@ static void first_walk_memory() {
     }
 }
 
+// A walk's passes by their size: one launch up to 2^24 entries, two beyond, and
+// neither waits for the host.
+static void pass_sizes() {
+    for (long entries : {2000L, 13421721L, 13421725L, 40000000L}) {  // a quarter more is expected
+        fake.what = std::to_string(entries) + " entries";
+        tfmm_ctx* c = make_ctx();
+        tfmm_tree* t = make_tree(c, kSizes[1]);
+        fake.pass_entries = entries;
+        CHECK(tfmm_tree_walk(t, 0.5, nullptr) == TFMM_OK);
+        fake.pass_launches = fake.emit_launches = fake.sized_passes = 0;
+        CHECK(tfmm_tree_walk(t, 0.6, nullptr) == TFMM_OK);
+        const bool one = entries + entries / 4 + 64 <= 1L << 24;
+        CHECK(fake.pass_launches == (one ? 1 : 0) && fake.emit_launches == (one ? 0 : 1) && fake.sized_passes == 0);
+        fake.pass_entries = 3000;
+        drop(t, c);
+    }
+}
+
 int main(int, char** argv) {
     for (const double& x : arrays) fake.user.insert(&x);
     const std::string what = argv[1];
@@ -234,6 +252,7 @@ int main(int, char** argv) {
     else if (what == "too_many_pairs") too_many_pairs();
     else if (what == "too_many_rows") too_many_rows();
     else if (what == "first_walk_memory") first_walk_memory();
+    else if (what == "pass_sizes") pass_sizes();
     else return 2;
     std::puts("host paths ok");
     return 0;

@@ -48,6 +48,8 @@ int main() {
     // as many particles as an ordinary leaf may hold: the count itself
     CHECK(source_step(1) == 1u && source_step(4095) == 4095u && source_step(4096) == 4096u);
     CHECK(source_step(4097) == 4096u && source_step(1 << 30) == 4096u);
+    // the counts of the largest pass in one launch, with every workgroup's share at its worst
+    CHECK(15 * (kPassMax / kPassGrid + 8) < (int64_t)1 << kCountBits && 3 * kCountBits <= 62);
     // the directed entries of the most pairs, and a loop's last step past them
     CHECK(lists_fit(0, 0) && lists_fit(kMaxPairs, kMaxPairs));
     CHECK(!lists_fit(kMaxPairs + 1, 0) && !lists_fit(0, kMaxPairs + 1) && !lists_fit((int64_t)1 << 31, 0));

@@ -12,7 +12,7 @@ import pytest
 ROOT = Path(__file__).resolve().parent.parent
 CSRC = ROOT / "paper_2107_07166_amd" / "csrc"
 CLANG = Path("/opt/rocm/llvm/bin/clang++")
-SCENARIOS = ["refused_memory", "wait_ran_out", "too_many_pairs", "too_many_rows", "first_walk_memory"]
+SCENARIOS = ["refused_memory", "wait_ran_out", "too_many_pairs", "too_many_rows", "first_walk_memory", "pass_sizes"]
 
 
 def _run(cmd):
