@@ -569,11 +569,13 @@ __global__ __launch_bounds__(kWave) void p2p_reduce_kernel(const int32_t* __rest
 // wavefronts per item: ball of 2048 (67 items) 409 / 362 / 365 us, Plummer
 // 5000 (300 items, four steps) 2660 / 2385 / 2314, Plummer 20011 in FP64 (2.9e3
 // items) 783 / 711 / 812, 16 sets of 131072 particles (5.7e3 items) 890 / 786 /
-// 832, Plummer 2^18 with the potential (1.7e4 items) 1776 / 1737.  Past that
-// the rounds' barriers cost more than the shorter tail gives; in FP64, with 12
-// wavefronts per compute unit, already at 1.7e4 items (2097 against 2178 us).
+// 832; one / four: Plummer 10^5 (conserving, order 4) 920 / 850, 2^18 (1.7e4 items)
+// 1256 / 1228.  Past that the rounds' barriers cost more than the shorter tail
+// gives: balls of 2e5 and 3e5 (1.7e4 and 1.8e4 items) even, Plummer 3.3e5 1379 /
+// 1440, 4.8e5 1786 / 1880; in FP64, with 12 wavefronts per compute unit, already
+// 1.3e5 even and 2^18 2097 / 2178.
 template <typename T>
-constexpr int64_t block_items() { return sizeof(T) == 4 ? 32768 : 8192; }
+constexpr int64_t block_items() { return sizeof(T) == 4 ? 18432 : 8192; }  // 72, 32 per compute unit
 constexpr int64_t kBlockItems8 = 512;
 
 template <typename T, bool POT>
