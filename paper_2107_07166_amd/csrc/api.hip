@@ -310,13 +310,16 @@ void evaluate_once(Tree& t, const tfmm_params* prm, const double* theta_sets, do
     };
     prepare_sources(t, prm->precision, s);
     // Of the two list chains the one queued second starts late by its sibling's
-    // launches.  Up to order 5 and 2^15 nodes the near field is what the end waits
-    // for, and its chain goes first: Plummer 2^18 with the potential 1351 -> 1325
-    // us, in FP64 1771 -> 1729, 5000 particles 1602 -> 1574.  Beyond, M2L gains
-    // more from its head start: 100000 particles at order 6 714 us against 730
-    // with the near chain first, a binary of 2^20 at order 4 1434 against 1473, a
-    // disk of 2^22 at order 6 6358 against 6489.
-    const bool near_first = pe <= 5 && t.n_nodes <= 32768;
+    // launches.  Up to 2^15 nodes and order 5 (4 where M2L is the conserving one in
+    // FP32, whose four polynomials take longer than the FP32 near field) the near
+    // field is what the end waits for, and its chain goes first.  Steps, far / near
+    // chain first: Plummer 4e5 at order 4 1490 / 1460 us, order 5 standard 1530 /
+    // 1480, FP64 2.5e5 at order 5 conserving 2200 / 2030.  Otherwise M2L gains more
+    // from its head start: conserving at order 5 in FP32 2e5 1235 / 1370, a ball of
+    // 4.5e5 1100 / 1200; standard at order 6 2e5 1175 / 1245; 5.2e5 (31000 nodes) at
+    // order 4 even.
+    const bool fast_near = ve == TFMM_CONSERVING && prm->precision == TFMM_MIXED32;
+    const bool near_first = pe <= (fast_near ? 4 : 5) && t.n_nodes <= 32768;
     if (need_walk) {
         t.walk_valid = false;
         if (t.timing) TFMM_HIP(hipEventRecord(t.ev[11], s));
