@@ -192,7 +192,7 @@ __global__ __launch_bounds__(LB) void l2l_level_kernel(int32_t b, int32_t e, con
 // the same order, so the result is the level launches' bit for bit and the
 // choice between the two may depend on the tree's size.  A shift is done once
 // per leaf below a node instead of once, but a level costs 3 to 4 us of latency
-// here against a launch of 11 us.  The conserving parts of a leaf are
+// here against a launch of 11 us (chain_runs).  The conserving parts of a leaf are
 // neighbouring lanes; P comes from part 0's lane.
 template <int P, int VAR>
 __global__ __launch_bounds__(LB) void l2l_chain_kernel(int64_t n_leaves, const int32_t* __restrict__ leaves,
@@ -257,11 +257,23 @@ __global__ __launch_bounds__(LB) void l2l_chain_kernel(int64_t n_leaves, const i
     for (int k = 0; k < NP; ++k) out[k] = acc[k];
 }
 
-// Trees of at most this many (leaf, part) threads run the chain, a round of
-// one wavefront on every SIMD: disk of 10^5 (p = 6, 2.5e3 leaves, conserving) 783 ->
-// 728 us per step, Plummer 2^18 with the raised scalar degree (7.3e3 leaves) 2737
-// -> 2670; the disk of 2^22 (1.2e5 leaves) would go from 6.78 to 6.87 ms.
-constexpr int64_t kChainThreads = 65536;
+// Trees of up to 65536 (leaf, part) threads run the chain, a round of one wavefront
+// on every SIMD.  L2L of Plummer spheres beside the near field, levels / chain: order 5
+// standard 269 leaves 29 / 21 us, 1754 52 / 25, 64376 90 / 37; order 6 conserving
+// 269 63 / 29, 13851 104 / 45; order 8 conserving 13851 513 / 148; the disk of 2^22
+// (1.2e5 leaves, order 6) would go from 6.78 to 6.87 ms.  The standard locals of
+// orders 7 and 8 do not fit a thread's registers.  At order 7 the chain, which
+// keeps a leaf's locals there from level to level, spills 700 and loses everywhere
+// (269 leaves 91 / 178 us, 5215 178 / 220, 64376 245 / 357).  At order 8, where one
+// level spills as much, it loses with few leaves and with many (269 348 / 383, 1754
+// 566 / 476, 26490 773 / 650, 46304 846 / 868, 64376 867 / 958).
+template <int P, int VAR>
+constexpr bool chain_runs(int64_t leaves) {
+    if (VAR == TFMM_CONSERVING) return 4 * leaves <= 65536;
+    if (P == 7) return false;
+    if (P == 8) return leaves >= 1024 && leaves <= 32768;
+    return leaves <= 65536;
+}
 
 struct LevelRange {
     int32_t b[kLevels + 2];
@@ -289,12 +301,15 @@ template <int P, int VAR>
 void l2l_levels(Tree& t, hipStream_t s) {
     constexpr int PARTS = VAR == TFMM_CONSERVING ? 4 : 1;
     constexpr int64_t kTopNodes = LB;
-    if (t.n_leaves * PARTS <= kChainThreads) {
-        hipLaunchKernelGGL((l2l_chain_kernel<P, VAR>), dim3((unsigned)cdiv(t.n_leaves * PARTS, LB)), dim3(LB), 0, s,
-                           t.n_leaves, t.leaves.as<int32_t>(), t.nd_parent.as<int32_t>(), t.nd_Z.as<double4>(),
-                           t.m2l_off.as<uint32_t>(), t.loc.as<double>(), t.loc_leaf.as<double>());
-        TFMM_LAUNCHED();
-        return;
+    if constexpr (VAR == TFMM_CONSERVING || P != 7) {
+        if (chain_runs<P, VAR>(t.n_leaves)) {
+            hipLaunchKernelGGL((l2l_chain_kernel<P, VAR>), dim3((unsigned)cdiv(t.n_leaves * PARTS, LB)), dim3(LB), 0,
+                               s, t.n_leaves, t.leaves.as<int32_t>(), t.nd_parent.as<int32_t>(),
+                               t.nd_Z.as<double4>(), t.m2l_off.as<uint32_t>(), t.loc.as<double>(),
+                               t.loc_leaf.as<double>());
+            TFMM_LAUNCHED();
+            return;
+        }
     }
     t.loc_has.ensure(t.ctx, (size_t)std::max<int64_t>(t.n_nodes, 1));
     int top = -1;
