@@ -29,7 +29,7 @@ __global__ __launch_bounds__(KB) void kick_kernel(int64_t n, double* __restrict_
 }
 
 // The kick that ends a step (if both), the one that starts the next, and its
-// drift: one launch between two force evaluations instead of three (eight steps
+// drift: one launch between two force evaluations instead of three (four steps
 // of 5000 particles, with the smaller sort and the single r_max launch of such sets,
 // 1690 -> 1657 us).
 __global__ __launch_bounds__(KB) void kick_drift_kernel(int64_t n, double* __restrict__ pos,

@@ -18,8 +18,8 @@
 // three passes, and deriving the bounds and prefixes in launches of their own,
 // this reads and writes them half as often and takes a third of the launches:
 // a solve of 2^11 particles 253 -> 223 us, of 2^18 1665 -> 1625 us, of 2^22
-// 6.83 -> 6.61 ms (order 3; 2^20 Plummer particles, where the near lists of the
-// halo hold one workgroup up, 3.19 ms both).
+// 6.83 -> 6.61 ms (disk, order 6; 2^20 Plummer particles, where the near lists of
+// the halo hold one workgroup up, 3.19 ms both).
 #include <algorithm>
 #include <cstddef>
 

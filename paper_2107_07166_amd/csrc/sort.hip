@@ -353,7 +353,9 @@ void radix_passes(Src src, K* kout, int32_t* vout, K* kalt, int32_t* valt, int64
             TFMM_LAUNCHED();
         };
         auto sized = [&](auto from, auto digit) {
-            if (n < kShortStatus) pass(uint32_t{}, from, digit);
+            // particles are always fewer
+            if constexpr (sizeof(K) == 8) pass(uint32_t{}, from, digit);
+            else if (n < kShortStatus) pass(uint32_t{}, from, digit);
             else pass((unsigned long long)0, from, digit);
         };
         // a later pass reads what the one before wrote, the other pair of arrays

@@ -806,7 +806,7 @@ __device__ __forceinline__ void geometry_inner(int32_t i, const int32_t* __restr
                                                const int32_t* __restrict__ nchild, double4* __restrict__ S,
                                                double4* __restrict__ Z) {
     const int32_t nc = nchild[i];
-    if (nc == 0) return;  // a leaf: done by geometry_leaf_kernel
+    if (nc == 0) return;  // a leaf: done by geometry_leaf
     double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
     const int32_t c0 = child_first[i];
     for (int32_t c = c0; c < c0 + nc; ++c) {
