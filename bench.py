@@ -55,8 +55,8 @@ P2P_FLOP_PER_PAIR = 20        # per directed particle interaction (convention)
 # factor a plain copy of known size reads) and WRITE_SIZE (x1); see
 # profiles/p2p_plummer1m_counters.md.  Valid only for the kernel source the
 # counters were taken with (first 16 hex digits of its sha256).
-P2P_TRAFFIC_BYTES = (2 * 144098 + 32322) * 1024
-P2P_TRAFFIC_SOURCE_SHA = "e2de8b9629187455"
+P2P_TRAFFIC_BYTES = (2 * 143623 + 32317) * 1024
+P2P_TRAFFIC_SOURCE_SHA = "2b908c529456bb2f"
 
 
 def _p2p_traffic():
