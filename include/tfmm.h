@@ -158,8 +158,10 @@ int tfmm_tree_walk(tfmm_tree *tree, double theta, void *stream);
  * -sum m_b (r^2 + eps^2)^(-1/2) plus the far field from the standard
  * expansion of Eq. taylor (potential coefficient L_0 included) truncated at
  * degree p, for every variant (the realigned variants change the forces,
- * not this potential).  It costs an extra far-field pass after the forces.  Asynchronous except for the walk
- * when params->theta differs from the tree's last walk.  Part of the work
+ * not this potential).  The standard variant takes it from the forces' own far
+ * field, the others make a far field of its own beside the near field.
+ * Asynchronous except for the walk when params->theta differs from the tree's
+ * last walk.  Part of the work
  * runs on a second stream owned by the tree, forked from `stream` at the call
  * and joined back into it before the forces are written, so the call is
  * ordered on `stream` like a single kernel.
